@@ -58,12 +58,17 @@ struct BF16 {
     static constexpr bool kSplit = true;
     __device__ static __forceinline__ void split(const float* v, frag_t& hi, frag_t& lo)
     {
+        // pairs share a conversion; the high parts come back out of the packed words
+        hi = pack(v);
+        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+        const u32x4_t w = __builtin_bit_cast(u32x4_t, hi);
+        float r[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint16_t h = f32_to_bf16(v[j]);
-            hi[j] = __builtin_bit_cast(__bf16, h);
-            lo[j] = __builtin_bit_cast(__bf16, f32_to_bf16(v[j] - bf16_to_f32(h)));
+        for (int j = 0; j < 4; ++j) {
+            r[2 * j] = v[2 * j] - __uint_as_float(w[j] << 16);
+            r[2 * j + 1] = v[2 * j + 1] - __uint_as_float(w[j] & 0xffff0000u);
         }
+        lo = pack(r);
     }
 };
 

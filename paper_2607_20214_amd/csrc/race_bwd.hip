@@ -45,9 +45,9 @@ struct LbArgs {
 template <class T, int D, int RP>
 struct Lb1Smem {
     using S = typename T::store_t;
-    S vt[D][kC + kPad];            // V chunk transposed
-    S dn[kC][D + kPad];            // dO chunk, rows (dNum_i = sc_lr,i dO_i: the products apply sc_lr)
-    S pk[kC][RP + kPad];           // Phi_K chunk, rows (Phi_K^T operands: transposed LDS reads)
+    S v[RowTile<T, D>::ELEMS];     // V chunk
+    S dn[RowTile<T, D>::ELEMS];    // dO chunk (dNum_i = sc_lr,i dO_i: the products apply sc_lr)
+    S pk[RowTile<T, RP>::ELEMS];   // Phi_K chunk
     S gg[kC][kC + kPad];           // G[i][j] = <dNum_i, V_j> + dDen_i, j <= i
     float ts[kC][RP / 4];          // tanh(W q) of the chunk's queries
     S du[kC][w_kdim<RP>() + kPad];
@@ -58,22 +58,22 @@ struct Lb1Smem {
 template <class T, int D, int RP>
 struct Lb2Smem {
     using S = typename T::store_t;
-    S vr[kC][D + kPad];            // V chunk, rows
-    S dnt[D][kC + kPad];           // dNum / L chunk, transposed
-    S pqt[RP][kC + kPad];          // Phi_Q transposed
+    S v[RowTile<T, D>::ELEMS];     // V chunk
+    S dn[RowTile<T, D>::ELEMS];    // dNum / L chunk
+    S pq[RowTile<T, RP>::ELEMS];   // Phi_Q chunk
     S ggt[kC][kC + kPad];          // G'[j][i] / L, i >= j
     float ts[kC][RP / 4];          // tanh(W k) of the chunk's keys
     S du[kC][w_kdim<RP>() + kPad];
-    float dden[kC];
-    float a_state[RP];             // dA = (1/L) sum phi(q) dDen of the queries after the chunk
+    Parts<T, kC> ddp;              // dDen / L as operand parts
+    float dden[kC];                // dDen / L
 };
 
 template <class T, int D, int RP>
 struct Lb3Smem {
     using S = typename T::store_t;
-    S dnt[D][kC + kPad];           // dNum / L chunk, transposed
-    S pk[kC][RP + kPad];           // Phi_K rows
-    S pq[kC][RP + kPad];           // Phi_Q rows (Phi_Q^T operands: transposed LDS reads)
+    S dn[RowTile<T, D>::ELEMS];    // dNum / L chunk
+    S pk[RowTile<T, RP>::ELEMS];   // Phi_K chunk
+    S pq[RowTile<T, RP>::ELEMS];   // Phi_Q chunk
     S mt[kC][kC + kPad];           // M'[j][i] = <phi(k_j), phi(q_i)>, i >= j
 };
 
@@ -117,6 +117,36 @@ __global__ __launch_bounds__(256) void race_wt_kernel(const float* W, typename T
     lo[((size_t)h * D + d) * WK + p] = T::store(T::kSplit ? w - T::load(vh) : 0.f);
 }
 
+// The state part of dphi' for the wave's feature tile in St (rows d, its
+// columns the tile's features) against the 64 rows of x: acc[t] = S' x_t for
+// the 16-row tiles t.  The state enters as hi + lo bf16 parts, split once per
+// chunk and k-step.
+template <class T, int D>
+__device__ __forceinline__ void state_product(const f32x4 (&St)[D / 16], const typename T::store_t* x, f32x4 (&acc)[4])
+{
+    using F = typename T::frag_t;
+    const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = f32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int ds = 0; ds < D / 32; ++ds) {
+        float sv[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sv[i] = St[2 * ds][i];
+            sv[4 + i] = St[2 * ds + 1][i];
+        }
+        F shi, slo;
+        T::split(sv, shi, slo);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const F bf = RowTile<T, D>::row44(x, 16 * t + col, 32 * ds + 4 * g);
+            acc[t] = T::mma(shi, bf, acc[t]);
+            if (T::kSplit) acc[t] = T::mma(slo, bf, acc[t]);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- LB1: dQ
 template <class T, int D, int RP>
 __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
@@ -125,7 +155,9 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
     using F = typename T::frag_t;
     constexpr int SPLIT = table_split<RP>(), RPW = RP / SPLIT;   // features of this workgroup
     constexpr int DT = D / 16, KS = D / 32, FT = RPW / 16, NFT = (FT + 3) / 4;
-    __shared__ Lb1Smem<T, D, RPW> sm;
+    using TV = RowTile<T, D>;
+    using TP = RowTile<T, RPW>;
+    __shared__ __attribute__((aligned(16))) Lb1Smem<T, D, RPW> sm;
     const int seg = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT, h = blockIdx.y, b = blockIdx.z;
     const int F0 = part * RPW, L = a.L - F0 / 16;                  // first feature; tables from here on
     const size_t bh = (size_t)b * a.H + h;
@@ -166,16 +198,15 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
         __syncthreads();
         // every global load of the chunk is issued first; the features (vector
         // work) run while they are in flight, then the rows go to LDS
-        StageR<T, D> sdn;
-        sdn.load(dO, t0, a.N, nullptr);
-        StageT<T, D> svt;
-        if (a.causal) svt.load(V, t0, a.N, nullptr, 1.f);
+        StageRows<T, D, false> sdn, sv;
+        sdn.load(dO, t0, a.N);
+        if (a.causal) sv.load(V, t0, a.N);
         const bool in = threadIdx.x < kC && t0 + (int)threadIdx.x < a.N;
         const float ddv = in ? dden[t0 + threadIdx.x] : 0.f, scv = in ? sclr[t0 + threadIdx.x] : 0.f;
-        features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, nullptr, nullptr, sm.ts);
-        if (a.causal) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk, nullptr, nullptr);
-        sdn.store(sm.dn, false);
-        if (a.causal) svt.store(sm.vt, false);
+        tanh_rows<RPW>(uq, sm.ts);
+        if (a.causal) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk);
+        sdn.store(sm.dn);
+        if (a.causal) sv.store(sm.v);
         if (threadIdx.x < kC) {
             sm.dden[threadIdx.x] = ddv;
             sm.sc[threadIdx.x] = scv;
@@ -194,14 +225,15 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
             // 16 w + col) so each lane stores four entries of its row at once
             const int qi = 16 * w + col;
             const float scq = sm.sc[qi], ddq = sm.dden[qi];
+            F df[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) df[ks] = TV::row8(sm.dn, qi, 32 * ks + 8 * g);
             for (int kt = 0; kt < 4; ++kt) {
                 f32x4 acc = {0, 0, 0, 0};
                 if (kt <= w) {
-                    // V rows of keys 16 kt .. 16 kt + 15 from the transposed chunk tile
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks)
-                        acc = T::mma(col8_t<T, kC + kPad>(sm.vt, 32 * ks, 16 * kt),
-                                     T::ld8(&sm.dn[16 * w + col][32 * ks + 8 * g]), acc);
+                        acc = T::mma(TV::row8(sm.v, 16 * kt + col, 32 * ks + 8 * g), df[ks], acc);
                 }
                 f32x4 v;
 #pragma unroll
@@ -211,61 +243,54 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
         }
         __syncthreads();
         // dphi(q)' tiles [features of table ft] x [16 queries]: sc_lr S dO + A dDen + intra
-        // (the state's hi / lo bf16 split is made once per chunk and k-step)
 #pragma unroll
         for (int j = 0; j < NFT; ++j) {
             const int ft = w + 4 * j;
             if (ft >= FT) break;
             f32x4 acc[4];
+            state_product<T, D>(St_[j], sm.dn, acc);
 #pragma unroll
-            for (int qt = 0; qt < 4; ++qt) acc[qt] = f32x4{0, 0, 0, 0};
-#pragma unroll
-            for (int ds = 0; ds < KS; ++ds) {
-                float sv[8];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sv[i] = St_[j][2 * ds][i];
-                    sv[4 + i] = St_[j][2 * ds + 1][i];
-                }
-                F shi, slo;
-                T::split(sv, shi, slo);
-#pragma unroll
-                for (int qt = 0; qt < 4; ++qt) {
-                    const F bf = T::ld44(&sm.dn[16 * qt + col][32 * ds + 4 * g],
-                                         &sm.dn[16 * qt + col][32 * ds + 16 + 4 * g]);
-                    acc[qt] = T::mma(shi, bf, acc[qt]);
-                    if (T::kSplit) acc[qt] = T::mma(slo, bf, acc[qt]);
-                }
-            }
             for (int qt = 0; qt < 4; ++qt) {
                 const float ddq = sm.dden[16 * qt + col], scq = sm.sc[16 * qt + col];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[qt][i] = acc[qt][i] * scq + Aacc[j][i] * ddq;
-                if (a.causal) {
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
-                        acc[qt] = T::mma(phi_t8<T, RPW>(sm.pk, 32 * kk, 16 * ft),
-                                         T::ld8(&sm.gg[16 * qt + col][32 * kk + 8 * g]), acc[qt]);
-                }
-                acc[qt] *= a.inv_L;
-                chain_rule_t<T, RPW>(acc[qt], qt, ft, L, a.beta, sm.ts, sm.du);
             }
+            if (a.causal) {
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    const F pf = TP::col8(sm.pk, 32 * kk, 16 * ft);
+#pragma unroll
+                    for (int qt = 0; qt < 4; ++qt)
+                        acc[qt] = T::mma(pf, T::ld8(&sm.gg[16 * qt + col][32 * kk + 8 * g]), acc[qt]);
+                }
+            }
+            // the four tiles' chain rules side by side: their exchanges overlap
+#pragma unroll
+            for (int qt = 0; qt < 4; ++qt)
+                chain_rule_t<T, RPW>(acc[qt], qt, ft, L, a.two_beta, a.two_beta * a.inv_L, sm.ts, sm.du);
         }
         __syncthreads();
         store_du<T, RPW, RP>(sm.du, du_out, t0, a.N);
         if (a.causal) {
-            // S' += V' Phi_K (chunk), A += Phi_K' 1 (one Phi_K^T fragment each)
+            // S' += V' Phi_K (chunk), A += Phi_K' 1
 #pragma unroll
-            for (int j = 0; j < NFT; ++j) {
-                const int ft = w + 4 * j;
-                if (ft >= FT) break;
+            for (int kk = 0; kk < 2; ++kk) {
+                F pf[NFT];
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    const F bf = phi_t8<T, RPW>(sm.pk, 32 * kk, 16 * ft);
+                for (int j = 0; j < NFT; ++j) {
+                    const int ft = w + 4 * j;
+                    if (ft >= FT) break;
+                    pf[j] = TP::col8(sm.pk, 32 * kk, 16 * ft);
+                    Aacc[j] = token_sums<T>(pf[j], Aacc[j]);
+                }
 #pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-                        St_[j][dt] = T::mma(T::ld8(&sm.vt[16 * dt + col][32 * kk + 8 * g]), bf, St_[j][dt]);
-                    Aacc[j] = token_sums<T>(bf, Aacc[j]);
+                for (int dt = 0; dt < DT; ++dt) {
+                    const F vf = TV::col8(sm.v, 32 * kk, 16 * dt);
+#pragma unroll
+                    for (int j = 0; j < NFT; ++j) {
+                        if (w + 4 * j >= FT) break;
+                        St_[j][dt] = T::mma(vf, pf[j], St_[j][dt]);
+                    }
                 }
             }
         }
@@ -280,7 +305,9 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
     using F = typename T::frag_t;
     constexpr int SPLIT = table_split<RP>(), RPW = RP / SPLIT;   // features of this workgroup
     constexpr int DT = D / 16, KS = D / 32, FT = RPW / 16, NFT = (FT + 3) / 4;
-    __shared__ Lb2Smem<T, D, RPW> sm;
+    using TV = RowTile<T, D>;
+    using TP = RowTile<T, RPW>;
+    __shared__ __attribute__((aligned(16))) Lb2Smem<T, D, RPW> sm;
     const int seg = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT, h = blockIdx.y, b = blockIdx.z;
     const int F0 = part * RPW, L = a.L - F0 / 16;                  // first feature; tables from here on
     const size_t bh = (size_t)b * a.H + h;
@@ -296,9 +323,10 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
 
     for (int it = threadIdx.x; it < kC * (w_kdim<RPW>() + kPad); it += kThreads)
         (&sm.du[0][0])[it] = T::store(0.f);
-    f32x4 St_[NFT][DT];
+    // the suffix state of the wave's feature tiles, as in the dQ pass:
+    // dS'[d][f], and dA[f] = (1/L) sum phi(q) dDen of the queries after the chunk
+    f32x4 St_[NFT][DT], Aacc[NFT];
     const float* st_in = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
-    for (int f = threadIdx.x; f < RPW; f += kThreads) sm.a_state[f] = st_in[RP * D + F0 + f];
 #pragma unroll
     for (int j = 0; j < NFT; ++j) {
         const int ft = w + 4 * j;
@@ -307,6 +335,8 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 St_[j][dt][i] = ft < FT ? st_in[(size_t)(F0 + 16 * ft + col) * D + 16 * dt + 4 * g + i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Aacc[j][i] = ft < FT ? st_in[RP * D + F0 + 16 * ft + 4 * g + i] : 0.f;
     }
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
@@ -318,17 +348,22 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
-        StageR<T, D> svr;
-        svr.load(V, t0, a.N, nullptr);
-        StageT<T, D> sdn;
-        if (a.causal) sdn.load(dO, t0, a.N, sclr, a.inv_L);
+        StageRows<T, D, false> svr;
+        StageRows<T, D, true> sdn;
+        svr.load(V, t0, a.N);
+        if (a.causal) sdn.load(dO, t0, a.N, sclr);
         const bool in = threadIdx.x < kC && t0 + (int)threadIdx.x < a.N;
-        const float ddv = in ? dden[t0 + threadIdx.x] : 0.f;
-        features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, nullptr, nullptr, sm.ts);
-        if (a.causal) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, nullptr, sm.pqt, nullptr);
-        svr.store(sm.vr, false);
-        if (a.causal) sdn.store(sm.dnt, true);
-        if (threadIdx.x < kC) sm.dden[threadIdx.x] = ddv;
+        const float ddv = in ? dden[t0 + threadIdx.x] * a.inv_L : 0.f;
+        tanh_rows<RPW>(uk, sm.ts);
+        if (a.causal) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, sm.pq);
+        svr.store(sm.v);
+        if (a.causal) {
+            sdn.store(sm.dn, a.inv_L);
+            if (threadIdx.x < kC) {
+                sm.dden[threadIdx.x] = ddv;
+                sm.ddp.put(threadIdx.x, ddv);
+            }
+        }
         __syncthreads();
         {
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
@@ -341,79 +376,70 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
             // i >= j, formed transposed (lane (g, col): queries 16 it + 4 g + i
             // of key 16 w + col) so each lane stores four entries of its row at once
             const int kj = 16 * w + col;
+            F vf[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) vf[ks] = TV::row8(sm.v, kj, 32 * ks + 8 * g);
             for (int it = 0; it < 4; ++it) {
                 f32x4 acc = {0, 0, 0, 0};
                 if (it >= w) {
-                    // dNum / L rows of queries 16 it .. 16 it + 15 from the transposed chunk tile
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks)
-                        acc = T::mma(col8_t<T, kC + kPad>(sm.dnt, 32 * ks, 16 * it),
-                                     T::ld8(&sm.vr[16 * w + col][32 * ks + 8 * g]), acc);
+                        acc = T::mma(TV::row8(sm.dn, 16 * it + col, 32 * ks + 8 * g), vf[ks], acc);
                 }
                 const f32x4 dd = *(const f32x4*)&sm.dden[16 * it + 4 * g];
                 f32x4 v;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = 16 * it + 4 * g + i >= kj ? acc[i] + dd[i] * a.inv_L : 0.f;
+                for (int i = 0; i < 4; ++i) v[i] = 16 * it + 4 * g + i >= kj ? acc[i] + dd[i] : 0.f;
                 store4<T>(&sm.ggt[kj][16 * it + 4 * g], v);
             }
         }
         __syncthreads();
         // dphi(k)' tiles [features of table ft] x [16 keys]: dS V + dA + intra
-        // (the state's hi / lo bf16 split is made once per chunk and k-step)
 #pragma unroll
         for (int j = 0; j < NFT; ++j) {
             const int ft = w + 4 * j;
             if (ft >= FT) break;
             f32x4 acc[4];
+            state_product<T, D>(St_[j], sm.v, acc);
 #pragma unroll
-            for (int kt = 0; kt < 4; ++kt) acc[kt] = f32x4{0, 0, 0, 0};
+            for (int kt = 0; kt < 4; ++kt) acc[kt] += Aacc[j];
+            if (a.causal) {
 #pragma unroll
-            for (int ds = 0; ds < KS; ++ds) {
-                float sv[8];
+                for (int kk = 0; kk < 2; ++kk) {
+                    const F pf = TP::col8(sm.pq, 32 * kk, 16 * ft);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sv[i] = St_[j][2 * ds][i];
-                    sv[4 + i] = St_[j][2 * ds + 1][i];
-                }
-                F shi, slo;
-                T::split(sv, shi, slo);
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    const F bf = T::ld44(&sm.vr[16 * kt + col][32 * ds + 4 * g],
-                                         &sm.vr[16 * kt + col][32 * ds + 16 + 4 * g]);
-                    acc[kt] = T::mma(shi, bf, acc[kt]);
-                    if (T::kSplit) acc[kt] = T::mma(slo, bf, acc[kt]);
+                    for (int kt = 0; kt < 4; ++kt)
+                        acc[kt] = T::mma(pf, T::ld8(&sm.ggt[16 * kt + col][32 * kk + 8 * g]), acc[kt]);
                 }
             }
-            for (int kt = 0; kt < 4; ++kt) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[kt][i] += sm.a_state[16 * ft + 4 * g + i];
-                if (a.causal) {
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
-                        acc[kt] = T::mma(T::ld8(&sm.pqt[16 * ft + col][32 * kk + 8 * g]),
-                                         T::ld8(&sm.ggt[16 * kt + col][32 * kk + 8 * g]), acc[kt]);
-                }
-                chain_rule_t<T, RPW>(acc[kt], kt, ft, L, a.beta, sm.ts, sm.du);
-            }
+            for (int kt = 0; kt < 4; ++kt)
+                chain_rule_t<T, RPW>(acc[kt], kt, ft, L, a.two_beta, a.two_beta, sm.ts, sm.du);
         }
         __syncthreads();
         store_du<T, RPW, RP>(sm.du, du_out, t0, a.N);
         if (a.causal) {
             // dS' += (dNum / L)' Phi_Q (chunk), dA += (1/L) Phi_Q' dDen
 #pragma unroll
-            for (int j = 0; j < NFT; ++j) {
-                const int ft = w + 4 * j;
-                if (ft >= FT) break;
+            for (int kk = 0; kk < 2; ++kk) {
+                F pf[NFT];
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    const F bf = T::ld8(&sm.pqt[16 * ft + col][32 * kk + 8 * g]);
+                for (int j = 0; j < NFT; ++j) {
+                    const int ft = w + 4 * j;
+                    if (ft >= FT) break;
+                    pf[j] = TP::col8(sm.pq, 32 * kk, 16 * ft);
+                    Aacc[j] = sm.ddp.mma_b(pf[j], 32 * kk + 8 * g, Aacc[j]);
+                }
 #pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-                        St_[j][dt] = T::mma(T::ld8(&sm.dnt[16 * dt + col][32 * kk + 8 * g]), bf, St_[j][dt]);
+                for (int dt = 0; dt < DT; ++dt) {
+                    const F df = TV::col8(sm.dn, 32 * kk, 16 * dt);
+#pragma unroll
+                    for (int j = 0; j < NFT; ++j) {
+                        if (w + 4 * j >= FT) break;
+                        St_[j][dt] = T::mma(df, pf[j], St_[j][dt]);
+                    }
                 }
             }
-            add_chunk_sums<T, RPW>(sm.pqt, sm.dden, a.inv_L, sm.a_state);
         }
     }
 }
@@ -425,7 +451,9 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
     using St = typename T::store_t;
     using F = typename T::frag_t;
     constexpr int DW = D / 64, FS = RP / 32;
-    __shared__ Lb3Smem<T, D, RP> sm;
+    using TV = RowTile<T, D>;
+    using TP = RowTile<T, RP>;
+    __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP> sm;
     const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const size_t bh = (size_t)b * a.H + h;
     const float* Uq = a.Uq + bh * a.N * (RP / 4);
@@ -455,12 +483,12 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
-        StageT<T, D> sdn;
-        if (a.causal) sdn.load(dO, t0, a.N, sclr, a.inv_L);
-        features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk, nullptr, nullptr);
+        StageRows<T, D, true> sdn;
+        if (a.causal) sdn.load(dO, t0, a.N, sclr);
+        features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk);
         if (a.causal) {
-            features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq, nullptr, nullptr);
-            sdn.store(sm.dnt, true);
+            features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq);
+            sdn.store(sm.dn, a.inv_L);
         }
         __syncthreads();
         {
@@ -474,13 +502,15 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
             // formed transposed (lane (g, col): queries 16 it + 4 g + i of key
             // 16 w + col) so each lane stores four entries of its row at once
             const int kj = 16 * w + col;
+            F kf[FS];
+#pragma unroll
+            for (int fs = 0; fs < FS; ++fs) kf[fs] = TP::row8(sm.pk, kj, 32 * fs + 8 * g);
             for (int it = 0; it < 4; ++it) {
                 f32x4 acc = {0, 0, 0, 0};
                 if (it >= w) {
 #pragma unroll
                     for (int fs = 0; fs < FS; ++fs)
-                        acc = T::mma(T::ld8(&sm.pq[16 * it + col][32 * fs + 8 * g]),
-                                     T::ld8(&sm.pk[16 * w + col][32 * fs + 8 * g]), acc);
+                        acc = T::mma(TP::row8(sm.pq, 16 * it + col, 32 * fs + 8 * g), kf[fs], acc);
                 }
                 f32x4 v;
 #pragma unroll
@@ -509,7 +539,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
             }
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) {
-                const F bf = T::ld44(&sm.pk[16 * kt + col][32 * fs + 4 * g], &sm.pk[16 * kt + col][32 * fs + 16 + 4 * g]);
+                const F bf = TP::row44(sm.pk, 16 * kt + col, 32 * fs + 4 * g);
 #pragma unroll
                 for (int j = 0; j < DW; ++j) {
                     accs[kt][j] = T::mma(shi[j], bf, accs[kt][j]);
@@ -518,35 +548,36 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
             }
         }
         // dV^T: lane (g, col) holds d = 16 (w DW + j) + 4 g + i of key 16 kt + col
+        F bv[2][DW];                     // (dNum / L)^T operands: the intra-chunk part and the state update
+        if (a.causal) {
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            f32x4 (&acc)[DW] = accs[kt];
-            if (a.causal) {
+            for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
+                for (int j = 0; j < DW; ++j) bv[kk][j] = TV::col8(sm.dn, 32 * kk, 16 * (w * DW + j));
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt) {
                     const F bf = T::ld8(&sm.mt[16 * kt + col][32 * kk + 8 * g]);
 #pragma unroll
-                    for (int j = 0; j < DW; ++j)
-                        acc[j] = T::mma(T::ld8(&sm.dnt[16 * (w * DW + j) + col][32 * kk + 8 * g]), bf, acc[j]);
+                    for (int j = 0; j < DW; ++j) accs[kt][j] = T::mma(bv[kk][j], bf, accs[kt][j]);
                 }
             }
+        }
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
             const int tok = t0 + 16 * kt + col;
             if (tok < a.N)
 #pragma unroll
-                for (int j = 0; j < DW; ++j) store4<T>(out + (size_t)tok * D + 16 * (w * DW + j) + 4 * g, acc[j]);
+                for (int j = 0; j < DW; ++j) store4<T>(out + (size_t)tok * D + 16 * (w * DW + j) + 4 * g, accs[kt][j]);
         }
         if (a.causal) {
             // dS += Phi_Q' (dNum / L) (chunk)
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
-                F bv[DW];
-#pragma unroll
-                for (int j = 0; j < DW; ++j) bv[j] = T::ld8(&sm.dnt[16 * (w * DW + j) + col][32 * kk + 8 * g]);
 #pragma unroll
                 for (int ft = 0; ft < RP / 16; ++ft) {
-                    const F af = phi_t8<T, RP>(sm.pq, 32 * kk, 16 * ft);
+                    const F af = TP::col8(sm.pq, 32 * kk, 16 * ft);
 #pragma unroll
-                    for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[j], S[ft][j]);
+                    for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[kk][j], S[ft][j]);
                 }
             }
         }

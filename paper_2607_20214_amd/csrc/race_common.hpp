@@ -9,6 +9,7 @@
 // wave w handles tokens 16w .. 16w+15 of a chunk when computing features.
 #pragma once
 #include "common.hpp"
+#include "tile.hpp"
 
 namespace elsaa {
 namespace race {
@@ -36,39 +37,49 @@ __device__ __forceinline__ float tanh_abs(float u)
     return 1.f - 2.f * __builtin_amdgcn_rcpf(1.f + __expf(2.f * u));
 }
 
-// 8-slot operand fragment from a tile stored transposed, xt[k][n] (row
-// stride LD elements): lane (i = lane % 16, g = lane / 16) receives column
-// c0 + i at rows kb + 8 g + j, j = 0..7 (16-bit: two transposed LDS reads).
-template <class T, int LD>
-__device__ __forceinline__ typename T::frag_t col8_t(const typename T::store_t (*xt)[LD], int kb, int c0)
-{
-    const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
-    const int r = kb + 8 * g;
-    if constexpr (T::bytes == 2) {
-        const bf16x4 lo = lds_read_tr4((const uint16_t*)&xt[r + (i >> 2)][c0 + 4 * (i & 3)]);
-        const bf16x4 hi = lds_read_tr4((const uint16_t*)&xt[r + 4 + (i >> 2)][c0 + 4 * (i & 3)]);
-        return typename T::frag_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    } else {
-        typename T::frag_t f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = xt[r + j][c0 + i];
-        return f;
+// A chunk's 64 rows of W elements in LDS, row-major, the rows in tile.hpp's
+// slot order: 16-byte reads of 16 rows, transposed reads and 16-byte stores
+// all hit distinct banks, so a chunk is staged once as whole rows and read
+// in both orientations (no transposed copy: storing one took about 70 vector
+// instructions and twelve 4-byte stores per 16 KB chunk and wave).
+template <class T, int W>
+struct RowTile {
+    using S = typename T::store_t;
+    using F = typename T::frag_t;
+    static constexpr int LD = W + kPad, ELEMS = kC * LD;
+    __device__ static __forceinline__ int row(int r) { return tile::slot_of(r) * LD; }
+    // elements [e0, e0 + 8) of row r
+    __device__ static __forceinline__ F row8(const S* t, int r, int e0) { return T::ld8(t + row(r) + e0); }
+    // elements e0 .. e0 + 3 and e0 + 16 .. e0 + 19 of row r (the k order of
+    // two accumulator tiles used as one operand)
+    __device__ static __forceinline__ F row44(const S* t, int r, int e0)
+    {
+        const S* p = t + row(r) + e0;
+        return T::ld44(p, p + 16);
     }
-}
-
-// Phi^T operand fragment from a row-major feature tile ph[token][feature]:
-// lane (i, g) receives feature f0 + i at tokens kb + 8 g + j (transposed LDS
-// reads, so no transposed copy of the tile is kept).
-template <class T, int RP>
-__device__ __forceinline__ typename T::frag_t phi_t8(const typename T::store_t (*ph)[RP + kPad], int kb, int f0)
-{
-    return col8_t<T, RP + kPad>(ph, kb, f0);
-}
+    // transposed operand: lane (i = lane % 16, g = lane / 16) receives column
+    // c0 + i at rows kb + 8 g + j, j = 0..7
+    __device__ static __forceinline__ F col8(const S* t, int kb, int c0)
+    {
+        const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+        const int r = kb + 8 * g;
+        if constexpr (T::bytes == 2) {
+            const bf16x4 lo = lds_read_tr4((const uint16_t*)(t + row(r + (i >> 2)) + c0 + 4 * (i & 3)));
+            const bf16x4 hi = lds_read_tr4((const uint16_t*)(t + row(r + 4 + (i >> 2)) + c0 + 4 * (i & 3)));
+            return F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        } else {
+            F f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = t[row(r + j) + c0 + i];
+            return f;
+        }
+    }
+};
 
 // Sums over 32 of the chunk's tokens on the matrix cores: Phi^T x 1 (every
 // entry of the B operand 1), so every lane of the product tile holds the
 // sums of its rows' features: lane (g, col) register i += sum over tokens
-// kb .. kb + 31 of phi_{f0 + 4g + i} (phit from phi_t8 at feature f0).
+// kb .. kb + 31 of phi_{f0 + 4g + i} (phit: the tile's col8 at feature f0).
 template <class T>
 __device__ __forceinline__ f32x4 token_sums(typename T::frag_t phit, f32x4 acc)
 {
@@ -76,31 +87,37 @@ __device__ __forceinline__ f32x4 token_sums(typename T::frag_t phit, f32x4 acc)
     return T::mma(phit, T::pack(one), acc);
 }
 
-// a_state[f] += scale * sum over the chunk's tokens k of xt[f][k] (* wk[k] when
-// wk is not null), xt a transposed feature tile [RP][kC + kPad]; all threads,
-// 256 / RP per feature (16-byte LDS reads, then a lane reduction).
-template <class T, int RP>
-__device__ __forceinline__ void add_chunk_sums(const typename T::store_t (*xt)[kC + kPad], const float* wk,
-                                               float scale, float* a_state)
-{
-    constexpr int TPF = RP >= kThreads ? 1 : kThreads / RP;   // threads per feature
-    constexpr int PER = kC / TPF;                               // tokens per thread
-    static_assert(PER % 8 == 0, "chunk split");
-    for (int f0 = 0; f0 < RP; f0 += kThreads / TPF) {
-        const int f = f0 + (int)threadIdx.x / TPF, part = threadIdx.x % TPF;
-        float s = 0.f;
+// float32 values as matrix-core operands without loss: bf16 storage keeps
+// v = p0 + p1 + p2, three bf16 parts (8 mantissa bits each), float32 storage
+// keeps v itself.  Split once where the value is produced, then read as
+// operand fragments (elements [e0, e0 + 8), the same for every column).
+template <class T, int N>
+struct Parts {
+    using S = typename T::store_t;
+    static constexpr int P = T::kSplit ? 3 : 1;
+    S v[P][N];
+    __device__ __forceinline__ void put(int i, float x)
+    {
 #pragma unroll
-        for (int k8 = 0; k8 < PER; k8 += 8) {
-            const int k = part * PER + k8;
-            const auto v = T::ld8(&xt[f][k]);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += wk ? (float)v[j] * wk[k + j] : (float)v[j];
+        for (int p = 0; p < P; ++p) {
+            const S s = T::store(x);
+            v[p][i] = s;
+            x -= T::load(s);
         }
-#pragma unroll
-        for (int m = 1; m < TPF; m <<= 1) s += __shfl_xor(s, m);
-        if (part == 0) a_state[f] += s * scale;
     }
-}
+    __device__ __forceinline__ f32x4 mma_b(typename T::frag_t a, int e0, f32x4 acc) const
+    {
+#pragma unroll
+        for (int p = P - 1; p >= 0; --p) acc = T::mma(a, T::ld8(&v[p][e0]), acc);
+        return acc;
+    }
+    __device__ __forceinline__ f32x4 mma_a(int e0, typename T::frag_t b, f32x4 acc) const
+    {
+#pragma unroll
+        for (int p = P - 1; p >= 0; --p) acc = T::mma(T::ld8(&v[p][e0]), b, acc);
+        return acc;
+    }
+};
 
 // projection count padded to whole 32-wide k-steps (backward du x W)
 template <int RP> constexpr int w_kdim() { return RP / 4 < 32 ? 32 : RP / 4; }
@@ -112,128 +129,57 @@ template <int RP> constexpr int w_kdim() { return RP / 4 < 32 ? 32 : RP / 4; }
 // so a workgroup's registers and LDS are those of the 128-feature passes.
 template <int RP> constexpr int table_split() { return RP == 256 ? 2 : 1; }
 
-// Rows [t0, t0 + 64) of X (zero past N), each multiplied by scale[row] * mul
-// when scale != nullptr (by mul otherwise), into a transposed tile
-// xt[d][token].  load() issues every global load of the thread into
-// registers and store() writes them to LDS, so a caller can load the next
-// chunk while the current one is consumed; stage_t does both at once.
-template <class T, int D>
-struct StageT {
+// Rows [t0, t0 + 64) of X (zero past N) into a RowTile, each multiplied by
+// scale[row] * mul when SCALED.  load() issues every global load of the
+// thread into registers (16 or 8 consecutive lanes cover a row) and store()
+// writes them to LDS, so the loads fly while the chunk's features are formed.
+// Rows past N are loaded clamped to row N - 1 and zeroed in store(), so the
+// loads carry no per-lane branches and later waits count exactly.
+template <class T, int D, bool SCALED>
+struct StageRows {
     using S = typename T::store_t;
-    static constexpr int PER = 16 / T::bytes;
-    static constexpr int CH = D / PER;
-    static constexpr int ITEMS = (kC / 2) * CH, PT = ITEMS / kThreads;
-    static_assert(ITEMS % kThreads == 0, "staging split");
-    uint4 va[PT], vb[PT];
-    float sa[PT], sb[PT];   // row scales as loaded (mul is applied in store())
-    float mul_;
-    int t0_, n_;
-    // Rows past N are loaded clamped to row N - 1 and zeroed in store(), so
-    // the loads carry no per-lane branches and later waits count exactly.
-    __device__ __forceinline__ void load(const S* X, int t0, int N, const float* scale, float mul)
-    {
-        t0_ = t0;
-        n_ = N;
-        mul_ = mul;
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int it = threadIdx.x + j * kThreads;
-            const int p = it & (kC / 2 - 1), c = it / (kC / 2);
-            const int r0 = min(t0 + 2 * p, N - 1), r1 = min(t0 + 2 * p + 1, N - 1);
-            va[j] = ldg16(X + (size_t)r0 * D + c * PER);
-            vb[j] = ldg16(X + (size_t)r1 * D + c * PER);
-            sa[j] = scale ? scale[r0] : 1.f;
-            sb[j] = scale ? scale[r1] : 1.f;
-        }
-    }
-    // the two rows of an item are adjacent in the transposed tile: one
-    // store per element pair
-    __device__ __forceinline__ void store(S (*xt)[kC + kPad], bool scaled) const
-    {
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int it = threadIdx.x + j * kThreads;
-            const int p = it & (kC / 2 - 1), c = it / (kC / 2);
-            const bool in0 = t0_ + 2 * p < n_, in1 = t0_ + 2 * p + 1 < n_;
-            const S* ea = (const S*)&va[j];
-            const S* eb = (const S*)&vb[j];
-#pragma unroll
-            for (int e = 0; e < PER; ++e) {
-                S x0 = in0 ? ea[e] : T::store(0.f), x1 = in1 ? eb[e] : T::store(0.f);
-                if (scaled) {
-                    x0 = T::store(T::load(x0) * (sa[j] * mul_));
-                    x1 = T::store(T::load(x1) * (sb[j] * mul_));
-                }
-                S* dst = &xt[c * PER + e][2 * p];
-                if constexpr (T::bytes == 2)
-                    *(uint32_t*)dst = (uint32_t)x0 | ((uint32_t)x1 << 16);
-                else
-                    *(float2*)dst = make_float2(x0, x1);
-            }
-        }
-    }
-};
-
-template <class T, int D>
-__device__ void stage_t(typename T::store_t (*xt)[kC + kPad], const typename T::store_t* X,
-                        int t0, int N, const float* scale = nullptr, float mul = 1.f)
-{
-    StageT<T, D> st;
-    st.load(X, t0, N, scale, mul);
-    st.store(xt, scale || mul != 1.f);
-}
-
-// Rows [t0, t0 + 64) of X (zero past N), optionally scaled per row, row-major;
-// load() / store() as in StageT, stage_r does both.
-template <class T, int D>
-struct StageR {
-    using S = typename T::store_t;
+    using Tl = RowTile<T, D>;
     static constexpr int PER = 16 / T::bytes;
     static constexpr int CH = D / PER;
     static constexpr int ITEMS = kC * CH, PT = ITEMS / kThreads;
     static_assert(ITEMS % kThreads == 0, "staging split");
     uint4 v[PT];
-    float sc[PT];
+    float sc[SCALED ? PT : 1];
     int t0_, n_;
-    // rows past N: loaded clamped, zeroed in store() (see StageT)
-    __device__ __forceinline__ void load(const S* X, int t0, int N, const float* scale)
+    __device__ __forceinline__ void load(const S* X, int t0, int N, const float* scale = nullptr)
     {
         t0_ = t0;
         n_ = N;
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
             const int it = threadIdx.x + j * kThreads;
-            const int row = it % kC, c = it / kC;
-            const int r = min(t0 + row, N - 1);
-            v[j] = ldg16(X + (size_t)r * D + c * PER);
-            sc[j] = scale ? scale[r] : 0.f;
+            const int r = min(t0 + it / CH, N - 1);
+            v[j] = ldg16(X + (size_t)r * D + (it % CH) * PER);
+            if constexpr (SCALED) sc[j] = scale[r];
         }
     }
-    __device__ __forceinline__ void store(S (*x)[D + kPad], bool scaled)
+    __device__ __forceinline__ void store(S* t, float mul = 1.f)
     {
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
             const int it = threadIdx.x + j * kThreads;
-            const int row = it % kC, c = it / kC;
-            if (t0_ + row >= n_) v[j] = make_uint4(0, 0, 0, 0);
-            if (scaled) {
-                S* e = (S*)&v[j];
+            const int r = it / CH;
+            if (t0_ + r >= n_) v[j] = make_uint4(0, 0, 0, 0);
+            S* dst = t + Tl::row(r) + (it % CH) * PER;
+            if constexpr (SCALED) {
+                const float f = sc[j] * mul;
+                const S* e = (const S*)&v[j];
+                float x[PER];
 #pragma unroll
-                for (int q = 0; q < PER; ++q) e[q] = T::store(T::load(e[q]) * sc[j]);
+                for (int q = 0; q < PER; ++q) x[q] = T::load(e[q]) * f;
+                if constexpr (T::bytes == 2) *(typename T::frag_t*)dst = T::pack(x);
+                else *(f32x4*)dst = f32x4{x[0], x[1], x[2], x[3]};
+            } else {
+                *(uint4*)dst = v[j];
             }
-            *(uint4*)&x[row][c * PER] = v[j];
         }
     }
 };
-
-template <class T, int D>
-__device__ void stage_r(typename T::store_t (*x)[D + kPad], const typename T::store_t* X, int t0,
-                        int N, const float* scale = nullptr)
-{
-    StageR<T, D> st;
-    st.load(X, t0, N, scale);
-    st.store(x, scale != nullptr);
-}
 
 // Projections t = tanh(u) of the tables this lane handles for chunk tokens
 // [t0 + 16w, t0 + 16w + 16) (table tb = g + 4 m of token 16w + col), loaded
@@ -261,68 +207,64 @@ struct URegs {
 };
 
 // Features of chunk tokens [t0 + 16w, t0 + 16w + 16) for every table, from
-// the projections t = tanh(u) in ur (URegs::load of the same chunk).
-// Writes phi (as T) row-major into ph[token][feature] and/or transposed into
-// pht[feature][token], and t into ts[token][4 * table + bit].
+// the projections t = tanh(u) in ur (URegs::load of the same chunk), into a
+// feature RowTile (zero for padded tables and rows past N).
 template <class T, int RP>
-__device__ void features_from(const URegs<RP>& ur, int t0, int N, int L, float two_beta,
-                              typename T::store_t (*ph)[RP + kPad], typename T::store_t (*pht)[kC + kPad],
-                              float (*ts)[RP / 4])
+__device__ __forceinline__ void features_from(const URegs<RP>& ur, int t0, int N, int L, float two_beta,
+                                              typename T::store_t* ph)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int g = lane >> 4, col = lane & 15;
     const int tl = 16 * wv + col;
-    const int tok = t0 + tl;
 #pragma unroll
     for (int m = 0; m < URegs<RP>::NU; ++m) {   // this lane: table tb of token tl
         const int tb = g + 4 * m;
         if (tb >= RP / 16) break;
         const f32x4 t = ur.u[m];                 // t = tanh(W x), formed by the projection pass
-        const bool live = tb < L && tok < N;
+        const bool live = tb < L && t0 + tl < N;
         float sp[4], sn[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) sigmoid_pair(two_beta * t[i], sp[i], sn[i]);
-        if (ts) *(f32x4*)&ts[tl][4 * tb] = f32x4{t[0], t[1], t[2], t[3]};
+        sp[3] = live ? sp[3] : 0.f;              // every product has one of these two factors
+        sn[3] = live ? sn[3] : 0.f;
         float phi[16];
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const float v = ((c & 1) ? sp[0] : sn[0]) * ((c & 2) ? sp[1] : sn[1]) *
-                            ((c & 4) ? sp[2] : sn[2]) * ((c & 8) ? sp[3] : sn[3]);
-            phi[c] = live ? v : 0.f;
-        }
-        if (ph) {
-            using F = typename T::frag_t;
-            *(F*)&ph[tl][16 * tb] = T::pack(phi);
-            *(F*)&ph[tl][16 * tb + 8] = T::pack(phi + 8);
-        }
-        if (pht) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c) pht[16 * tb + c][tl] = T::store(phi[c]);
-        }
+        for (int c = 0; c < 16; ++c)
+            phi[c] = (((c & 1) ? sp[0] : sn[0]) * ((c & 2) ? sp[1] : sn[1])) *
+                     (((c & 4) ? sp[2] : sn[2]) * ((c & 8) ? sp[3] : sn[3]));
+        using F = typename T::frag_t;
+        typename T::store_t* dst = ph + RowTile<T, RP>::row(tl) + 16 * tb;
+        *(F*)dst = T::pack(phi);
+        *(F*)(dst + 8) = T::pack(phi + 8);
     }
 }
 
-// features_from with the projections loaded on the spot.
-template <class T, int RP>
-__device__ void features(const float* U, int t0, int N, int L, float two_beta,
-                         typename T::store_t (*ph)[RP + kPad], typename T::store_t (*pht)[kC + kPad],
-                         float (*ts)[RP / 4])
+// t = tanh(u) of the same tokens and tables into ts[token][4 * table + bit]
+// (the chain rule's input).
+template <int RP>
+__device__ __forceinline__ void tanh_rows(const URegs<RP>& ur, float (*ts)[RP / 4])
 {
-    URegs<RP> ur;
-    ur.load(U, t0, N);
-    features_from<T, RP>(ur, t0, N, L, two_beta, ph, pht, ts);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int g = lane >> 4, tl = 16 * wv + (lane & 15);
+#pragma unroll
+    for (int m = 0; m < URegs<RP>::NU; ++m)
+        if (g + 4 * m < RP / 16) *(f32x4*)&ts[tl][4 * (g + 4 * m)] = ur.u[m];
 }
 
 // Chain rule from a transposed feature-gradient tile to the projection
 // gradients du.  dphi: accumulator tile of the 16 features of table tb x 16
 // rows (lane (g, col) register i holds feature c = 4g + i of row
-// 16*qt + col).  With phi_c = prod_b sigmoid(2 beta v_cb t_b), t = tanh(u):
-//   dt_b = beta * sum_c dphi_c phi_c (v_cb - tanh(beta t_b)),  du_b = dt_b (1 - t_b^2)
-// (tanh(beta t_b) = sigmoid(2 beta t_b) - sigmoid(-2 beta t_b) is the mean of
-// v_cb under phi).  Sums over c: 4 registers, then the 4 lane groups.  Lane
-// group g writes du[row][4 tb + g] (zero for padded tables).
+// 16*qt + col).  phi_c = prod_b s_b(v_cb) with s_b(+1) = sigmoid(2 beta t_b),
+// s_b(-1) = sigmoid(-2 beta t_b), so by the product rule
+//   du_b = 2 beta s_b(1) s_b(-1) (1 - t_b^2) T_b,
+//   T_b  = sum_c v_cb dphi_c prod_{b' != b} s_b'(v_cb').
+// Bits 0, 1 of c are i, bits 2, 3 are g: each lane forms its four registers'
+// share of the four T_b, and the four lane groups' shares are summed so that
+// group b ends with T_b: two swaps of two different values give both halves
+// of the sums at once (three exchanges in all).  Lane group g writes
+// mul * du_b / (2 beta) into du[row][4 tb + g] (zero for padded tables).
 template <class T, int RP>
-__device__ __forceinline__ void chain_rule_t(f32x4 dphi, int qt, int tb, int L, float beta,
+__device__ __forceinline__ void chain_rule_t(f32x4 dphi, int qt, int tb, int L, float two_beta, float mul,
                                              const float (*ts)[RP / 4],
                                              typename T::store_t (*du)[w_kdim<RP>() + kPad])
 {
@@ -332,31 +274,25 @@ __device__ __forceinline__ void chain_rule_t(f32x4 dphi, int qt, int tb, int L, 
     // lane group g evaluates bit g's sigmoid pair; the groups then share them
     const float tg = ts[row][4 * tb + g];
     float spg, sng, sp[4], sn[4];
-    sigmoid_pair(2.f * beta * tg, spg, sng);
+    sigmoid_pair(two_beta * tg, spg, sng);
     gather16x4(spg, sp);
     gather16x4(sng, sn);
-    // features c = 4g + i: bits 0, 1 from i, bits 2, 3 from g
-    const float hi = ((g & 1) ? sp[2] : sn[2]) * ((g & 2) ? sp[3] : sn[3]);
-    float p0 = 0.f, p1 = 0.f, p2 = 0.f;       // sums over i of x, x v_c0, x v_c1
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float phi = ((i & 1) ? sp[0] : sn[0]) * ((i & 2) ? sp[1] : sn[1]) * hi;
-        const float x = dphi[i] * phi;
-        p0 += x;
-        p1 += (i & 1) ? x : -x;
-        p2 += (i & 2) ? x : -x;
-    }
-    // over the lane groups: g & 1 (lane bit 4) is feature bit 2, g >> 1 (lane
-    // bit 5) feature bit 3; each exchange gives both the sum and the
-    // difference of the two groups
-    const LanePair a0 = xpair16(p0), a1 = xpair16(p1), a2 = xpair16(p2);
-    const LanePair b0 = xpair32(a0.lo + a0.hi), bd = xpair32(a0.hi - a0.lo);
-    const LanePair b1 = xpair32(a1.lo + a1.hi), b2 = xpair32(a2.lo + a2.hi);
-    const float s0 = b0.lo + b0.hi;            // sum over c of x_c
-    // sums over c of x_c v_cb for b = 0..3
-    const float sb[4] = {b1.lo + b1.hi, b2.lo + b2.hi, bd.lo + bd.hi, b0.hi - b0.lo};
-    const float sbg = g == 0 ? sb[0] : g == 1 ? sb[1] : g == 2 ? sb[2] : sb[3];
-    const float v = beta * (sbg - (spg - sng) * s0) * (1.f - tg * tg);
+    const float s2 = (g & 1) ? sp[2] : sn[2], s3 = (g & 2) ? sp[3] : sn[3];
+    const float e0 = sn[0] * dphi[0] + sp[0] * dphi[1], e1 = sn[0] * dphi[2] + sp[0] * dphi[3];
+    const float w = sn[1] * e0 + sp[1] * e1;       // sum over i without bits 2, 3
+    const float hi = s2 * s3;
+    const float a0 = hi * (sn[1] * (dphi[1] - dphi[0]) + sp[1] * (dphi[3] - dphi[2]));
+    const float a1 = hi * (e1 - e0);
+    const float a2 = ((g & 1) ? s3 : -s3) * w;
+    const float a3 = ((g & 2) ? s2 : -s2) * w;
+    // groups 0, 1 take the sums of a0 (group pairs), groups 2, 3 those of a2; a1, a3 alike
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0), __float_as_uint(a2), false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(a1), __float_as_uint(a3), false, false);
+    const float c0 = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    const float c1 = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+    const auto z = __builtin_amdgcn_permlane16_swap(__float_as_uint(c0), __float_as_uint(c1), false, false);
+    const float tsum = __uint_as_float(z[0]) + __uint_as_float(z[1]);
+    const float v = mul * (spg * sng) * (1.f - tg * tg) * tsum;
     du[row][4 * tb + g] = T::store(tb < L ? v : 0.f);
 }
 

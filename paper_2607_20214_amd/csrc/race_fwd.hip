@@ -30,106 +30,130 @@ namespace {
 template <class T, int D, int RP>
 struct StateSmem {
     using S = typename T::store_t;
-    S vt[D][kC + kPad];
-    S pht[RP][kC + kPad];
-    float aw[kC];
-    float a_state[RP];
+    S v[RowTile<T, D>::ELEMS];    // value rows
+    S ph[RowTile<T, RP>::ELEMS];  // feature rows
+    Parts<T, kC> aw;              // weights of A (backward)
 };
 
 template <class T, int D, int RP>
 struct OutSmem {
     using S = typename T::store_t;
-    S vt[D][kC + kPad];           // V chunk, transposed
-    S phq[kC][RP + kPad];         // Phi_Q chunk
-    S phk[kC][RP + kPad];         // Phi_K chunk (its transpose is read with transposed LDS reads)
+    S v[RowTile<T, D>::ELEMS];    // V chunk
+    S phq[RowTile<T, RP>::ELEMS]; // Phi_Q chunk
+    S phk[RowTile<T, RP>::ELEMS]; // Phi_K chunk
     S mm[kC][kC + kPad];          // tril(Phi_Q Phi_K') / L
-    float a_state[RP];
-    float den_a[kC];
-    float den_b[kC];
+    Parts<T, RP> a_state;
+    float den[kC];
 };
 
 struct StateArgs {
     const float* U;       // projections of the feature rows [BH][N][RP/4]
     const void* Val;      // value rows [BH][N][D]
-    const float* vscale;  // per-row value scale [BH][N] or null
-    const float* aw;      // per-row weight of A [BH][N] or null (1)
+    const float* vscale;  // per-row value scale [BH][N] (backward; else null)
+    const float* aw;      // per-row weight of A [BH][N] (backward; else null: 1)
     float* states;        // [BH][nseg][RP*D + RP]
     int H, N, L, seg_len, nseg;
     float two_beta, mul;
 };
 
-template <class T, int D, int RP>
+// BWD: the values are scaled per row (vscale) and A is weighted (aw).
+template <class T, int D, int RP, bool BWD>
 __global__ __launch_bounds__(kThreads) void race_state_kernel(StateArgs a)
 {
     using St = typename T::store_t;
+    using F = typename T::frag_t;
     constexpr int DW = D / 64;
     constexpr int SPLIT = table_split<RP>(), RPW = RP / SPLIT;   // features of this workgroup
-    __shared__ StateSmem<T, D, RPW> sm;
+    constexpr int FT = RPW / 16, NFA = (FT + 3) / 4;
+    using TV = RowTile<T, D>;
+    using TP = RowTile<T, RPW>;
+    __shared__ __attribute__((aligned(16))) StateSmem<T, D, RPW> sm;
     const int seg = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT, h = blockIdx.y, b = blockIdx.z;
     const int F0 = part * RPW, L = a.L - F0 / 16;                  // first feature; tables from here on
     const size_t bh = (size_t)b * a.H + h;
     const float* U = a.U + bh * a.N * (RP / 4) + F0 / 4;
     const St* Vl = (const St*)a.Val + bh * a.N * D;
-    const float* vs = a.vscale ? a.vscale + bh * a.N : nullptr;
-    const float* aw = a.aw ? a.aw + bh * a.N : nullptr;
+    const float* vs = BWD ? a.vscale + bh * a.N : nullptr;
+    const float* aw = BWD ? a.aw + bh * a.N : nullptr;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int g = lane >> 4, col = lane & 15;
 
-    for (int f = threadIdx.x; f < RPW; f += kThreads) sm.a_state[f] = 0.f;
-    f32x4 S[RPW / 16][DW];
+    f32x4 S[FT][DW];
 #pragma unroll
-    for (int ft = 0; ft < RPW / 16; ++ft)
+    for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
         for (int j = 0; j < DW; ++j) S[ft][j] = f32x4{0, 0, 0, 0};
+    // A of the feature tiles ft = w, w + 4, ...: bf16 on the matrix cores
+    // (every column alike), float32 in the vector units (lane (g, col): feature
+    // 16 ft + col over the tokens of lane group g, Aacc[j][0]; a float32 product
+    // takes eight matrix instructions of 32 cycles)
+    f32x4 Aacc[NFA];
+#pragma unroll
+    for (int j = 0; j < NFA; ++j) Aacc[j] = f32x4{0, 0, 0, 0};
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     // projections, value rows and A weights of the chunk, loaded one chunk ahead
     URegs<RPW> ur;
-    StageT<T, D> vr;
+    StageRows<T, D, BWD> vr;
     float awv = 0.f;
     auto load_chunk = [&](int c0) {
         ur.load(U, c0, a.N, RP / 4);
-        vr.load(Vl, c0, a.N, vs, 1.f);
-        const int r = min(c0 + (int)threadIdx.x, a.N - 1);
-        awv = aw ? aw[r] : 1.f;   // masked to the chunk's rows where stored
+        vr.load(Vl, c0, a.N, vs);
+        if constexpr (BWD) awv = aw[min(c0 + (int)threadIdx.x, a.N - 1)];   // masked to the chunk's rows where stored
     };
     load_chunk(t_beg);
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
-        vr.store(sm.vt, vs != nullptr);
-        if (threadIdx.x < kC) sm.aw[threadIdx.x] = t0 + (int)threadIdx.x < a.N ? awv : 0.f;
-        features_from<T, RPW>(ur, t0, a.N, L, a.two_beta, nullptr, sm.pht, nullptr);
+        vr.store(sm.v);
+        if (BWD && threadIdx.x < kC) sm.aw.put(threadIdx.x, t0 + (int)threadIdx.x < a.N ? awv : 0.f);
+        features_from<T, RPW>(ur, t0, a.N, L, a.two_beta, sm.ph);
         __syncthreads();
         load_chunk(t0 + kC < t_end ? t0 + kC : t0);   // the last chunk reloads its own (unconditional loads)
         // S[f][cols of wave] += Phi'[f][rows] V[rows][cols]
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            typename T::frag_t bv[DW];
+            F bv[DW];
 #pragma unroll
-            for (int j = 0; j < DW; ++j) bv[j] = T::ld8(&sm.vt[16 * (w * DW + j) + col][32 * kk + 8 * g]);
+            for (int j = 0; j < DW; ++j) bv[j] = TV::col8(sm.v, 32 * kk, 16 * (w * DW + j));
 #pragma unroll
-            for (int ft = 0; ft < RPW / 16; ++ft) {
-                const auto af = T::ld8(&sm.pht[16 * ft + col][32 * kk + 8 * g]);
+            for (int ft = 0; ft < FT; ++ft) {
+                const F af = TP::col8(sm.ph, 32 * kk, 16 * ft);
 #pragma unroll
                 for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[j], S[ft][j]);
+                if (ft % 4 == w) {
+                    if constexpr (!T::kSplit) {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            Aacc[ft / 4][0] += BWD ? af[i] * sm.aw.v[0][32 * kk + 8 * g + i] : af[i];
+                    } else if constexpr (BWD) {
+                        Aacc[ft / 4] = sm.aw.mma_b(af, 32 * kk + 8 * g, Aacc[ft / 4]);
+                    } else {
+                        Aacc[ft / 4] = token_sums<T>(af, Aacc[ft / 4]);
+                    }
+                }
             }
         }
-        for (int f = threadIdx.x; f < RPW; f += kThreads) {
-            float s = 0.f;
-            for (int k = 0; k < kC; ++k) s += T::load(sm.pht[f][k]) * sm.aw[k];
-            sm.a_state[f] += s;
-        }
     }
-    __syncthreads();
     float* out = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
 #pragma unroll
-    for (int ft = 0; ft < RPW / 16; ++ft)
+    for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
         for (int j = 0; j < DW; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 out[(size_t)(F0 + 16 * ft + 4 * g + i) * D + 16 * (w * DW + j) + col] = S[ft][j][i] * a.mul;
-    for (int f = threadIdx.x; f < RPW; f += kThreads) out[RP * D + F0 + f] = sm.a_state[f] * a.mul;
+#pragma unroll
+    for (int j = 0; j < NFA; ++j) {
+        const int ft = w + 4 * j;
+        if (ft >= FT) break;
+        if constexpr (!T::kSplit) {
+            const float s = wave_sum16(Aacc[j][0]);
+            if (g == 0) out[RP * D + F0 + 16 * ft + col] = s * a.mul;
+        } else if (col == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[RP * D + F0 + 16 * ft + 4 * g + i] = Aacc[j][i] * a.mul;
+        }
+    }
 }
 
 // mode 0: total in every segment; 1: exclusive prefix; 2: exclusive suffix.
@@ -180,7 +204,9 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
     using F = typename T::frag_t;
     constexpr int DW = D / 64;
     constexpr int FS = RP / 32;
-    __shared__ OutSmem<T, D, RP> sm;
+    using TV = RowTile<T, D>;
+    using TP = RowTile<T, RP>;
+    __shared__ __attribute__((aligned(16))) OutSmem<T, D, RP> sm;
     const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const size_t bh = (size_t)b * a.H + h;
     const float* Uq = a.Uq + bh * a.N * (RP / 4);
@@ -200,7 +226,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 S[ft][j][i] = st_in[(size_t)(16 * ft + 4 * g + i) * D + 16 * (w * DW + j) + col];
-    for (int f = threadIdx.x; f < RP; f += kThreads) sm.a_state[f] = st_in[RP * D + f];
+    for (int f = threadIdx.x; f < RP; f += kThreads) sm.a_state.put(f, st_in[RP * D + f]);
     // A runs on the matrix cores (causal): wave w keeps the feature tiles
     // ft = w, w + 4, ... in accumulator tiles (every column holds the sums;
     // column 0 starts from the segment's prefix state and is published to
@@ -216,64 +242,69 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     URegs<RP> uq, uk;                    // projections and V rows of the chunk, loaded one chunk ahead
-    StageT<T, D> vr;
+    StageRows<T, D, false> vr;
     uq.load(Uq, t_beg, a.N);
-    if (a.causal) uk.load(Uk, t_beg, a.N);
-    vr.load(V, t_beg, a.N, nullptr, 1.f);
+    if (a.causal) {
+        uk.load(Uk, t_beg, a.N);
+        vr.load(V, t_beg, a.N);
+    }
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
-        vr.store(sm.vt, false);
-        features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.phq, nullptr, nullptr);
-        if (a.causal) features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.phk, nullptr, nullptr);
+        features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.phq);
+        if (a.causal) {
+            vr.store(sm.v);
+            features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.phk);
+        }
         __syncthreads();
         {
             // next chunk's rows (the last chunk reloads its own: unconditional loads)
             const int tn = t0 + kC < t_end ? t0 + kC : t0;
             uq.load(Uq, tn, a.N);
-            if (a.causal) uk.load(Uk, tn, a.N);
-            vr.load(V, tn, a.N, nullptr, 1.f);
+            if (a.causal) {
+                uk.load(Uk, tn, a.N);
+                vr.load(V, tn, a.N);
+            }
         }
-        // Den, inter part: (1/L) Phi_Q . A   (4 threads per query)
+        // the wave's 16 queries: Den, inter part (1/L) Phi_Q . A (every row of
+        // the product tile alike), and the rows [16w, 16w + 16) of the
+        // intra-chunk kernel matrix (causal), formed transposed: lane (g, col)
+        // holds keys 16 kt + 4 g + i of query 16 w + col, so a row's four
+        // entries leave in one store and its sum is in-lane plus one exchange
+        // over the lane groups
         {
-            const int q = threadIdx.x >> 2, part = threadIdx.x & 3;
-            float s = 0.f;
-#pragma unroll
-            for (int f0 = part * (RP / 4); f0 < (part + 1) * (RP / 4); f0 += 8) {
-                const auto ph = T::ld8(&sm.phq[q][f0]);
-                const f32x4 a0 = *(const f32x4*)&sm.a_state[f0], a1 = *(const f32x4*)&sm.a_state[f0 + 4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s += (float)ph[j] * a0[j] + (float)ph[4 + j] * a1[j];
-            }
-            s += __shfl_xor(s, 1);
-            s += __shfl_xor(s, 2);
-            if (part == 0) sm.den_a[q] = s * a.inv_L;
-        }
-        // intra-chunk kernel matrix rows [16w, 16w + 16) (causal), formed
-        // transposed: lane (g, col) holds keys 16 kt + 4 g + i of query
-        // 16 w + col, so a row's four entries leave in one store and its sum
-        // is in-lane plus one exchange over the lane groups
-        if (a.causal) {
             const int qi = 16 * w + col;
-            float rs = 0.f;
-            for (int kt = 0; kt < 4; ++kt) {
-                f32x4 mt = {0, 0, 0, 0};
-                if (kt <= w) {
+            F qf[FS];
+            f32x4 da = {0, 0, 0, 0};
 #pragma unroll
-                    for (int fs = 0; fs < FS; ++fs)
-                        mt = T::mma(T::ld8(&sm.phk[16 * kt + col][32 * fs + 8 * g]),
-                                    T::ld8(&sm.phq[16 * w + col][32 * fs + 8 * g]), mt);
-                }
-                f32x4 v;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int kj = 16 * kt + 4 * g + i;
-                    v[i] = (kj <= qi) ? mt[i] * a.inv_L : 0.f;
-                    rs += v[i];
-                }
-                store4<T>(&sm.mm[qi][16 * kt + 4 * g], v);
+            for (int fs = 0; fs < FS; ++fs) {
+                qf[fs] = TP::row8(sm.phq, qi, 32 * fs + 8 * g);
+                da = sm.a_state.mma_a(32 * fs + 8 * g, qf[fs], da);
             }
-            rs = wave_sum16(rs);
-            if (g == 0) sm.den_b[qi] = rs;
+            float rs = 0.f;
+            if (a.causal) {
+                for (int kt = 0; kt < 4; ++kt) {
+                    f32x4 mt = {0, 0, 0, 0};
+                    if (kt <= w) {
+#pragma unroll
+                        for (int fs = 0; fs < FS; ++fs)
+                            mt = T::mma(TP::row8(sm.phk, 16 * kt + col, 32 * fs + 8 * g), qf[fs], mt);
+                    }
+                    f32x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int kj = 16 * kt + 4 * g + i;
+                        v[i] = (kj <= qi) ? mt[i] * a.inv_L : 0.f;
+                        rs += v[i];
+                    }
+                    store4<T>(&sm.mm[qi][16 * kt + 4 * g], v);
+                }
+                rs = wave_sum16(rs);
+            }
+            if (g == 0) {
+                const float den = da[0] * a.inv_L + rs;
+                sm.den[qi] = den;
+                if (t0 + qi < a.N) dlr[t0 + qi] = den;
+            }
         }
         __syncthreads();
         // Num^T for the wave's d columns, all 64 queries (lane (g, col) holds
@@ -301,49 +332,49 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
             }
 #pragma unroll
             for (int qt = 0; qt < 4; ++qt) {
-                const F af = T::ld44(&sm.phq[16 * qt + col][32 * fs + 4 * g],
-                                     &sm.phq[16 * qt + col][32 * fs + 16 + 4 * g]);
+                const F af = TP::row44(sm.phq, 16 * qt + col, 32 * fs + 4 * g);
 #pragma unroll
                 for (int j = 0; j < DW; ++j) num[qt][j] = T::mma(sf[j], af, num[qt][j]);
             }
         }
 #pragma unroll
-        for (int qt = 0; qt < 4; ++qt) {
+        for (int qt = 0; qt < 4; ++qt)
 #pragma unroll
             for (int j = 0; j < DW; ++j) num[qt][j] *= a.inv_L;
-            if (a.causal) {
+        F bv[2][DW];                     // V^T operands: the intra-chunk part and the state update
+        if (a.causal) {
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
+            for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+                for (int j = 0; j < DW; ++j) bv[kk][j] = TV::col8(sm.v, 32 * kk, 16 * (w * DW + j));
+#pragma unroll
+                for (int qt = 0; qt < 4; ++qt) {
                     const F bf = T::ld8(&sm.mm[16 * qt + col][32 * kk + 8 * g]);
 #pragma unroll
-                    for (int j = 0; j < DW; ++j)
-                        num[qt][j] = T::mma(T::ld8(&sm.vt[16 * (w * DW + j) + col][32 * kk + 8 * g]), bf, num[qt][j]);
+                    for (int j = 0; j < DW; ++j) num[qt][j] = T::mma(bv[kk][j], bf, num[qt][j]);
                 }
             }
+        }
+#pragma unroll
+        for (int qt = 0; qt < 4; ++qt) {
             const int ql = 16 * qt + col;
             const int tok = t0 + ql;
+            const float inv = 1.f / (sm.den[ql] + a.eps);
             if (tok < a.N) {
-                const float den = sm.den_a[ql] + (a.causal ? sm.den_b[ql] : 0.f);
-                const float inv = 1.f / (den + a.eps);
 #pragma unroll
                 for (int j = 0; j < DW; ++j)
                     store4<T>(Olr + (size_t)tok * D + 16 * (w * DW + j) + 4 * g, num[qt][j] * inv);
             }
         }
-        if (threadIdx.x < kC && t0 + threadIdx.x < a.N)
-            dlr[t0 + threadIdx.x] = sm.den_a[threadIdx.x] + (a.causal ? sm.den_b[threadIdx.x] : 0.f);
         if (a.causal) {
             // S += Phi_K' V (chunk), A += Phi_K' 1
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
-                F bv[DW];
-#pragma unroll
-                for (int j = 0; j < DW; ++j) bv[j] = T::ld8(&sm.vt[16 * (w * DW + j) + col][32 * kk + 8 * g]);
 #pragma unroll
                 for (int ft = 0; ft < FT; ++ft) {
-                    const F af = phi_t8<T, RP>(sm.phk, 32 * kk, 16 * ft);
+                    const F af = TP::col8(sm.phk, 32 * kk, 16 * ft);
 #pragma unroll
-                    for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[j], S[ft][j]);
+                    for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[kk][j], S[ft][j]);
                     if (ft % 4 == w) Aacc[ft / 4] = token_sums<T>(af, Aacc[ft / 4]);
                 }
             }
@@ -353,7 +384,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
                 const int ft = w + 4 * j;
                 if (ft < FT && col == 0)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) sm.a_state[16 * ft + 4 * g + i] = Aacc[j][i];
+                    for (int i = 0; i < 4; ++i) sm.a_state.put(16 * ft + 4 * g + i, Aacc[j][i]);
             }
         }
     }
@@ -374,8 +405,8 @@ hipError_t launch_states_t(const Shape& s, const StateArgs& a, int scan_mode, hi
         dim3 grid(s.nseg * table_split<RP>(), s.H, s.B);
         // the forward sums key rows, the backward (vscale set) query rows
         const bool bwd = a.vscale != nullptr;
-        ELSAA_LAUNCH(bwd ? "race_state_bwd" : "race_state_fwd", (race_state_kernel<T, D, RP>), grid, dim3(kThreads),
-                     0, st, a);
+        if (bwd) ELSAA_LAUNCH("race_state_bwd", (race_state_kernel<T, D, RP, true>), grid, dim3(kThreads), 0, st, a);
+        else ELSAA_LAUNCH("race_state_fwd", (race_state_kernel<T, D, RP, false>), grid, dim3(kThreads), 0, st, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const int per = RP * D + RP;
