@@ -67,7 +67,7 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
     u["lowrank_fwd"] = (bh * N * lr_tok_bytes, bh * N * lr_tok_flops,
                         ["race_state_fwd", "race_scan_fwd", "race_out"])
     u["lowrank_bwd"] = (2 * bh * N * lr_tok_bytes, int(2.25 * bh * N * lr_tok_flops),
-                        ["race_state_bwd", "race_scan_bwd", "race_dq", "race_dk", "race_dv", "race_wt"])
+                        ["race_state_bwd", "race_scan_bwd", "race_bwd", "race_dv"])
     u["bwd_rows"] = (bh * N * (D * s + 8 * D + 12), bh * N * 4 * D, ["bwd_rows"])
     base_fwd = bh * (3 * N * D * s + 4 * N * D + 12 * N) + bh * N * (D * s + 4 * D + 8)
     base_bwd = bh * (4 * N * D * s + 12 * N * D + 8 * N)
@@ -149,8 +149,7 @@ KERNEL_SOURCES = {
     "race_state_bwd": ["race_fwd.hip", "race_common.hpp", "common.hpp"],
     "race_scan_fwd": ["race_fwd.hip"], "race_scan_bwd": ["race_fwd.hip"],
     "race_out": ["race_fwd.hip", "race_common.hpp", "common.hpp"],
-    "race_dq": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
-    "race_dk": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
+    "race_bwd": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
     "race_dv": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
     "bwd_rows": ["bwd_rows.hip", "common.hpp"],
     "gemm": ["gemm.hip", "common.hpp"], "gemm_reduce": ["gemm.hip"],

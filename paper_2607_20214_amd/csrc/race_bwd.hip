@@ -20,6 +20,8 @@
 // enter the MFMAs split the same way: their products cancel against the dDen
 // terms.  LB3 writes dV in the storage dtype [BH][N][D]; the sparse backward
 // adds it to its float32 dV before the final rounding.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "race_common.hpp"
 
@@ -35,9 +37,16 @@ struct LbArgs {
     const void* V;
     const void* dO;
     const float* rs;        // row scalars (sc_lr at 3*BHN, dDen at 4*BHN)
-    const float* states;    // LB1: forward prefix states; LB2/LB3: backward suffix states
-    void* out;              // LB1 / LB2: du rows [BH][N][wk]; LB3: dV rows [BH][N][D] (storage dtype)
+    const float* states_f;  // forward prefix states (LB1)
+    const float* states_b;  // backward suffix states (LB2, LB3)
+    void* du_q;             // du rows [BH][N][wk] (storage dtype)
+    void* du_k;
+    void* dv;               // dV rows [BH][N][D] (storage dtype)
+    const float* W;         // W_race [H][4L][D]
+    void* wt_hi;            // W' parts [H][D][wk] (storage dtype)
+    void* wt_lo;
     int H, N, L, seg_len, nseg, causal;
+    int items;              // B H nseg
     size_t BHN;
     float two_beta, beta, inv_L;
 };
@@ -89,32 +98,36 @@ constexpr bool bwd_fits()
 // [N][WK], 16 bytes per thread and store.
 template <class T, int RPW, int RP>
 __device__ __forceinline__ void store_du(const typename T::store_t (*du)[w_kdim<RPW>() + kPad],
-                                         typename T::store_t* out, int t0, int N)
+                                         typename T::store_t* out, int t0, int N, int tx)
 {
     // a workgroup holding all the features writes whole (padded) rows,
     // one holding some of the tables their RPW / 4 columns
     constexpr int WK = w_kdim<RP>(), COLS = RPW == RP ? WK : RPW / 4;
     constexpr int PER = 16 / T::bytes, CH = COLS / PER;
     static_assert(COLS % PER == 0, "du row of whole 16-byte pieces");
-    for (int it = threadIdx.x; it < kC * CH; it += kThreads) {
+    for (int it = tx; it < kC * CH; it += kThreads) {
         const int r = it / CH, c = it % CH;
         if (t0 + r < N) stg16(out + (size_t)(t0 + r) * WK + c * PER, *(const uint4*)&du[r][c * PER]);
     }
 }
 
-// W' = W_hi' + W_lo' of every head, [H][D][WK] (rows 4l + b, zero past 4L).
+// W' = W_hi' + W_lo' of every head, [H][D][WK] (rows 4l + b, zero past 4L):
+// kWtPer elements per workgroup of the passes' launch.
+constexpr int kWtPer = 8 * kThreads;
 template <class T>
-__global__ __launch_bounds__(256) void race_wt_kernel(const float* W, typename T::store_t* hi,
-                                                      typename T::store_t* lo, int L, int D, int WK)
+__device__ __forceinline__ void wt_body(const LbArgs& a, int blk, int D, int WK)
 {
-    const int h = blockIdx.y;
-    const int it = blockIdx.x * 256 + threadIdx.x;
-    if (it >= D * WK) return;
-    const int d = it / WK, p = it % WK;
-    const float w = p < 4 * L ? W[((size_t)h * 4 * L + p) * D + d] : 0.f;
-    const typename T::store_t vh = T::store(w);
-    hi[((size_t)h * D + d) * WK + p] = vh;
-    lo[((size_t)h * D + d) * WK + p] = T::store(T::kSplit ? w - T::load(vh) : 0.f);
+    using St = typename T::store_t;
+    const int per = D * WK, n = a.H * per;
+    for (int j = 0; j < kWtPer / kThreads; ++j) {
+        const int it = blk * kWtPer + j * kThreads + threadIdx.x;
+        if (it >= n) return;
+        const int h = it / per, d = it % per / WK, p = it % WK;
+        const float w = p < 4 * a.L ? a.W[((size_t)h * 4 * a.L + p) * D + d] : 0.f;
+        const St vh = T::store(w);
+        ((St*)a.wt_hi)[it] = vh;
+        ((St*)a.wt_lo)[it] = T::store(T::kSplit ? w - T::load(vh) : 0.f);
+    }
 }
 
 // The state part of dphi' for the wave's feature tile in St (rows d, its
@@ -122,10 +135,11 @@ __global__ __launch_bounds__(256) void race_wt_kernel(const float* W, typename T
 // the 16-row tiles t.  The state enters as hi + lo bf16 parts, split once per
 // chunk and k-step.
 template <class T, int D>
-__device__ __forceinline__ void state_product(const f32x4 (&St)[D / 16], const typename T::store_t* x, f32x4 (&acc)[4])
+__device__ __forceinline__ void state_product(const f32x4 (&St)[D / 16], const typename T::store_t* x, f32x4 (&acc)[4],
+                                              int tx)
 {
     using F = typename T::frag_t;
-    const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+    const int lane = tx & 63, g = lane >> 4, col = lane & 15;
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t] = f32x4{0, 0, 0, 0};
 #pragma unroll
@@ -149,35 +163,35 @@ __device__ __forceinline__ void state_product(const f32x4 (&St)[D / 16], const t
 
 // ---------------------------------------------------------------- LB1: dQ
 template <class T, int D, int RP>
-__global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
+__device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg, int part,
+                                             Lb1Smem<T, D, RP / table_split<RP>()>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
-    constexpr int SPLIT = table_split<RP>(), RPW = RP / SPLIT;   // features of this workgroup
+    constexpr int RPW = RP / table_split<RP>();                    // features of this workgroup
     constexpr int DT = D / 16, KS = D / 32, FT = RPW / 16, NFT = (FT + 3) / 4;
     using TV = RowTile<T, D>;
     using TP = RowTile<T, RPW>;
-    __shared__ __attribute__((aligned(16))) Lb1Smem<T, D, RPW> sm;
-    const int seg = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT, h = blockIdx.y, b = blockIdx.z;
     const int F0 = part * RPW, L = a.L - F0 / 16;                  // first feature; tables from here on
-    const size_t bh = (size_t)b * a.H + h;
     const float* Uq = a.Uq + bh * a.N * (RP / 4) + F0 / 4;
     const float* Uk = a.Uk + bh * a.N * (RP / 4) + F0 / 4;
     const St* V = (const St*)a.V + bh * a.N * D;
     const St* dO = (const St*)a.dO + bh * a.N * D;
     const float* sclr = a.rs + 3 * a.BHN + bh * a.N;
     const float* dden = a.rs + 4 * a.BHN + bh * a.N;
-    St* du_out = (St*)a.out + bh * a.N * w_kdim<RP>() + F0 / 4;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    St* du_out = (St*)a.du_q + bh * a.N * w_kdim<RP>() + F0 / 4;
+    int tx = threadIdx.x;
+    asm volatile("" : "+v"(tx));                                  // this body's own copy (race_common.hpp)
+    const int lane = tx & 63, w = __builtin_amdgcn_readfirstlane(tx >> 6);
     const int g = lane >> 4, col = lane & 15;
 
-    for (int it = threadIdx.x; it < kC * (w_kdim<RPW>() + kPad); it += kThreads)
+    for (int it = tx; it < kC * (w_kdim<RPW>() + kPad); it += kThreads)
         (&sm.du[0][0])[it] = T::store(0.f);
     // state S'[d][f] for the wave's features f = 16 (w + 4j) + col, and
     // A[f] of the same feature tiles (lane (g, col) register i: feature
     // 16 (w + 4j) + 4 g + i, every column alike; token_sums keeps it so)
     f32x4 St_[NFT][DT], Aacc[NFT];
-    const float* st_in = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
+    const float* st_in = a.states_f + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
 #pragma unroll
     for (int j = 0; j < NFT; ++j) {
         const int ft = w + 4 * j;
@@ -192,32 +206,32 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     URegs<RPW> uq, uk;                    // projections of the chunk, loaded one chunk ahead
-    uq.load(Uq, t_beg, a.N, RP / 4);
-    if (a.causal) uk.load(Uk, t_beg, a.N, RP / 4);
+    uq.load(Uq, t_beg, a.N, RP / 4, tx);
+    if (a.causal) uk.load(Uk, t_beg, a.N, RP / 4, tx);
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
         // every global load of the chunk is issued first; the features (vector
         // work) run while they are in flight, then the rows go to LDS
         StageRows<T, D, false> sdn, sv;
-        sdn.load(dO, t0, a.N);
-        if (a.causal) sv.load(V, t0, a.N);
-        const bool in = threadIdx.x < kC && t0 + (int)threadIdx.x < a.N;
-        const float ddv = in ? dden[t0 + threadIdx.x] : 0.f, scv = in ? sclr[t0 + threadIdx.x] : 0.f;
-        tanh_rows<RPW>(uq, sm.ts);
-        if (a.causal) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk);
-        sdn.store(sm.dn);
-        if (a.causal) sv.store(sm.v);
-        if (threadIdx.x < kC) {
-            sm.dden[threadIdx.x] = ddv;
-            sm.sc[threadIdx.x] = scv;
+        sdn.load(dO, t0, a.N, nullptr, tx);
+        if (a.causal) sv.load(V, t0, a.N, nullptr, tx);
+        const bool in = tx < kC && t0 + tx < a.N;
+        const float ddv = in ? dden[t0 + tx] : 0.f, scv = in ? sclr[t0 + tx] : 0.f;
+        tanh_rows<RPW>(uq, sm.ts, tx);
+        if (a.causal) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk, tx);
+        sdn.store(sm.dn, 1.f, tx);
+        if (a.causal) sv.store(sm.v, 1.f, tx);
+        if (tx < kC) {
+            sm.dden[tx] = ddv;
+            sm.sc[tx] = scv;
         }
         __syncthreads();
         {
             // next chunk's projections (the last chunk reloads its own, so
             // the loads are unconditional)
             const int tn = t0 + kC < t_end ? t0 + kC : t0;
-            uq.load(Uq, tn, a.N, RP / 4);
-            if (a.causal) uk.load(Uk, tn, a.N, RP / 4);
+            uq.load(Uq, tn, a.N, RP / 4, tx);
+            if (a.causal) uk.load(Uk, tn, a.N, RP / 4, tx);
         }
         if (a.causal) {
             // G rows [16w, 16w + 16): sc_lr,i <dO_i, V_j> + dDen_i for j <= i,
@@ -248,7 +262,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
             const int ft = w + 4 * j;
             if (ft >= FT) break;
             f32x4 acc[4];
-            state_product<T, D>(St_[j], sm.dn, acc);
+            state_product<T, D>(St_[j], sm.dn, acc, tx);
 #pragma unroll
             for (int qt = 0; qt < 4; ++qt) {
                 const float ddq = sm.dden[16 * qt + col], scq = sm.sc[16 * qt + col];
@@ -258,7 +272,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
             if (a.causal) {
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
-                    const F pf = TP::col8(sm.pk, 32 * kk, 16 * ft);
+                    const F pf = TP::col8(sm.pk, 32 * kk, 16 * ft, tx);
 #pragma unroll
                     for (int qt = 0; qt < 4; ++qt)
                         acc[qt] = T::mma(pf, T::ld8(&sm.gg[16 * qt + col][32 * kk + 8 * g]), acc[qt]);
@@ -267,10 +281,10 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
             // the four tiles' chain rules side by side: their exchanges overlap
 #pragma unroll
             for (int qt = 0; qt < 4; ++qt)
-                chain_rule_t<T, RPW>(acc[qt], qt, ft, L, a.two_beta, a.two_beta * a.inv_L, sm.ts, sm.du);
+                chain_rule_t<T, RPW>(acc[qt], qt, ft, L, a.two_beta, a.two_beta * a.inv_L, sm.ts, sm.du, tx);
         }
         __syncthreads();
-        store_du<T, RPW, RP>(sm.du, du_out, t0, a.N);
+        store_du<T, RPW, RP>(sm.du, du_out, t0, a.N, tx);
         if (a.causal) {
             // S' += V' Phi_K (chunk), A += Phi_K' 1
 #pragma unroll
@@ -280,12 +294,12 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
                 for (int j = 0; j < NFT; ++j) {
                     const int ft = w + 4 * j;
                     if (ft >= FT) break;
-                    pf[j] = TP::col8(sm.pk, 32 * kk, 16 * ft);
+                    pf[j] = TP::col8(sm.pk, 32 * kk, 16 * ft, tx);
                     Aacc[j] = token_sums<T>(pf[j], Aacc[j]);
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const F vf = TV::col8(sm.v, 32 * kk, 16 * dt);
+                    const F vf = TV::col8(sm.v, 32 * kk, 16 * dt, tx);
 #pragma unroll
                     for (int j = 0; j < NFT; ++j) {
                         if (w + 4 * j >= FT) break;
@@ -299,34 +313,34 @@ __global__ __launch_bounds__(kThreads, 2) void race_dq_kernel(LbArgs a)
 
 // ---------------------------------------------------------------- LB2: dK
 template <class T, int D, int RP>
-__global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
+__device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg, int part,
+                                             Lb2Smem<T, D, RP / table_split<RP>()>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
-    constexpr int SPLIT = table_split<RP>(), RPW = RP / SPLIT;   // features of this workgroup
+    constexpr int RPW = RP / table_split<RP>();                    // features of this workgroup
     constexpr int DT = D / 16, KS = D / 32, FT = RPW / 16, NFT = (FT + 3) / 4;
     using TV = RowTile<T, D>;
     using TP = RowTile<T, RPW>;
-    __shared__ __attribute__((aligned(16))) Lb2Smem<T, D, RPW> sm;
-    const int seg = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT, h = blockIdx.y, b = blockIdx.z;
     const int F0 = part * RPW, L = a.L - F0 / 16;                  // first feature; tables from here on
-    const size_t bh = (size_t)b * a.H + h;
     const float* Uq = a.Uq + bh * a.N * (RP / 4) + F0 / 4;
     const float* Uk = a.Uk + bh * a.N * (RP / 4) + F0 / 4;
     const St* V = (const St*)a.V + bh * a.N * D;
     const St* dO = (const St*)a.dO + bh * a.N * D;
     const float* sclr = a.rs + 3 * a.BHN + bh * a.N;
     const float* dden = a.rs + 4 * a.BHN + bh * a.N;
-    St* du_out = (St*)a.out + bh * a.N * w_kdim<RP>() + F0 / 4;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    St* du_out = (St*)a.du_k + bh * a.N * w_kdim<RP>() + F0 / 4;
+    int tx = threadIdx.x;
+    asm volatile("" : "+v"(tx));                                  // this body's own copy (race_common.hpp)
+    const int lane = tx & 63, w = __builtin_amdgcn_readfirstlane(tx >> 6);
     const int g = lane >> 4, col = lane & 15;
 
-    for (int it = threadIdx.x; it < kC * (w_kdim<RPW>() + kPad); it += kThreads)
+    for (int it = tx; it < kC * (w_kdim<RPW>() + kPad); it += kThreads)
         (&sm.du[0][0])[it] = T::store(0.f);
     // the suffix state of the wave's feature tiles, as in the dQ pass:
     // dS'[d][f], and dA[f] = (1/L) sum phi(q) dDen of the queries after the chunk
     f32x4 St_[NFT][DT], Aacc[NFT];
-    const float* st_in = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
+    const float* st_in = a.states_b + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
 #pragma unroll
     for (int j = 0; j < NFT; ++j) {
         const int ft = w + 4 * j;
@@ -342,34 +356,34 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     const int nch = (t_end - t_beg + kC - 1) / kC;
     URegs<RPW> uq, uk;                    // projections of the chunk, loaded one chunk ahead
-    uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4);
-    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4);
+    uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
+    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
     for (int c = nch - 1; c >= 0; --c) {
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
         StageRows<T, D, false> svr;
         StageRows<T, D, true> sdn;
-        svr.load(V, t0, a.N);
-        if (a.causal) sdn.load(dO, t0, a.N, sclr);
-        const bool in = threadIdx.x < kC && t0 + (int)threadIdx.x < a.N;
-        const float ddv = in ? dden[t0 + threadIdx.x] * a.inv_L : 0.f;
-        tanh_rows<RPW>(uk, sm.ts);
-        if (a.causal) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, sm.pq);
-        svr.store(sm.v);
+        svr.load(V, t0, a.N, nullptr, tx);
+        if (a.causal) sdn.load(dO, t0, a.N, sclr, tx);
+        const bool in = tx < kC && t0 + tx < a.N;
+        const float ddv = in ? dden[t0 + tx] * a.inv_L : 0.f;
+        tanh_rows<RPW>(uk, sm.ts, tx);
+        if (a.causal) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, sm.pq, tx);
+        svr.store(sm.v, 1.f, tx);
         if (a.causal) {
-            sdn.store(sm.dn, a.inv_L);
-            if (threadIdx.x < kC) {
-                sm.dden[threadIdx.x] = ddv;
-                sm.ddp.put(threadIdx.x, ddv);
+            sdn.store(sm.dn, a.inv_L, tx);
+            if (tx < kC) {
+                sm.dden[tx] = ddv;
+                sm.ddp.put(tx, ddv);
             }
         }
         __syncthreads();
         {
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
             const int tn = c > 0 ? t0 - kC : t0;
-            uk.load(Uk, tn, a.N, RP / 4);
-            if (a.causal) uq.load(Uq, tn, a.N, RP / 4);
+            uk.load(Uk, tn, a.N, RP / 4, tx);
+            if (a.causal) uq.load(Uq, tn, a.N, RP / 4, tx);
         }
         if (a.causal) {
             // G' rows j in [16w, 16w + 16): (<V_j, dNum_i> + dDen_i) / L for
@@ -400,13 +414,13 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
             const int ft = w + 4 * j;
             if (ft >= FT) break;
             f32x4 acc[4];
-            state_product<T, D>(St_[j], sm.v, acc);
+            state_product<T, D>(St_[j], sm.v, acc, tx);
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) acc[kt] += Aacc[j];
             if (a.causal) {
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
-                    const F pf = TP::col8(sm.pq, 32 * kk, 16 * ft);
+                    const F pf = TP::col8(sm.pq, 32 * kk, 16 * ft, tx);
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt)
                         acc[kt] = T::mma(pf, T::ld8(&sm.ggt[16 * kt + col][32 * kk + 8 * g]), acc[kt]);
@@ -414,10 +428,10 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
             }
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt)
-                chain_rule_t<T, RPW>(acc[kt], kt, ft, L, a.two_beta, a.two_beta, sm.ts, sm.du);
+                chain_rule_t<T, RPW>(acc[kt], kt, ft, L, a.two_beta, a.two_beta, sm.ts, sm.du, tx);
         }
         __syncthreads();
-        store_du<T, RPW, RP>(sm.du, du_out, t0, a.N);
+        store_du<T, RPW, RP>(sm.du, du_out, t0, a.N, tx);
         if (a.causal) {
             // dS' += (dNum / L)' Phi_Q (chunk), dA += (1/L) Phi_Q' dDen
 #pragma unroll
@@ -427,12 +441,12 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
                 for (int j = 0; j < NFT; ++j) {
                     const int ft = w + 4 * j;
                     if (ft >= FT) break;
-                    pf[j] = TP::col8(sm.pq, 32 * kk, 16 * ft);
+                    pf[j] = TP::col8(sm.pq, 32 * kk, 16 * ft, tx);
                     Aacc[j] = sm.ddp.mma_b(pf[j], 32 * kk + 8 * g, Aacc[j]);
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const F df = TV::col8(sm.dn, 32 * kk, 16 * dt);
+                    const F df = TV::col8(sm.dn, 32 * kk, 16 * dt, tx);
 #pragma unroll
                     for (int j = 0; j < NFT; ++j) {
                         if (w + 4 * j >= FT) break;
@@ -446,25 +460,24 @@ __global__ __launch_bounds__(kThreads, 2) void race_dk_kernel(LbArgs a)
 
 // ---------------------------------------------------------------- LB3: dV
 template <class T, int D, int RP>
-__global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
+__device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg, Lb3Smem<T, D, RP>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
     constexpr int DW = D / 64, FS = RP / 32;
     using TV = RowTile<T, D>;
     using TP = RowTile<T, RP>;
-    __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP> sm;
-    const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const size_t bh = (size_t)b * a.H + h;
     const float* Uq = a.Uq + bh * a.N * (RP / 4);
     const float* Uk = a.Uk + bh * a.N * (RP / 4);
     const St* dO = (const St*)a.dO + bh * a.N * D;
     const float* sclr = a.rs + 3 * a.BHN + bh * a.N;
-    St* out = (St*)a.out + bh * a.N * D;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    St* out = (St*)a.dv + bh * a.N * D;
+    int tx = threadIdx.x;
+    asm volatile("" : "+v"(tx));                                  // this body's own copy (race_common.hpp)
+    const int lane = tx & 63, w = __builtin_amdgcn_readfirstlane(tx >> 6);
     const int g = lane >> 4, col = lane & 15;
 
-    const float* st_in = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
+    const float* st_in = a.states_b + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
     f32x4 S[RP / 16][DW];
 #pragma unroll
     for (int ft = 0; ft < RP / 16; ++ft)
@@ -477,25 +490,25 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     const int nch = (t_end - t_beg + kC - 1) / kC;
     URegs<RP> uq, uk;                    // projections of the chunk, loaded one chunk ahead
-    uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4);
-    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4);
+    uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
+    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
     for (int c = nch - 1; c >= 0; --c) {
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
         StageRows<T, D, true> sdn;
-        if (a.causal) sdn.load(dO, t0, a.N, sclr);
-        features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk);
+        if (a.causal) sdn.load(dO, t0, a.N, sclr, tx);
+        features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk, tx);
         if (a.causal) {
-            features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq);
-            sdn.store(sm.dn, a.inv_L);
+            features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq, tx);
+            sdn.store(sm.dn, a.inv_L, tx);
         }
         __syncthreads();
         {
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
             const int tn = c > 0 ? t0 - kC : t0;
-            uk.load(Uk, tn, a.N, RP / 4);
-            if (a.causal) uq.load(Uq, tn, a.N, RP / 4);
+            uk.load(Uk, tn, a.N, RP / 4, tx);
+            if (a.causal) uq.load(Uq, tn, a.N, RP / 4, tx);
         }
         if (a.causal) {
             // M' rows j in [16w, 16w + 16): <phi(k_j), phi(q_i)> for i >= j,
@@ -553,7 +566,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-                for (int j = 0; j < DW; ++j) bv[kk][j] = TV::col8(sm.dn, 32 * kk, 16 * (w * DW + j));
+                for (int j = 0; j < DW; ++j) bv[kk][j] = TV::col8(sm.dn, 32 * kk, 16 * (w * DW + j), tx);
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt) {
                     const F bf = T::ld8(&sm.mt[16 * kt + col][32 * kk + 8 * g]);
@@ -575,7 +588,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
             for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
                 for (int ft = 0; ft < RP / 16; ++ft) {
-                    const F af = TP::col8(sm.pq, 32 * kk, 16 * ft);
+                    const F af = TP::col8(sm.pq, 32 * kk, 16 * ft, tx);
 #pragma unroll
                     for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[kk][j], S[ft][j]);
                 }
@@ -584,21 +597,64 @@ __global__ __launch_bounds__(kThreads, 2) void race_dv_kernel(LbArgs a)
     }
 }
 
+// The three passes in one launch: they depend on the states only, so one
+// pass's workgroups start in the places the previous one's leave (three
+// launches left three partly filled last rounds and two gaps: 16K 243 + 7 us
+// with W' apart, 223 us together; 4096 tokens x 16 heads 37 + 8 against 24).
+// Pass after pass, not interleaved: with the passes of a segment side by side
+// the compute units fetch three loops' instructions in turn (253 us at 16K),
+// which costs more than their shared rows in L2 save.  W' for the sparse
+// epilogues is formed by a few workgroups at the end of the grid.
+// 256 features keep dV on its own: its state takes a whole compute unit's
+// registers, which would halve the dQ and dK workgroups in flight.
+template <int RP> constexpr bool dv_joins() { return RP < 256; }
+
+template <class T, int D, int RP>
+__global__ __launch_bounds__(kThreads, 2) void race_bwd_kernel(LbArgs a)
+{
+    constexpr int SPLIT = table_split<RP>(), ROLES = 2 * SPLIT + (dv_joins<RP>() ? 1 : 0);
+    constexpr bool DV = dv_joins<RP>();
+    __shared__ __attribute__((aligned(16))) union {
+        Lb1Smem<T, D, RP / SPLIT> q;
+        Lb2Smem<T, D, RP / SPLIT> k;
+        typename std::conditional<DV, Lb3Smem<T, D, RP>, char>::type v;
+    } sm;
+    const int role = blockIdx.x / a.items, item = blockIdx.x - role * a.items;
+    if (role >= ROLES) {
+        wt_body<T>(a, blockIdx.x - ROLES * a.items, D, w_kdim<RP>());
+        return;
+    }
+    const int seg = item % a.nseg;
+    const size_t bh = item / a.nseg;
+    if (role < SPLIT) race_dq_body<T, D, RP>(a, bh, seg, role, sm.q);
+    else if (role < 2 * SPLIT) race_dk_body<T, D, RP>(a, bh, seg, role - SPLIT, sm.k);
+    else if constexpr (DV) race_dv_body<T, D, RP>(a, bh, seg, sm.v);
+}
+
+template <class T, int D, int RP>
+__global__ __launch_bounds__(kThreads, 1) void race_dv_kernel(LbArgs a)
+{
+    __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP> sm;
+    race_dv_body<T, D, RP>(a, blockIdx.y, blockIdx.x, sm);
+}
+
 template <class T, int D, int RP>
 struct BwdFn {
-    static hipError_t run(const Shape& s, const LbArgs& a1, const LbArgs& a2, const LbArgs& a3, hipStream_t st)
+    static hipError_t run(const Shape& s, const LbArgs& a, hipStream_t st)
     {
         if constexpr (!bwd_fits<T, D, RP>()) {
             return hipErrorInvalidConfiguration;
         } else {
-            dim3 grid(s.nseg, s.H, s.B), grid_t(s.nseg * table_split<RP>(), s.H, s.B);
-            ELSAA_LAUNCH("race_dq", (race_dq_kernel<T, D, RP>), grid_t, dim3(kThreads), 0, st, a1);
+            constexpr int ROLES = 2 * table_split<RP>() + (dv_joins<RP>() ? 1 : 0);
+            const int wt = (s.H * D * w_kdim<RP>() + kWtPer - 1) / kWtPer;   // W' rides along
+            ELSAA_LAUNCH("race_bwd", (race_bwd_kernel<T, D, RP>), dim3(a.items * ROLES + wt), dim3(kThreads), 0, st, a);
             hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            ELSAA_LAUNCH("race_dk", (race_dk_kernel<T, D, RP>), grid_t, dim3(kThreads), 0, st, a2);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP>), grid, dim3(kThreads), 0, st, a3);
-            return hipGetLastError();
+            if constexpr (!dv_joins<RP>()) {
+                if (e != hipSuccess) return e;
+                ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
+                e = hipGetLastError();
+            }
+            return e;
         }
     }
 };
@@ -650,19 +706,6 @@ hipError_t launch_race_bwd(const Shape& s, const float* Uq, const float* Uk, con
                            const float* states_f, float* states_b, void* wt_hi, void* wt_lo,
                            void* du_q, void* du_k, void* dv_lr, hipStream_t st)
 {
-    {
-        const int rp = race_padded_features(s.r);
-        const int wk = rp / 4 < 32 ? 32 : rp / 4;
-        dim3 grid((s.D * wk + 255) / 256, s.H);
-        if (s.bf16)
-            ELSAA_LAUNCH("race_wt", race_wt_kernel<BF16>, grid, dim3(256), 0, st, W_race,
-                         (uint16_t*)wt_hi, (uint16_t*)wt_lo, s.L, s.D, wk);
-        else
-            ELSAA_LAUNCH("race_wt", race_wt_kernel<F32>, grid, dim3(256), 0, st, W_race, (float*)wt_hi,
-                         (float*)wt_lo, s.L, s.D, wk);
-        hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return e0;
-    }
     const size_t BHN = (size_t)s.B * s.H * s.N;
     // backward suffix states of phi(q) dNum' / L and phi(q) dDen / L (the
     // forward prefix states of phi(k) V' and phi(k) come from the forward)
@@ -671,14 +714,13 @@ hipError_t launch_race_bwd(const Shape& s, const float* Uq, const float* Uk, con
     if (e != hipSuccess) return e;
     LbArgs a;
     a.Uq = Uq; a.Uk = Uk; a.V = V; a.dO = dO; a.rs = rs;
+    a.W = W_race; a.wt_hi = wt_hi; a.wt_lo = wt_lo; a.items = s.B * s.H * s.nseg;
     a.H = s.H; a.N = s.N; a.L = s.L; a.seg_len = s.seg_len; a.nseg = s.nseg; a.causal = s.causal;
     a.BHN = BHN;
     a.two_beta = 2.f * s.beta; a.beta = s.beta; a.inv_L = 1.f / (float)s.L;
-    LbArgs a1 = a, a2 = a, a3 = a;
-    a1.states = states_f; a1.out = du_q;
-    a2.states = states_b; a2.out = du_k;
-    a3.states = states_b; a3.out = dv_lr;
-    return dispatch<BwdFn>(s, a1, a2, a3, st);
+    a.states_f = states_f; a.states_b = states_b;
+    a.du_q = du_q; a.du_k = du_k; a.dv = dv_lr;
+    return dispatch<BwdFn>(s, a, st);
 }
 
 }  // namespace elsaa

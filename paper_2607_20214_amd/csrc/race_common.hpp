@@ -19,6 +19,11 @@ constexpr int kThreads = 256;
 constexpr int kPad = 8;
 constexpr size_t kMaxLds = 160 * 1024;
 
+// The helpers take the thread index as an argument (default threadIdx.x): a
+// kernel with several bodies passes each a copy that the compiler cannot
+// share between them, so one body's lane addresses are not kept in registers
+// through another.
+
 // sigmoid(x) and sigmoid(-x) from one hardware exp and reciprocal: with
 // e = exp(-|x|) in (0, 1], sigmoid(|x|) = 1 / (1 + e) and
 // sigmoid(-|x|) = e / (1 + e), each within a few ulp and without overflow.
@@ -59,9 +64,9 @@ struct RowTile {
     }
     // transposed operand: lane (i = lane % 16, g = lane / 16) receives column
     // c0 + i at rows kb + 8 g + j, j = 0..7
-    __device__ static __forceinline__ F col8(const S* t, int kb, int c0)
+    __device__ static __forceinline__ F col8(const S* t, int kb, int c0, int tx = threadIdx.x)
     {
-        const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+        const int lane = tx & 63, g = lane >> 4, i = lane & 15;
         const int r = kb + 8 * g;
         if constexpr (T::bytes == 2) {
             const bf16x4 lo = lds_read_tr4((const uint16_t*)(t + row(r + (i >> 2)) + c0 + 4 * (i & 3)));
@@ -146,23 +151,23 @@ struct StageRows {
     uint4 v[PT];
     float sc[SCALED ? PT : 1];
     int t0_, n_;
-    __device__ __forceinline__ void load(const S* X, int t0, int N, const float* scale = nullptr)
+    __device__ __forceinline__ void load(const S* X, int t0, int N, const float* scale = nullptr, int tx = threadIdx.x)
     {
         t0_ = t0;
         n_ = N;
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int it = threadIdx.x + j * kThreads;
+            const int it = tx + j * kThreads;
             const int r = min(t0 + it / CH, N - 1);
             v[j] = ldg16(X + (size_t)r * D + (it % CH) * PER);
             if constexpr (SCALED) sc[j] = scale[r];
         }
     }
-    __device__ __forceinline__ void store(S* t, float mul = 1.f)
+    __device__ __forceinline__ void store(S* t, float mul = 1.f, int tx = threadIdx.x)
     {
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int it = threadIdx.x + j * kThreads;
+            const int it = tx + j * kThreads;
             const int r = it / CH;
             if (t0_ + r >= n_) v[j] = make_uint4(0, 0, 0, 0);
             S* dst = t + Tl::row(r) + (it % CH) * PER;
@@ -193,9 +198,9 @@ struct URegs {
     // the loads carry no per-lane branches.
     // stride: floats per projection row (RP / 4 unless this workgroup holds
     // only some of the row's tables, U then pointing at its first table)
-    __device__ __forceinline__ void load(const float* U, int t0, int N, int stride = RP / 4)
+    __device__ __forceinline__ void load(const float* U, int t0, int N, int stride = RP / 4, int tx = threadIdx.x)
     {
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        const int lane = tx & 63, wv = tx >> 6;
         const int g = lane >> 4, col = lane & 15;
         const int tok = min(t0 + 16 * wv + col, N - 1);
 #pragma unroll
@@ -211,9 +216,9 @@ struct URegs {
 // feature RowTile (zero for padded tables and rows past N).
 template <class T, int RP>
 __device__ __forceinline__ void features_from(const URegs<RP>& ur, int t0, int N, int L, float two_beta,
-                                              typename T::store_t* ph)
+                                              typename T::store_t* ph, int tx = threadIdx.x)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = tx & 63, wv = tx >> 6;
     const int g = lane >> 4, col = lane & 15;
     const int tl = 16 * wv + col;
 #pragma unroll
@@ -242,9 +247,9 @@ __device__ __forceinline__ void features_from(const URegs<RP>& ur, int t0, int N
 // t = tanh(u) of the same tokens and tables into ts[token][4 * table + bit]
 // (the chain rule's input).
 template <int RP>
-__device__ __forceinline__ void tanh_rows(const URegs<RP>& ur, float (*ts)[RP / 4])
+__device__ __forceinline__ void tanh_rows(const URegs<RP>& ur, float (*ts)[RP / 4], int tx = threadIdx.x)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = tx & 63, wv = tx >> 6;
     const int g = lane >> 4, tl = 16 * wv + (lane & 15);
 #pragma unroll
     for (int m = 0; m < URegs<RP>::NU; ++m)
@@ -266,9 +271,9 @@ __device__ __forceinline__ void tanh_rows(const URegs<RP>& ur, float (*ts)[RP / 
 template <class T, int RP>
 __device__ __forceinline__ void chain_rule_t(f32x4 dphi, int qt, int tb, int L, float two_beta, float mul,
                                              const float (*ts)[RP / 4],
-                                             typename T::store_t (*du)[w_kdim<RP>() + kPad])
+                                             typename T::store_t (*du)[w_kdim<RP>() + kPad], int tx = threadIdx.x)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = tx & 63;
     const int g = lane >> 4, col = lane & 15;
     const int row = 16 * qt + col;
     // lane group g evaluates bit g's sigmoid pair; the groups then share them
