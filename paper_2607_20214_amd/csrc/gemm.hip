@@ -1,23 +1,24 @@
 // gemm.hip -- bfloat16 matrix-core GEMM for the dense projections around the
 // attention operator (Alg. 1 / Alg. 6: Q, K, V = X W_{Q,K,V}; O_head W_O).
 //
-// Two kernels.  Products whose M and N are multiples of 256 and K of 64 run
-// gemm_big_kernel (256 x 256 tiles, one workgroup per compute unit, 128 x 128
-// per wave with the accumulators in the accumulation registers; see the
-// large-tile section).  Every other shape runs gemm_kernel: workgroup tile
+// Two kernels: gemm_big_kernel (256 x 256 tiles, one workgroup per compute
+// unit, 128 x 128 per wave with the accumulators in the accumulation
+// registers; see the large-tile section) and gemm_kernel (workgroup tile
 // 128 x 128 x 64, four waves in a 2 x 2 grid, each wave a 64 x 64 block of
-// 4 x 4 accumulators of v_mfma_f32_16x16x32_bf16.  Both compute C^T tiles
-// (the B operand feeds the MFMA's first input) so that every lane ends with
-// four consecutive columns of one C row, which makes the stores 8- or
-// 16-byte vectors.
+// 4 x 4 accumulators of v_mfma_f32_16x16x32_bf16); plan_of chooses.  Both
+// take any M, N, K (multiples of 8): rows and columns past the matrix repeat
+// its last ones and are not stored, and a K range that is no multiple of 64
+// starts with its short K-tile, filled up with zeros, so the loop runs on
+// whole K-tiles without masks.  Both compute C^T tiles (the B operand feeds
+// the MFMA's first input) so that every lane ends with four consecutive
+// columns of one C row, which makes the stores 8- or 16-byte vectors.
 //
 // Operands are staged through LDS in the orientation in which they are
 // stored: a tile whose contraction dimension is contiguous is read with
 // 16-byte LDS loads; a tile stored the other way round ([K][M] for A^T,
 // [K][N] for B) is read with the gfx950 transposed LDS load, so no operand
-// is ever transposed in memory.  Global loads of the next K-tile are issued
-// into registers before the MFMAs of the current one (two LDS buffers, one
-// barrier per K-tile).
+// is ever transposed in memory.  Global loads run two K-tiles ahead in
+// registers (two LDS buffers, one barrier per K-tile).
 //
 // Long-K products with few output tiles (the weight gradients) split K over
 // workgroups; float32 partials go to the workspace and a second kernel sums
@@ -25,6 +26,7 @@
 // eight XCDs (own L2) works on a contiguous group of tiles.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.hpp"
 #include "elsaa.h"
@@ -57,6 +59,29 @@ __device__ __forceinline__ int64_t mat_offset(const Mat& m, int r, int c)
     return ((((int64_t)b * m.heads + h) * m.seq + n) << m.dh_shift) + e;
 }
 
+// 16 bytes at the uniform address q plus a per-lane byte offset < 2^31.
+__device__ __forceinline__ uint4 ldb16(const char* q, uint32_t off)
+{
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(q), (short)0, 0x7fffffff, 0x00027000);
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// mat_offset as a row part plus a column part.
+__device__ __forceinline__ int64_t row_part(const Mat& m, int r)
+{
+    if (m.heads == 0) return (int64_t)r * m.ld;
+    const int b = r / m.seq;
+    return ((int64_t)r + (int64_t)b * (m.heads - 1) * m.seq) << m.dh_shift;
+}
+__device__ __forceinline__ int64_t row_stride(const Mat& m) { return m.heads == 0 ? m.ld : ((int64_t)1 << m.dh_shift); }
+__device__ __forceinline__ int64_t col_part(const Mat& m, int c)
+{
+    if (m.heads == 0) return c;
+    return (((int64_t)(c >> m.dh_shift) * m.seq) << m.dh_shift) + (c & ((1 << m.dh_shift) - 1));
+}
+
 struct GArgs {
     Mat A, B, C;
     int M, N, K;
@@ -83,28 +108,82 @@ __device__ __forceinline__ void tile_of(const GArgs& a, int& sp, int& tm, int& t
     tn = r / gm;
 }
 
-// Global -> register staging of one K-tile of a stored operand.  KMAJOR:
-// the operand is stored [k][x] (x = m or n contiguous); else [x][k].
-template <bool KMAJOR>
-__device__ __forceinline__ void load_tile(const Mat& m, int x0, int xlim, int k0, int klim, uint4 (&r)[4])
-{
+// Global loads of one operand's K-tiles, rows (or columns) [x0, x0 + XT).
+// KMAJOR: the operand is stored [k][x] (x = m or n contiguous), thread tx
+// loads k-rows tx / TPR + RPC c at columns x0 + 8 (tx % TPR); else [x][k],
+// rows x0 + tx / 8 + 32 c at columns k0 + 8 (tx % 8).  x positions past xlim
+// repeat the last ones.  The byte offsets from the tile's first element are
+// formed once per thread (32 bits; an address in the K loop is then a scalar
+// base plus one register, no vector instruction), which needs a K-tile's
+// k-rows in one sequence (KMAJOR) or its columns in one head: fast_operand.
+template <bool KMAJOR, int XT>
+struct Stream {
+    static constexpr int C = XT * BK / 8 / kThreads;                    // 16-byte chunks per thread
+    static constexpr int TPR = KMAJOR ? XT / 8 : 8, RPC = kThreads / TPR;
+    const char* p;       // element (x0, 0) or (0, x0)
+    uint32_t off[C];
+    __device__ __forceinline__ void init(const Mat& m, int x0, int xlim)
+    {
+        const int r = threadIdx.x / TPR, c8 = 8 * (threadIdx.x % TPR);
+        p = (const char*)((const uint16_t*)m.p + (KMAJOR ? col_part(m, x0) : row_part(m, x0)));
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int id = threadIdx.x + kThreads * c;
-        int row, col;
-        bool ok;
-        if (KMAJOR) {
-            row = k0 + (id >> 4);
-            col = x0 + (id & 15) * 8;
-            ok = row < klim && col < xlim;
-        } else {
-            row = x0 + (id >> 3);
-            col = k0 + (id & 7) * 8;
-            ok = row < xlim && col < klim;
+        for (int c = 0; c < C; ++c) {
+            if (KMAJOR)
+                off[c] = (uint32_t)(((r + RPC * c) * row_stride(m) + col_part(m, min(x0 + c8, xlim - 8)) - col_part(m, x0)) * 2);
+            else
+                off[c] = (uint32_t)((row_part(m, min(x0 + r + RPC * c, xlim - 1)) - row_part(m, x0) + c8) * 2);
         }
-        r[c] = ok ? ldg16((const uint16_t*)m.p + mat_offset(m, row, col)) : make_uint4(0, 0, 0, 0);
     }
-}
+    // first element of the K-tile at k0 (uniform)
+    __device__ __forceinline__ const char* tile(const Mat& m, int k0) const
+    {
+        return p + 2 * (KMAJOR ? row_part(m, k0) : col_part(m, k0));
+    }
+    // (as a buffer load: scalar base, one offset register; written as pointer
+    // arithmetic the compiler keeps 64-bit offsets and adds in the loop)
+    __device__ __forceinline__ uint4 chunk(const char* q, int c) const { return ldb16(q, off[c]); }
+    __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[C]) const
+    {
+        const char* q = tile(m, k0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) r[c] = chunk(q, c);
+    }
+    // a K-tile of kn <= 64 values of k, the rest zero
+    __device__ __forceinline__ void load_short(const Mat& m, int k0, int kn, uint4 (&r)[C]) const
+    {
+        const char* q = tile(m, k0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int k = KMAJOR ? (int)threadIdx.x / TPR + RPC * c : 8 * ((int)threadIdx.x % TPR);
+            r[c] = k < kn ? chunk(q, c) : make_uint4(0, 0, 0, 0);
+        }
+    }
+};
+
+// The same K-tiles element by element (any layout): 128-row tiles of operands
+// that Stream does not take.
+template <bool KMAJOR>
+struct StreamAny {
+    static constexpr int C = 4;
+    int x0, xlim;
+    __device__ __forceinline__ void init(const Mat&, int x0_, int xlim_)
+    {
+        x0 = x0_;
+        xlim = xlim_;
+    }
+    __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[C]) const { load_short(m, k0, BK, r); }
+    __device__ __forceinline__ void load_short(const Mat& m, int k0, int kn, uint4 (&r)[C]) const
+    {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int id = threadIdx.x + kThreads * c;
+            const int k = KMAJOR ? id >> 4 : (id & 7) * 8, x = x0 + (KMAJOR ? (id & 15) * 8 : id >> 3);
+            const bool ok = k < kn && x < xlim;
+            const uint16_t* q = (const uint16_t*)m.p + (ok ? (KMAJOR ? mat_offset(m, k0 + k, x) : mat_offset(m, x, k0 + k)) : 0);
+            r[c] = ok ? ldg16(q) : make_uint4(0, 0, 0, 0);
+        }
+    }
+};
 
 template <bool KMAJOR>
 __device__ __forceinline__ void store_tile(uint16_t* s, const uint4 (&r)[4])
@@ -130,7 +209,7 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* s, int x0, int ks)
     return *(const bf16x8*)&s[(x0 + i) * kLdD + 32 * ks + 8 * g];
 }
 
-template <bool TA, bool BKN, bool OUT_BF16>
+template <bool TA, bool BKN, bool OUT_BF16, bool ANY>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint16_t sa[2][kTileElems];
@@ -140,6 +219,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
     const int m0 = tm * BM, n0 = tn * BN;
     const int kb = sp * a.kper, ke = min(a.K, kb + a.kper);
     const int nkt = (ke - kb + BK - 1) / BK;
+    const int kfirst = ke - kb - (nkt - 1) * BK;          // the first K-tile's values of k
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w & 1, wn = w >> 1;
     const int g = lane >> 4, col = lane & 15;
@@ -150,21 +230,35 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[j][i] = f32x4{0, 0, 0, 0};
 
-    uint4 ra[4], rb[4];
-    load_tile<TA>(a.A, m0, a.M, kb, ke, ra);
-    load_tile<BKN>(a.B, n0, a.N, kb, ke, rb);
-    store_tile<TA>(sa[0], ra);
-    store_tile<BKN>(sb[0], rb);
+    typename std::conditional<ANY, StreamAny<TA>, Stream<TA, BM>>::type gA;
+    typename std::conditional<ANY, StreamAny<BKN>, Stream<BKN, BN>>::type gB;
+    gA.init(a.A, m0, a.M);
+    gB.init(a.B, n0, a.N);
+    // LDS buffer t & 1 holds K-tile t, register set (t + 1) & 1 K-tile t + 1,
+    // and iteration t requests K-tile t + 2: a load has two iterations to
+    // arrive, which is what bounds short products (few workgroups, each
+    // K-tile's 32 products a fifth of a memory round trip).  Tile indices
+    // past the end repeat the last tile (never read).
+    uint4 ra[2][4], rb[2][4];
+    auto k_of = [&](int t) { return kb + (t > 0 ? kfirst + (min(t, nkt - 1) - 1) * BK : 0); };
+    gA.load_short(a.A, kb, kfirst, ra[0]);
+    gB.load_short(a.B, kb, kfirst, rb[0]);
+    if (nkt > 1) {
+        gA.load(a.A, k_of(1), ra[1]);
+        gB.load(a.B, k_of(1), rb[1]);
+    }
+    store_tile<TA>(sa[0], ra[0]);
+    store_tile<BKN>(sb[0], rb[0]);
     __syncthreads();
 
-    for (int t = 0; t < nkt; ++t) {
-        const bool more = t + 1 < nkt;
-        if (more) {
-            load_tile<TA>(a.A, m0, a.M, kb + (t + 1) * BK, ke, ra);
-            load_tile<BKN>(a.B, n0, a.N, kb + (t + 1) * BK, ke, rb);
+    auto step = [&](int t, auto parity) {
+        constexpr int P = decltype(parity)::value;        // t & 1
+        if (t + 2 < nkt) {
+            gA.load(a.A, k_of(t + 2), ra[P]);
+            gB.load(a.B, k_of(t + 2), rb[P]);
         }
-        const uint16_t* A_ = sa[t & 1];
-        const uint16_t* B_ = sb[t & 1];
+        const uint16_t* A_ = sa[P];
+        const uint16_t* B_ = sb[P];
 #pragma unroll
         for (int ks = 0; ks < BK / 32; ++ks) {
             bf16x8 xf[4], yf[4];
@@ -178,11 +272,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
                 for (int i = 0; i < 4; ++i)
                     acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[j], yf[i], acc[j][i], 0, 0, 0);
         }
-        if (more) {
-            store_tile<TA>(sa[(t + 1) & 1], ra);
-            store_tile<BKN>(sb[(t + 1) & 1], rb);
+        if (t + 1 < nkt) {
+            store_tile<TA>(sa[1 - P], ra[1 - P]);
+            store_tile<BKN>(sb[1 - P], rb[1 - P]);
         }
         __syncthreads();
+    };
+    for (int t = 0; t < nkt; t += 2) {
+        step(t, std::integral_constant<int, 0>{});
+        if (t + 1 < nkt) step(t + 1, std::integral_constant<int, 1>{});
     }
 
     // lane holds C[m0 + 64 wm + 16 i + col][n0 + 64 wn + 16 j + 4 g + (0..3)]
@@ -209,8 +307,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
 }
 
 // ---------------------------------------------------------------- large tiles
-// Workgroup tile 256 x 256 x 64 for products whose M and N are multiples of
-// 256 and K of 64: four waves in a 2 x 2 grid, each a 128 x 128 block of
+// Workgroup tile 256 x 256 x 64: four waves in a 2 x 2 grid, each a 128 x 128 block of
 // 8 x 8 accumulators (256 float32 per lane, held in the accumulation
 // registers; one workgroup per compute unit).  Per 32-wide k-step a wave
 // reads 16 operand fragments for 64 matrix-core operations, half the LDS
@@ -226,60 +323,6 @@ static_assert(BK * kLdT <= kTile, "tile orientations fit one buffer");
 static_assert(BK == 64, "two 32-wide k-steps per K-tile");
 constexpr int kChunks = BM * BK / 8 / kThreads;   // 16-byte chunks per thread per operand tile
 static_assert(kChunks == 8, "one chunk of each operand per group of eight operations");
-
-// Element offset of (row r, column c) split into a row part and a column
-// part.  Within an aligned block of rows that does not cross a sequence
-// (head-major operands have seq % 256 == 0 on this path), the row part is
-// affine in r with stride row_stride(); blk0 is the block's first row.
-__device__ __forceinline__ int64_t row_part(const Mat& m, int r, int blk0)
-{
-    if (m.heads == 0) return (int64_t)r * m.ld;
-    const int b = blk0 / m.seq;
-    return ((int64_t)r + (int64_t)b * (m.heads - 1) * m.seq) << m.dh_shift;
-}
-__device__ __forceinline__ int64_t row_stride(const Mat& m) { return m.heads == 0 ? m.ld : ((int64_t)1 << m.dh_shift); }
-__device__ __forceinline__ int64_t col_part(const Mat& m, int c)
-{
-    if (m.heads == 0) return c;
-    return (((int64_t)(c >> m.dh_shift) * m.seq) << m.dh_shift) + (c & ((1 << m.dh_shift) - 1));
-}
-
-// Global -> registers: K-tile [k0, k0 + 64) of the operand rows [x0, x0 + 256).
-// KMAJOR: stored [k][x], thread tx loads k-rows k0 + tx / 32 + 8 c at columns
-// x0 + 8 (tx % 32); else stored [x][k], rows x0 + tx / 8 + 32 c at k0 + 8 (tx % 8).
-// Each address is a per-thread offset fixed for the whole tile plus a
-// workgroup-uniform offset of the K-tile: the rows of a K-tile (KMAJOR) or of
-// the tile (else) lie in one sequence, and 64 consecutive k of a [x][k]
-// operand in one head (head widths >= 64 on this path).
-template <bool KMAJOR>
-struct Stream {
-    const uint16_t* p;
-    int64_t rs;      // element stride between rows of one sequence
-    int64_t toff;    // this thread's fixed element offset
-    __device__ __forceinline__ void init(const Mat& m, int x0)
-    {
-        const int tx = threadIdx.x;
-        p = (const uint16_t*)m.p;
-        rs = row_stride(m);
-        if (KMAJOR) toff = (int64_t)(tx >> 5) * rs + col_part(m, x0 + (tx & 31) * 8);
-        else toff = row_part(m, x0 + (tx >> 3), x0) + (tx & 7) * 8;
-    }
-    // first element of K-tile k0 for chunk 0 (uniform part only)
-    __device__ __forceinline__ const uint16_t* tile(const Mat& m, int k0) const
-    {
-        return p + (KMAJOR ? row_part(m, k0, k0) : col_part(m, k0));
-    }
-    __device__ __forceinline__ uint4 chunk(const uint16_t* q, int c) const
-    {
-        return ldg16(q + (KMAJOR ? 8 : 32) * c * rs + toff);
-    }
-    __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[kChunks]) const
-    {
-        const uint16_t* q = tile(m, k0);
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) r[c] = chunk(q, c);
-    }
-};
 
 template <bool KMAJOR>
 __device__ __forceinline__ void store1(uint16_t* s, uint4 v, int c)
@@ -333,7 +376,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     tile_of(a, sp, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int kb = sp * a.kper, ke = min(a.K, kb + a.kper);
-    const int nkt = (ke - kb) / BK;
+    const int nkt = (ke - kb + BK - 1) / BK;
+    const int kfirst = ke - kb - (nkt - 1) * BK;          // the first K-tile's values of k
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w & 1, wn = w >> 1;
     const int g = lane >> 4, col = lane & 15;
@@ -344,10 +388,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[j][i] = f32x4{0, 0, 0, 0};
 
-    Stream<TA> gA;
-    Stream<BKN> gB;
-    gA.init(a.A, m0);
-    gB.init(a.B, n0);
+    Stream<TA, BM> gA;
+    Stream<BKN, BN> gB;
+    gA.init(a.A, m0, a.M);
+    gB.init(a.B, n0, a.N);
+    auto k_of = [&](int t) { return kb + (t > 0 ? kfirst + (min(t, nkt - 1) - 1) * BK : 0); };
     // Pipeline: LDS buffer t & 1 holds K-tile t, the registers K-tile t + 1.
     // The first half of an iteration runs k-step 0 of tile t (fragments
     // already read) in eight groups of eight operations; before group i it
@@ -361,15 +406,15 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     // last tile (the redundant loads and stores are never read), so the
     // groups carry no branches.
     uint4 ra[kChunks], rb[kChunks];
-    gA.load(a.A, kb, ra);
-    gB.load(a.B, kb, rb);
+    gA.load_short(a.A, kb, kfirst, ra);
+    gB.load_short(a.B, kb, kfirst, rb);
     store<TA>(sa[0], ra);
     store<BKN>(sb[0], rb);
     {
         // same issue order as the loop's loads (A and B chunks alternating),
         // so the stores' waits count exactly across the loop entry
-        const uint16_t* qa = gA.tile(a.A, kb + min(1, nkt - 1) * BK);
-        const uint16_t* qb = gB.tile(a.B, kb + min(1, nkt - 1) * BK);
+        const char* qa = gA.tile(a.A, k_of(min(1, nkt - 1)));
+        const char* qb = gB.tile(a.B, k_of(min(1, nkt - 1)));
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) {
             ra[i] = gA.chunk(qa, i);
@@ -389,9 +434,9 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
         const uint16_t* B_ = sb[t & 1];
         uint16_t* An = sa[(t + 1) & 1];
         uint16_t* Bn = sb[(t + 1) & 1];
-        const int k2 = kb + min(t + 2, nkt - 1) * BK;
-        const uint16_t* qa = gA.tile(a.A, k2);
-        const uint16_t* qb = gB.tile(a.B, k2);
+        const int k2 = k_of(min(t + 2, nkt - 1));
+        const char* qa = gA.tile(a.A, k2);
+        const char* qb = gB.tile(a.B, k2);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             x1[i] = frag<BKN>(B_, 128 * wn + 16 * i, 1);
@@ -419,6 +464,15 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     __syncthreads();
     mfma_drain();
 
+    // row m's offset in C; a whole tile inside one sequence takes it from its
+    // first row's (no division, no bounds)
+    const int64_t c0 = row_part(a.C, m0), cs_ = row_stride(a.C);
+    const bool whole = m0 + BM <= a.M && n0 + BN <= a.N &&
+                       (a.C.heads == 0 || m0 / a.C.seq == (m0 + BM - 1) / a.C.seq);
+    auto epilogue = [&](auto whole_tile) {
+    constexpr bool WHOLE = decltype(whole_tile)::value;
+    auto c_row = [&](int m) { return WHOLE ? c0 + (m - m0) * cs_ : row_part(a.C, m); };
+    auto inside = [&](int m, int n) { return WHOLE || (m < a.M && n < a.N); };
     if (OUT_BF16 && a.splits == 1) {
         // bf16 output: the float32 accumulators pass through LDS (each wave
         // its own 64 x 128 block per half, row stride 132) and leave as
@@ -444,7 +498,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
                 o.z = f32_to_bf16(y[0]) | ((uint32_t)f32_to_bf16(y[1]) << 16);
                 o.w = f32_to_bf16(y[2]) | ((uint32_t)f32_to_bf16(y[3]) << 16);
                 const int m = m0 + 128 * wm + 64 * hh + r, n = n0 + 128 * wn + c8;
-                stg16((uint16_t*)a.C.p + row_part(a.C, m, m0) + col_part(a.C, n), o);
+                if (inside(m, n)) stg16((uint16_t*)a.C.p + c_row(m) + col_part(a.C, n), o);
             }
             __syncthreads();
         }
@@ -455,14 +509,19 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int m = m0 + 128 * wm + 16 * i + col;
-        const int64_t ro = a.splits > 1 ? ((int64_t)sp * a.M + m) * a.N : row_part(a.C, m, m0);
+        if (!inside(m, 0)) continue;
+        const int64_t ro = a.splits > 1 ? ((int64_t)sp * a.M + m) * a.N : c_row(m);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int n = n0 + 128 * wn + 16 * j + 4 * g;
+            if (!inside(0, n)) continue;
             if (a.splits > 1) *(f32x4*)(a.part + ro + n) = acc[j][i];
             else *(f32x4*)((float*)a.C.p + ro + col_part(a.C, n)) = acc[j][i];
         }
     }
+    };
+    if (whole) epilogue(std::true_type{});
+    else epilogue(std::false_type{});
 }
 
 }  // namespace big
@@ -489,42 +548,75 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* part, Mat
 
 struct Plan {
     bool big;                 // 256 x 256 tiles (gemm_big_kernel)
+    bool any;                 // 128 x 128 tiles with StreamAny
     int tiles_m, tiles_n, splits, kper;
     size_t ws_bytes;
 };
 
-// The large-tile kernel takes whole tiles only, head-major operands whose
-// sequences hold whole 256-row blocks (so no tile or K-tile crosses one) and
-// head-major A / B with heads at least 64 wide.
-bool big_fits(const elsaa_gemm_desc* d)
+// Whether Stream can read an operand stored as rows x cols: `kmajor` ones
+// need every K-tile's 64 rows in one sequence (a single sequence, or whole
+// 64-row pieces of several), the others its 64 columns in one head; offsets
+// within a 256-row tile and a K-tile must fit 32 bits.
+bool fast_operand(bool kmajor, int rows, int cols, int64_t ld, int heads, int seq)
 {
-    if (d->M % big::BM || d->N % big::BN || d->K % big::BK) return false;
-    const bool hm = d->a_heads > 0 || d->b_heads > 0 || d->c_heads > 0;
-    if (hm && (d->seq <= 0 || d->seq % 256 != 0)) return false;
-    const int a_cols = d->trans_a ? d->M : d->K, b_cols = d->trans_b ? d->K : d->N;
-    if (d->a_heads > 0 && a_cols / d->a_heads < 64) return false;
-    if (d->b_heads > 0 && b_cols / d->b_heads < 64) return false;
-    return true;
+    const int64_t lim = (int64_t)1 << 31;
+    if (heads <= 0) return ld >= 0 && ld < lim / 512;
+    if (seq < 1 || cols / heads < 8) return false;                     // (refused by check_mat)
+    const int64_t dh = cols / heads, plane = (int64_t)seq * dh * 2;     // bytes of one head's rows
+    if (kmajor) return (seq >= rows || seq % BK == 0) && (256 / dh + 2) * plane < lim;
+    return dh % BK == 0 && (256 / (int64_t)seq + 2) * heads * plane < lim;
 }
 
 Plan plan_of(const elsaa_gemm_desc* d)
 {
     Plan p;
-    p.big = big_fits(d);
-    const int bm = p.big ? big::BM : BM, bn = p.big ? big::BN : BN, bk = p.big ? big::BK : BK;
-    // workgroups resident per compute unit (256 compute units)
-    const int fill = p.big ? 256 : 512;
-    p.tiles_m = (d->M + bm - 1) / bm;
-    p.tiles_n = (d->N + bn - 1) / bn;
-    const int tiles = p.tiles_m * p.tiles_n;
-    const int ktiles = (d->K + bk - 1) / bk;
-    int splits = 1;
-    // fewer tiles than resident workgroups and a long K: split K into as
-    // many parts as fit in one round of resident workgroups, keeping at
-    // least 8 K-tiles per split
-    if (tiles < fill && ktiles >= 16) splits = std::max(1, std::min(fill / tiles, ktiles / 8));
-    const int per = (ktiles + splits - 1) / splits;
-    p.kper = per * bk;
+    const int ar = d->trans_a ? d->K : d->M, ac = d->trans_a ? d->M : d->K;
+    const int br = d->trans_b ? d->N : d->K, bc = d->trans_b ? d->K : d->N;
+    p.any = !fast_operand(d->trans_a != 0, ar, ac, d->lda, d->a_heads, d->seq) ||
+            !fast_operand(d->trans_b == 0, br, bc, d->ldb, d->b_heads, d->seq);
+    const int ktiles = (d->K + BK - 1) / BK;
+    // Estimated microseconds of a tile size and split count.  A round is the
+    // workgroups resident at once on 256 compute units (256 large tiles or
+    // 512 small ones); measured per K-tile 1.55 us for a round of large
+    // tiles (1040 - 1140 TFLOP/s at M 9000 .. 32768), 1.05 us for a full and
+    // 0.8 of that for an at most half full round of small ones (870 TFLOP/s
+    // at M 9000 x N 6144 x K 2048; one workgroup a compute unit at M 1000),
+    // 1.25 where both operands are read transposed (dW: 670 TFLOP/s), about
+    // 2.5 us for a round's first loads and last stores.  Splitting K costs
+    // a launch and the partials' way to memory and back (6 TB/s: mostly the
+    // memory-side cache).  The lines this
+    // draws: M 9000, d_model 2048: QKV 219 us large against 272 small, dX
+    // (288 large tiles, a second round of 32) 284 against 273; M 1000 small
+    // throughout (16 - 22 us against 28 - 34).
+    const double small_us = d->trans_a && !d->trans_b ? 1.25 : 1.05;
+    auto estimate = [&](bool big, int splits) {
+        const int t = big ? big::BM : BM, fill = big ? 256 : 512;
+        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
+        const int per = (ktiles + splits - 1) / splits;
+        const int wgs = tiles * ((ktiles + per - 1) / per), rem = wgs % fill;
+        const double rounds = wgs / fill + (rem == 0 ? 0. : !big && 2 * rem <= fill ? 0.8 : 1.);
+        const double reduce = splits > 1 ? 5. + 2e-6 * splits * (double)d->M * d->N * 4 / 6. : 0.;
+        return rounds * (per * (big ? 1.55 : small_us) + 2.5) + reduce;
+    };
+    double best = 0.;
+    for (int kind = 0; kind < (p.any ? 1 : 2); ++kind) {
+        const int t = kind ? big::BM : BM, fill = kind ? 256 : 512;
+        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
+        // at least 8 K-tiles per split, at most one round of workgroups
+        const int most = tiles < fill ? std::max(1, std::min(fill / tiles, ktiles / 8)) : 1;
+        for (int splits = 1; splits <= most; ++splits) {
+            const double e = estimate(kind == 1, splits);
+            if ((kind == 0 && splits == 1) || e < best) {
+                best = e;
+                p.big = kind == 1;
+                p.splits = splits;
+            }
+        }
+    }
+    const int t = p.big ? big::BM : BM;
+    p.tiles_m = (d->M + t - 1) / t;
+    p.tiles_n = (d->N + t - 1) / t;
+    p.kper = (ktiles + p.splits - 1) / p.splits * BK;
     p.splits = (d->K + p.kper - 1) / p.kper;
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * d->M * d->N * sizeof(float) : 0;
     return p;
@@ -623,7 +715,8 @@ int elsaa_gemm(const elsaa_gemm_desc* d, const void* A, const void* B, void* C, 
 #define ELSAA_GEMM_CASE(TA, BKN, OB)                                                                 \
     if (d->trans_a == TA && bkn == BKN && out_bf16 == OB) {                                           \
         if (p.big) ELSAA_LAUNCH("gemm", (big::gemm_big_kernel<TA, BKN, OB>), grid, block, 0, stream, a); \
-        else ELSAA_LAUNCH("gemm", (gemm_kernel<TA, BKN, OB>), grid, block, 0, stream, a);              \
+        else if (p.any) ELSAA_LAUNCH("gemm", (gemm_kernel<TA, BKN, OB, true>), grid, block, 0, stream, a); \
+        else ELSAA_LAUNCH("gemm", (gemm_kernel<TA, BKN, OB, false>), grid, block, 0, stream, a);         \
     }
     ELSAA_GEMM_CASE(0, 0, 0) ELSAA_GEMM_CASE(0, 0, 1) ELSAA_GEMM_CASE(0, 1, 0) ELSAA_GEMM_CASE(0, 1, 1)
     ELSAA_GEMM_CASE(1, 0, 0) ELSAA_GEMM_CASE(1, 0, 1) ELSAA_GEMM_CASE(1, 1, 0) ELSAA_GEMM_CASE(1, 1, 1)

@@ -34,8 +34,7 @@ def _check(got, ref, out_dtype, what=""):
         assert (err <= bound).all(), f"{what}: worst element ratio {(err / bound).max():.3f}"
 
 
-# ragged and small shapes (128 x 128 tiles) and whole 256 x 256 tiles with K
-# a multiple of 64 (the large-tile kernel)
+# ragged and small shapes, and whole tiles
 SHAPES = [(200, 136, 72), (384, 256, 320), (8, 8, 8), (512, 256, 128), (256, 768, 192)]
 
 
@@ -66,7 +65,7 @@ def test_gemm_split_k(ta, od):
 
 @pytest.mark.parametrize("ta,tb,od", [(1, 0, torch.float32), (1, 1, torch.bfloat16), (0, 1, torch.float32)])
 def test_gemm_split_k_large_tiles(ta, tb, od):
-    """Whole 256 x 256 tiles with a long K: the large-tile kernel split over K."""
+    """Whole tiles with a long K, split over K."""
     M, N, K = 256, 512, 8192
     A = W.random_matrix(45 + ta, 1, (K, M) if ta else (M, K))
     B = W.random_matrix(45 + tb, 2, (N, K) if tb else (K, N))
@@ -75,6 +74,44 @@ def test_gemm_split_k_large_tiles(ta, tb, od):
     desc = E._GemmDesc(M, N, K, ta, tb, M if ta else K, K if tb else N, N, 0, 0, 0, 0, 0)
     assert E.gemm_workspace_bytes(desc) > 0
     _check(got, oracle.gemm(A, B, ta, tb), od, "split-K large tiles")
+
+
+# large tiles with every edge ragged (M 11 x 256 + 24, N 12 x 256 + 8, K 15 x
+# 64 + 40: the short K-tile comes first), and split over a ragged K
+@pytest.mark.parametrize("shape,ta,tb,od", [
+    ((2840, 3080, 1000), ta, tb, torch.bfloat16 if ta == tb else torch.float32)
+    for ta, tb in itertools.product([0, 1], repeat=2)] + [((1016, 3080, 9000), 1, 0, torch.float32),
+                                                          ((1016, 3080, 8968), 0, 1, torch.bfloat16)])
+def test_gemm_large_tiles_ragged(shape, ta, tb, od):
+    M, N, K = shape
+    A = W.random_matrix(46 + ta, 1, (K, M) if ta else (M, K))
+    B = W.random_matrix(46 + tb, 2, (N, K) if tb else (K, N))
+    got = E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=od)
+    torch.cuda.synchronize()
+    _check(got, oracle.gemm(A, B, ta, tb), od, f"{shape}")
+
+
+# head-major operands whose sequences are not whole tiles: K-tiles and row
+# tiles that cross sequences (72, 200 tokens), 64-row pieces of several
+# sequences (192), one ragged sequence (1000)
+@pytest.mark.parametrize("Bb,S,H,dh", [(5, 72, 4, 64), (3, 200, 2, 32), (3, 192, 4, 64), (1, 1000, 4, 128),
+                                       (9, 320, 16, 64)])
+def test_gemm_head_major_ragged_sequences(Bb, S, H, dh):
+    dm, n = H * dh, Bb * S
+    X, Y = (W.random_matrix(90, i, (n, dm)) for i in (1, 2))
+    Wm = W.random_matrix(90, 3, (dm, dm), 0.1)
+    O = W.random_matrix(90, 4, (Bb, H, S, dh))
+    out = torch.empty(Bb, H, S, dh, dtype=torch.bfloat16, device=DEV)
+    E.gemm(_t(X), _t(Wm), out=out)
+    y = E.gemm(_t(O), _t(Wm), trans_b=True, out_dtype=torch.float32)
+    dw = E.gemm(_t(O), _t(Y), trans_a=True, out_dtype=torch.float32)
+    dw2 = E.gemm(_t(X), _t(O), trans_a=True, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    Om = oracle.heads_to_matrix(O)
+    _check(out, oracle.matrix_to_heads(oracle.gemm(X, Wm), H, S), torch.bfloat16, "out")
+    _check(y, oracle.gemm(Om, Wm, False, True), torch.float32, "y")
+    _check(dw, oracle.gemm(Om, Y, True, False), torch.float32, "dw")
+    _check(dw2, oracle.gemm(X, Om, True, False), torch.float32, "dw2")
 
 
 def test_gemm_repeatable():
@@ -89,8 +126,7 @@ def test_gemm_repeatable():
 @pytest.mark.parametrize("Bb,S,H,dh", [(2, 96, 4, 16), (2, 256, 4, 64)])
 def test_block_projections_head_major(Bb, S, H, dh):
     """Every product of one attention block (fwd and bwd) with the attention
-    tensors in head-major [B, H, S, dh] storage (the second size takes the
-    large-tile kernel for all six products)."""
+    tensors in head-major [B, H, S, dh] storage."""
     dm = H * dh
     X = W.random_matrix(60, 1, (Bb * S, dm))
     Wqkv = W.random_matrix(60, 2, (dm, 3 * dm), 0.1)
