@@ -896,8 +896,10 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<D, BQ>())) void sparse_bwd_blo
         const int x = item % a.nbx;
         k.bh = (size_t)(item / a.nbx);                   // b * H + h
         if (MODE == kLevels && !FULL) {
-            // level lists of any even length: ceil(h / QB) blocks per list of
-            // h entries, the last one short (no zero tokens: unpadded levels)
+            // level lists of any length: ceil(h / QB) blocks per list of h
+            // entries, the last one short; a padded recursion's query lists
+            // hold zero tokens (-1), which are masked like a short block's
+            // missing queries
             int level = 0, first = 0;
             for (;;) {
                 const int cnt = ((a.lt.len[level + 1] + QB - 1) / QB) << level;
@@ -965,7 +967,7 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<D, BQ>())) void sparse_bwd_blo
         for (int j = 0; j < PT; ++j) {
             const int r = 64 * t + TD::row_of(j, tx);
             if constexpr (kFull) ix.qtk[t][j] = k.ql[(uint32_t)r];
-            else if constexpr (kClamp) ix.qtk[t][j] = k.ql[(uint32_t)min(r, k.nv - 1)];
+            else if constexpr (kClamp) ix.qtk[t][j] = max(k.ql[(uint32_t)min(r, k.nv - 1)], 0);
             else ix.qtk[t][j] = r < k.nv ? k.ql[(uint32_t)r] : -1;
         }
         const int r = 64 * t + (tx & 63);
@@ -1248,25 +1250,41 @@ void launch_blocks(const char* name, BArgs a, int nbx, int BH, hipStream_t st)
     ELSAA_LAUNCH(name, kern, dim3(grid), dim3(BQ * 4), 0, st, a);
 }
 
-// causal b = 256 levels run as two 128-key halves per block (bf16, no
-// neighbouring blocks, no padded level)
-bool block_halves(const Shape& s)
+// Blocks of QB entries in the lists of every causal level (the last block of
+// a list may be short).
+int level_blocks(const Shape& s, int qb)
 {
-    return s.causal && s.bf16 && s.Lv > 0 && s.k == 256 && s.neighbors == 0 && !s.lt.padded;
+    int n = 0;
+    for (int l = 0; l < s.Lv; ++l) n += ((s.lt.len[l + 1] + qb - 1) / qb) << l;
+    return n;
+}
+
+// The causal levels with blocks of QB: whole blocks throughout (N = n_leaf
+// 2^Lv with n_leaf a multiple of QB), or lists of any length.
+template <class T, int D, int BQ, int QB>
+void launch_level_blocks(const Shape& s, const BArgs& a, hipStream_t st)
+{
+    const int nbx = level_blocks(s, QB);
+    if (!s.lt.padded && s.n_leaf % QB == 0)
+        launch_blocks<T, D, BQ, kLevels, QB, true>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
+    else launch_blocks<T, D, BQ, kLevels, QB, false>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
 }
 
 template <class T, int D>
 hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
 {
     hipError_t e;
-    // whole-block kernel: b in {64, 128}, blocks never straddle a segment;
-    // b = 128 only where its registers fit without spilling (bf16 storage;
-    // non-causal blocks, which also form the low-rank parts, only at d_h 64);
-    // causal b = 256 (block_halves) as two 128-key halves per block
+    // whole-block kernel: b in {64, 128}; b = 128 only where its registers
+    // fit without spilling (bf16 storage; non-causal blocks, which also form
+    // the low-rank parts, only at d_h 64); causal b = 256 in bf16 as two
+    // 128-key halves per block.  Level lists that end in a short block or
+    // hold zero tokens take it too: its one pass reads each row once where
+    // the dQ and dK / dV pair reads them twice (16 heads, d_h 128, N = 11111,
+    // lists of 174 to 5556 entries: b = 128 backward 822 -> 709 us, of which
+    // the levels 328 -> 272; b = 256 838 -> 764; N = 30000, b = 256 2455 -> 2137)
     const int bq = s.k;
     const bool fits128 = T::bytes == 2 && (s.causal || D == 64);
-    const bool whole = (bq == 64 || (bq == 128 && fits128)) && s.neighbors == 0 &&
-                       (s.causal ? (!s.lt.padded && s.n_leaf % bq == 0) : true);
+    const bool whole = (bq == 64 || (bq == 128 && fits128) || (bq == 256 && s.causal && T::bytes == 2)) && s.neighbors == 0;
     if (!s.causal) {
         if (whole) {
             if (!(parts & kSparseFinalQ)) return hipSuccess;
@@ -1289,22 +1307,10 @@ hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
     }
     if (s.Lv > 0 && (parts & kSparseLevels)) {
         if (whole) {
-            const int nbx = s.Lv * (s.N / 2) / bq;
-            if (bq == 64) launch_blocks<T, D, 64, kLevels>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
-            else if constexpr (T::bytes == 2) launch_blocks<T, D, 128, kLevels>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        } else if (block_halves(s)) {
-            // 256-key blocks as two 128-key halves in turn; a level whose
-            // half length is not a multiple of 256 ends its lists with a short block
-            if (s.n_leaf % 256 == 0) {
-                const int nbx = s.Lv * (s.N / 2) / 256;
-                if constexpr (T::bytes == 2)
-                    launch_blocks<T, D, 128, kLevels, 256>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
-            } else {
-                int nbx = 0;
-                for (int l = 0; l < s.Lv; ++l) nbx += ((s.lt.len[l + 1] + 255) / 256) << l;
-                if constexpr (T::bytes == 2)
-                    launch_blocks<T, D, 128, kLevels, 256, false>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
+            if (bq == 64) launch_level_blocks<T, D, 64, 64>(s, a, st);
+            else if constexpr (T::bytes == 2) {
+                if (bq == 128) launch_level_blocks<T, D, 128, 128>(s, a, st);
+                else launch_level_blocks<T, D, 128, 256>(s, a, st);
             }
             if ((e = hipGetLastError()) != hipSuccess) return e;
         } else {

@@ -70,6 +70,27 @@ def test_ragged_causal(w):
     _check(w)
 
 
+# the whole-block level backward on lists that end in a short block and on
+# padded ones (zero tokens in the query lists): every block size it takes,
+# halves shorter than a block, a last block of one entry, several zero tokens
+BLOCK_CASES = [
+    _w("c-bf16-d128-k64-777-padded", 1, 2, 777, 128, 64, 64, "bf16", 0),
+    _w("c-bf16-d64-k64-1155-padded", 1, 1, 1155, 64, 64, 32, "bf16", 0, recipe="clustered"),
+    _w("c-bf16-d128-k128-1111-padded", 1, 2, 1111, 128, 128, 64, "bf16", 0, recipe="clustered"),
+    _w("c-bf16-d64-k128-1032-one-entry-block", 1, 2, 1032, 64, 128, 64, "bf16", 130),
+    _w("c-bf16-d128-k128-300-half-shorter", 2, 1, 300, 128, 128, 64, "bf16", 80),
+    _w("c-bf16-d128-k256-2051-padded", 1, 2, 2051, 128, 256, 64, "bf16", 0),
+    _w("c-bf16-d64-k256-1001-half-shorter", 1, 1, 1001, 64, 256, 64, "bf16", 130),
+    _w("c-f32-d64-k64-387-padded", 1, 2, 387, 64, 64, 32, "f32", 0),
+    _w("c-f32-d128-k64-650", 1, 1, 650, 128, 64, 64, "f32", 0, recipe="clustered"),
+]
+
+
+@pytest.mark.parametrize("w", BLOCK_CASES, ids=[w.name for w in BLOCK_CASES])
+def test_ragged_causal_whole_blocks(w):
+    _check(w)
+
+
 def test_ragged_causal_with_neighbours():
     _check(_w("c-bf16-d128-2000-leaf250-nbr1", 1, 1, 2000, 128, 64, 128, "bf16", 300, seed=81), neighbors=1)
 
