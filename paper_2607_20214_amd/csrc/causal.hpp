@@ -28,13 +28,16 @@ namespace elsaa {
 
 constexpr int kMaxLevels = 26;
 constexpr int kRowTile = 64;
+constexpr int kWideTile = 128;   // rows of the wide forward's query tiles
 
 struct LevelTiles {
     int Lv;                      // levels (0 non-causal or a single leaf)
     int len[kMaxLevels + 1];     // list length L_l of a depth-l segment (len[0] = N)
     int64_t off[kMaxLevels + 1]; // first entry of level l's lists within one (b,h); off[Lv] = all levels
     int first[kMaxLevels + 1];   // first tile of level l; first[Lv] = tiles of all levels
+    int wfirst[kMaxLevels + 1];  // the same for tiles of kWideTile rows
     int per_leaf;                // tiles per leaf
+    int wper_leaf;               // tiles of kWideTile rows per leaf
     int leaves;                  // 2^Lv
     int padded;                  // some segment carries zero tokens
     int leaf_tiles() const { return per_leaf * leaves; }
@@ -50,15 +53,17 @@ inline bool level_tiles(int N, int n0, LevelTiles& t)
     int L = N, lv = 0, pads = 0;                 // pads: the most zero tokens of any depth-lv segment
     t.len[0] = N;
     int64_t off = 0;
-    int acc = 0;
+    int acc = 0, wacc = 0;
     while (L > n0) {
         if (lv >= kMaxLevels) return false;
         const int m = (L + 1) / 2;
         if (pads > L - m) return false;          // the past half would reach a zero token
         t.off[lv] = off;
         t.first[lv] = acc;
+        t.wfirst[lv] = wacc;
         off += (int64_t)m << lv;
         acc += (1 << lv) * ((m + kRowTile - 1) / kRowTile);
+        wacc += (1 << lv) * ((m + kWideTile - 1) / kWideTile);
         pads += L & 1;                           // the all-future path collects every pad
         L = m;
         ++lv;
@@ -68,7 +73,9 @@ inline bool level_tiles(int N, int n0, LevelTiles& t)
     t.Lv = lv;
     t.off[lv] = off;
     t.first[lv] = acc;
+    t.wfirst[lv] = wacc;
     t.per_leaf = (L + kRowTile - 1) / kRowTile;
+    t.wper_leaf = (L + kWideTile - 1) / kWideTile;
     t.leaves = 1 << lv;
     return true;
 }
@@ -129,26 +136,30 @@ __device__ __forceinline__ unsigned leaf_levels(const LevelTiles& lt, int leaf, 
     return mask;
 }
 
-// tile -> (level, half length m_l, segment, first list position of the tile)
+// tile (of ROWS rows) -> (level, half length m_l, segment, first list position of the tile)
+template <int ROWS = kRowTile>
 __device__ __forceinline__ void level_tile(const LevelTiles& lt, int tile, int& level, int& half, int& seg, int& p0)
 {
+    const int* first = ROWS == kRowTile ? lt.first : lt.wfirst;
     level = 0;
-    while (level + 1 < lt.Lv && tile >= lt.first[level + 1]) ++level;
-    const int t = tile - lt.first[level];
+    while (level + 1 < lt.Lv && tile >= first[level + 1]) ++level;
+    const int t = tile - first[level];
     half = lt.len[level + 1];
-    const int tps = (half + kRowTile - 1) / kRowTile;
+    const int tps = (half + ROWS - 1) / ROWS;
     seg = t / tps;
-    p0 = (t - seg * tps) * kRowTile;
+    p0 = (t - seg * tps) * ROWS;
 }
 
 // tile -> (leaf, first token of its leaf, first token of the tile, end of
 // the leaf's real tokens); tiles past the real tokens have t0 >= lend.
+template <int ROWS = kRowTile>
 __device__ __forceinline__ void leaf_tile(const LevelTiles& lt, int tile, int& leaf, int& lbeg, int& t0, int& lend)
 {
-    leaf = tile / lt.per_leaf;
+    const int per = ROWS == kRowTile ? lt.per_leaf : lt.wper_leaf;
+    leaf = tile / per;
     int r;
     seg_range(lt, lt.Lv, leaf, lbeg, r);
-    t0 = lbeg + (tile - leaf * lt.per_leaf) * kRowTile;
+    t0 = lbeg + (tile - leaf * per) * ROWS;
     lend = lbeg + r;
 }
 

@@ -91,6 +91,25 @@ def test_ragged_causal_whole_blocks(w):
     _check(w)
 
 
+# the forward's 128-query tiles: levels of b >= 128 whose lists end anywhere in
+# a tile and whose blocks straddle tiles (b = 160, 200), neighbouring blocks,
+# zero tokens; leaves of 1024 and more that end in a tile's first, third and
+# last wave
+WIDE_CASES = [
+    (_w("c-bf16-d128-k160-1500", 1, 2, 1500, 128, 160, 64, "bf16", 0), 0),
+    (_w("c-bf16-d64-k200-1111-padded", 2, 1, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0),
+    (_w("c-bf16-d64-k128-1300-nbr1", 1, 1, 1300, 64, 128, 64, "bf16", 0), 1),
+    (_w("c-bf16-d128-leaf1025", 1, 1, 2049, 128, 128, 64, "bf16", 1100), 0),
+    (_w("c-bf16-d64-leaf1110", 1, 2, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0),
+    (_w("c-bf16-d128-leaf1152-k64", 1, 1, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0),
+]
+
+
+@pytest.mark.parametrize("w,nbr", WIDE_CASES, ids=[w.name for w, _ in WIDE_CASES])
+def test_ragged_causal_wide_tiles(w, nbr):
+    _check(w, neighbors=nbr)
+
+
 def test_ragged_causal_with_neighbours():
     _check(_w("c-bf16-d128-2000-leaf250-nbr1", 1, 1, 2000, 128, 64, 128, "bf16", 300, seed=81), neighbors=1)
 
