@@ -60,6 +60,7 @@ hipError_t launch_project(const Shape& s, const void* Q, const void* K, const fl
                           hipStream_t st);
 hipError_t launch_sort(const Shape& s, const uint8_t* keyq, const uint8_t* keyk, int32_t* perm_q,
                        int32_t* perm_k, hipStream_t st);
+int sort_steps(const Shape& s);             // 64-key steps of a wave in the longest list (about 0.8 us each)
 
 // RACE low-rank branch
 int race_padded_features(int r);            // r rounded up to 32, 64, 128 or 256

@@ -224,24 +224,25 @@ hipError_t launch_project(const Shape& s, const void* Q, const void* K, const fl
 //           token of that key; their entries are -1.
 // --------------------------------------------------------------------------
 
-constexpr int kSortThreads = 256;
-constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kKeyCache = 16384;       // keys of a list staged in LDS (longer lists read the rest from HBM)
 
-// One workgroup per list.  The list is cut into one contiguous quarter per
-// wave.  A histogram of every quarter gives each wave, for every bucket, the
-// output position of its first element of that bucket (all smaller buckets,
-// then the same bucket in earlier quarters); each wave then ranks its
-// quarter 64 keys at a time (lanes of equal key found by ballots over the
-// key bits) with no further synchronisation, so equal keys keep their index
-// order within the whole list.
-__global__ __launch_bounds__(kSortThreads) void sort_kernel(const uint8_t* __restrict__ keyq,
-                                                            const uint8_t* __restrict__ keyk,
-                                                            int32_t* __restrict__ perm_q,
-                                                            int32_t* __restrict__ perm_k, int H,
-                                                            int N, int causal, LevelTiles lt, int bits)
+// One workgroup of WAVES waves per list.  The list is cut into one contiguous
+// part per wave.  A histogram of every part gives each wave, for every bucket,
+// the output position of its first element of that bucket (all smaller
+// buckets, then the same bucket in earlier parts); each wave then ranks its
+// part 64 keys at a time (lanes of equal key found by ballots over the key
+// bits) with no further synchronisation, so equal keys keep their index order
+// within the whole list.  A 64-key step is a chain of about 0.8 us, so the
+// steps per wave are the list's time.
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void sort_kernel(const uint8_t* __restrict__ keyq,
+                                                             const uint8_t* __restrict__ keyk,
+                                                             int32_t* __restrict__ perm_q,
+                                                             int32_t* __restrict__ perm_k, int H,
+                                                             int N, int causal, LevelTiles lt, int bits)
 {
-    __shared__ int hist[kSortWaves][256];   // per quarter; then its running output positions
+    constexpr int kSortWaves = WAVES, kSortThreads = WAVES * kWave;
+    __shared__ int hist[kSortWaves][256];   // per part; then its running output positions
     __shared__ uint8_t kc[kKeyCache];
     const int h = blockIdx.y, b = blockIdx.z;
     const int task = blockIdx.x;
@@ -273,12 +274,12 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const uint8_t* __res
     int32_t* out = (is_k ? perm_k : perm_q) + out_off;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int quarter = (len + kSortWaves - 1) / kSortWaves;
-    const int qbeg = min(len, wave * quarter), qend = min(len, qbeg + quarter);
+    const int part = (len + kSortWaves - 1) / kSortWaves;
+    const int qbeg = min(len, wave * part), qend = min(len, qbeg + part);
 
     for (int i = threadIdx.x; i < kSortWaves * 256; i += kSortThreads) (&hist[0][0])[i] = 0;
     __syncthreads();
-    // the quarter's histogram; the first kKeyCache keys of the list are staged
+    // the part's histogram; the first kKeyCache keys of the list are staged
     // in LDS on the way, eight loads per lane in flight at a time
     for (int i0 = qbeg; i0 < qend; i0 += 8 * kWave) {
         uint8_t v[8];
@@ -297,8 +298,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const uint8_t* __res
         }
     }
     __syncthreads();
-    // first output position of bucket c in quarter w: all keys < c, then key c
-    // in quarters before w (one wave scans the buckets, 64 at a time)
+    // first output position of bucket c in part w: all keys < c, then key c
+    // in parts before w (one wave scans the buckets, 64 at a time)
     if (wave == 0) {
         int carry = 0;
         for (int c0 = 0; c0 < nb; c0 += kWave) {
@@ -326,8 +327,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const uint8_t* __res
         }
     }
     __syncthreads();
-    // rank the quarter, 64 keys per step; hist[wave][c] is the next output
-    // position of bucket c in this quarter
+    // rank the part, 64 keys per step; hist[wave][c] is the next output
+    // position of bucket c in this part
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     for (int i0 = qbeg; i0 < qend; i0 += kWave) {
         const int i = i0 + lane;
@@ -346,14 +347,31 @@ __global__ __launch_bounds__(kSortThreads) void sort_kernel(const uint8_t* __res
     }
 }
 
+namespace {
+int sort_waves(const Shape& s) { return s.causal || s.N < 1024 ? 4 : 16; }
+}  // namespace
+
+int sort_steps(const Shape& s)
+{
+    const int longest = s.causal ? (s.Lv > 0 ? s.lt.len[1] : 0) : s.N;
+    return (longest + sort_waves(s) * kWave - 1) / (sort_waves(s) * kWave);
+}
+
 hipError_t launch_sort(const Shape& s, const uint8_t* keyq, const uint8_t* keyk, int32_t* perm_q,
                        int32_t* perm_k, hipStream_t st)
 {
     const int tasks = s.causal ? (1 << (s.Lv + 1)) - 2 : 2;
     if (tasks <= 0) return hipSuccess;
     dim3 grid(tasks, s.H, s.B);
-    ELSAA_LAUNCH("sort", sort_kernel, grid, dim3(kSortThreads), 0, st, keyq, keyk, perm_q, perm_k,
-                       s.H, s.N, s.causal, s.lt, s.sort_bits);
+    // non-causal: two long lists per (b, h), so few workgroups: sixteen waves
+    // each (30720 tokens 121 -> 36 us, 4096: 13 -> 5); causal levels have
+    // 2^(l + 1) lists, most of them short, and fill the device with four
+#define ELSAA_SORT(W_)                                                                                       \
+    ELSAA_LAUNCH("sort", sort_kernel<W_>, grid, dim3(W_ * kWave), 0, st, keyq, keyk, perm_q, perm_k, s.H, s.N, \
+                 s.causal, s.lt, s.sort_bits)
+    if (sort_waves(s) == 4) ELSAA_SORT(4);
+    else ELSAA_SORT(16);
+#undef ELSAA_SORT
     return hipGetLastError();
 }
 

@@ -33,6 +33,12 @@ CASES = [
     _w("c-bf16-d64-2048-clustered", 1, 2, 2048, 64, 64, True, "bf16", recipe="clustered", centres=4),
     _w("nc-bf16-d128-5000-clustered-bits1", 1, 1, 5000, 128, 128, False, "bf16", recipe="clustered",
        sort_bits=1, centres=3),
+    # sixteen waves a list (non-causal from 1024 tokens): one step each, a last
+    # wave without keys, all buckets, and the last length of four waves
+    _w("nc-bf16-d64-1023", 1, 1, 1023, 64, 64, False, "bf16"),
+    _w("nc-bf16-d64-1024-bits8", 1, 2, 1024, 64, 64, False, "bf16", sort_bits=8),
+    _w("nc-f32-d64-1030", 1, 1, 1030, 64, 64, False, "f32", recipe="clustered", centres=2),
+    _w("nc-bf16-d64-16385-bits8", 1, 1, 16385, 64, 64, False, "bf16", sort_bits=8),
 ]
 
 
