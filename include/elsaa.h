@@ -36,12 +36,13 @@
  *
  * Library-owned HIP objects: on its first call on a device, elsaa_fwd
  * creates one non-blocking stream of default priority and two events on
- * that device and keeps them until the process ends.  Each elsaa_fwd call
- * records an event on the given stream, runs the sort of the selection on
- * that second stream while the given stream runs the low-rank branch, and
- * makes the given stream wait for the second stream before the sparse
- * kernels (also when a launch in between failed), so the call behaves as if
- * everything ran on the given stream.  Concurrent elsaa_fwd calls on one
+ * that device and keeps them until the process ends.  An elsaa_fwd call with
+ * long lists to sort (where the overlap is worth the events) records an event
+ * on the given stream, runs the sort of the selection on that second stream
+ * while the given stream runs the low-rank branch, and makes the given stream
+ * wait for the second stream before the sparse kernels (also when a launch in
+ * between failed), so the call behaves as if everything ran on the given
+ * stream; other calls use the given stream alone.  Concurrent elsaa_fwd calls on one
  * device share the second stream, so their sorts run one after another.
  *
  * Graph capture: elsaa_fwd and elsaa_bwd enqueue only kernels and event

@@ -229,12 +229,13 @@ hipError_t clear_error() { return hipGetLastError(); }
 const StreamOps kHipStreamOps = {record_event, hipStreamWaitEvent, hipStreamSynchronize, clear_error};
 
 // first(side) on the device's side stream beside second(main) (fork_join.hpp);
-// without a side stream both run on `main` in order.
+// without a side stream, or when a fork does not pay, both run on `main` in
+// order.
 template <class A, class B>
-hipError_t fork_join(hipStream_t main, A first, B second)
+hipError_t fork_join(bool pays, hipStream_t main, A first, B second)
 {
-    Side* sd = side_stream();
-    if (!sd) {
+    Side* sd = side_stream();        // created by the first call whatever its sizes, so a later call can be captured
+    if (!sd || !pays) {
         hipError_t e = first(main);
         return e != hipSuccess ? e : second(main);
     }
@@ -444,9 +445,15 @@ int elsaa_fwd(const elsaa_config* cfg, const void* Q, const void* K, const void*
     // the sort on the side stream beside the low-rank branch (its kernels and
     // the level kernel's cannot share a compute unit, so the levels run after
     // it rather than competing for the device), then the causal levels, then
-    // the leaf (or sorted blocks) with the fusion epilogue
+    // the leaf (or sorted blocks) with the fusion epilogue.  Recording and
+    // waiting for the two events costs the host about 30 us and the device
+    // some more, so short sorts stay on the caller's stream: forward of 512
+    // tokens float32 65 -> 28 us, 4096 x 16 heads 64 -> 48, 8192 x 8 heads
+    // 65 -> 54 in order; a longest list of 16 steps gains by the fork (16384
+    // x 8 heads 79 us against 83, causal 7919 x 16 heads 202 against 209),
+    // one of 8 steps is equal (causal 4096 x 8 heads, 80 us).
     e = fork_join(
-        stream, [&](hipStream_t st) { return launch_sort(s, kq, kk, pq, pk, st); },
+        sort_steps(s) >= 12, stream, [&](hipStream_t st) { return launch_sort(s, kq, kk, pq, pk, st); },
         [&](hipStream_t st) { return launch_race_fwd(s, uq, uk, V, at<float>(saved, SL.race_states), o_lr, d_lr, st); });
     if (e == hipSuccess)
         e = launch_sparse_fwd(s, Q, K, V, pq, pk, gates, lambda_rows, o_lr, d_lr, part_o, part_lse, O, lse, m, o_s,

@@ -1,6 +1,6 @@
 """The operator under HIP graph capture: elsaa_fwd and elsaa_bwd enqueue only
-kernels and event record / wait pairs (the forward's sort runs on the
-library's second stream between a fork and a join), so a caller can capture
+kernels and event record / wait pairs (a forward with long lists sorts on
+the library's second stream between a fork and a join), so a caller can capture
 a whole step and replay it.  Each replay is checked, bit for bit, against
 the eager call on the same inputs, with other eager work and host
 synchronisation between the replays."""
@@ -23,6 +23,9 @@ CASES = [
     (_w("c-bf16-d128-2048", 1, 2, 2048, 128, 128, 128, True, "bf16", 70), True),
     (_w("nc-bf16-d64-1000", 2, 1, 1000, 64, 64, 64, False, "bf16", 71), True),
     (W.TINY_FP32, False),
+    # lists long enough for the forward's second stream
+    (_w("c-bf16-d64-8192", 1, 2, 8192, 64, 64, 32, True, "bf16", 72), True),
+    (_w("nc-bf16-d64-16384", 1, 1, 16384, 64, 128, 32, False, "bf16", 73), True),
 ]
 
 
