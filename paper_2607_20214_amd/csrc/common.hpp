@@ -290,12 +290,15 @@ __device__ __forceinline__ float wave_sum16(float v)   // sum over lanes l, l^16
     return b.lo + b.hi;
 }
 
-__device__ __forceinline__ float row_sum16(float v)    // sum over the 16 lanes of a row group
+// Sum over the 16 lanes of a row group, in every lane: four rotations within
+// the group on the vector unit (DPP row_ror; each partial sum has the
+// rotation's period, so all lanes end with the same value).
+__device__ __forceinline__ float row_sum16(float v)
 {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x128, 0xf, 0xf, true));   // row_ror:8
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x124, 0xf, 0xf, true));
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x122, 0xf, 0xf, true));
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x121, 0xf, 0xf, true));
     return v;
 }
 

@@ -48,7 +48,16 @@ struct TrArgs {
     int H, N, nchunk, chunk_rows;
 };
 
-__device__ __forceinline__ float sigm(float x) { return 1.f / (1.f + __expf(-x)); }
+// sigmoid(x) from e = exp(-|x|) in (0, 1] and one reciprocal refined by a
+// Newton step (within an ulp; a full division takes ten more instructions,
+// and the two layers evaluate this 80 to 160 times per row tile and lane)
+__device__ __forceinline__ float sigm(float x)
+{
+    const float e = __expf(-fabsf(x)), d = 1.f + e;
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
+    return x >= 0.f ? r : e * r;
+}
 
 template <class T, int D, int G, bool LAM>
 struct TokenRules {
@@ -136,9 +145,9 @@ struct TokenRules {
     // ---- first layer ---------------------------------------------------
     // acc[s][cb] register i of lane group g: z1 (without b1) of tile row
     // wr0 + 8g + 4s + i, column 16 cb + lane % 16.
-    __device__ static void first_layer(const Smem& sm, int wr0, f32x4 (&acc)[2][NB])
+    __device__ static void first_layer(const Smem& sm, int wr0, f32x4 (&acc)[2][NB], int tx)
     {
-        const int lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
+        const int lane = tx & 63, g = lane >> 4, rho = lane & 15;
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -165,9 +174,9 @@ struct TokenRules {
     // Second-layer logits of the 8 rows of the lane group (all 16 lanes of
     // the group get them): z2[o][s][i] for row 8g + 4s + i.
     __device__ static void second_layer(const Smem& sm, const f32x4 (&acc)[2][NB], float b20, float b21,
-                                        float (&z2)[2][2][4])
+                                        float (&z2)[2][2][4], int tx)
     {
-        const int rho = threadIdx.x & 15;
+        const int rho = tx & 15;
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -221,7 +230,7 @@ struct TokenRules {
         int bh, h, rbeg, rend;
         chunk(a, bh, h, rbeg, rend);
         const int N = a.N;
-        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
+        const int w = threadIdx.x >> 6;
         const int wr0 = 32 * w;
         const S* X = (const S*)a.Q + (size_t)bh * N * D;
         float b20 = 0.f, b21 = 0.f, lb = 0.f, lc = 0.f;
@@ -235,13 +244,19 @@ struct TokenRules {
             store_rows(sm.qt, rg);
             if (row0 + RT < rend) load_rows(X, row0 + RT, N, rg);
             __syncthreads();
+            // this tile's own copy of the thread index: lane-dependent LDS
+            // addresses are formed where used, not held in registers across
+            // the tiles (holding them spilled)
+            int tx = threadIdx.x;
+            asm volatile("" : "+v"(tx));
+            const int lane = tx & 63, g = lane >> 4, rho = lane & 15;
             f32x4 acc[2][NB];
-            first_layer(sm, wr0, acc);
+            first_layer(sm, wr0, acc, tx);
             const int row = row0 + wr0 + 8 * g + rho;     // row written by lanes rho < 8
             const bool wr = rho < 8 && row < rend;
             if constexpr (G > 0) {
                 float z2[2][2][4];
-                second_layer(sm, acc, b20, b21, z2);
+                second_layer(sm, acc, b20, b21, z2, tx);
                 const float v0 = pick(z2[0], rho), v1 = pick(z2[1], rho);
                 if (wr) *(float2*)&a.gates[((size_t)bh * N + row) * 2] = make_float2(sigm(v0), sigm(v1));
             }
@@ -265,7 +280,7 @@ struct TokenRules {
         int bh, h, rbeg, rend;
         chunk(a, bh, h, rbeg, rend);
         const int N = a.N;
-        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
+        const int w = threadIdx.x >> 6;
         const int wr0 = 32 * w;
         const S* X = (const S*)a.Q + (size_t)bh * N * D;
         float b20 = 0.f, b21 = 0.f, lb = 0.f, lc = 0.f;
@@ -290,6 +305,12 @@ struct TokenRules {
             store_rows(sm.qt, rg);
             if (row0 + RT < rend) load_rows(X, row0 + RT, N, rg);
             __syncthreads();
+            // this tile's own copy of the thread index: lane-dependent LDS
+            // addresses are formed where used, not held in registers across
+            // the tiles (holding them spilled)
+            int tx = threadIdx.x;
+            asm volatile("" : "+v"(tx));
+            const int lane = tx & 63, g = lane >> 4, rho = lane & 15;
             // the row gradients and the dQ rows this wave adds to, loaded
             // before the products so that their latency is hidden
             const size_t rb = (size_t)bh * N + row0 + wr0 + 8 * g;   // row of (s, i): rb + 4s + i
@@ -306,13 +327,13 @@ struct TokenRules {
                 }
             DqRegs dqv;
             if constexpr (G > 0 && DQ_EARLY)
-                if (a.dQ) dq_load((const S*)a.dQ + (size_t)bh * N * D, row0, wr0, rend, dqv);
+                if (a.dQ) dq_load((const S*)a.dQ + (size_t)bh * N * D, row0, wr0, rend, dqv, tx);
             {
                 f32x4 acc[2][NB];
-                first_layer(sm, wr0, acc);
+                first_layer(sm, wr0, acc, tx);
                 if constexpr (G > 0) {
                     float z2[2][2][4], dz0[2][4], dz1[2][4];
-                    second_layer(sm, acc, b20, b21, z2);
+                    second_layer(sm, acc, b20, b21, z2, tx);
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -371,7 +392,7 @@ struct TokenRules {
             for (int kr = 0; kr < RT / 32; ++kr) {
                 F bq[CBW];
 #pragma unroll
-                for (int j = 0; j < CBW; ++j) bq[j] = TQ::col8(sm.qt, 32 * kr, 16 * (w * CBW + j));
+                for (int j = 0; j < CBW; ++j) bq[j] = TQ::col8(sm.qt, 32 * kr, 16 * (w * CBW + j), tx);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     const F az = TZ::row8(sb.zt, 16 * nb + rho, 32 * kr + 8 * g);
@@ -386,10 +407,10 @@ struct TokenRules {
                     S* dQ = (S*)a.dQ + (size_t)bh * N * D;
                     if constexpr (DQ_EARLY) {
 #pragma unroll
-                        for (int cbk = 0; cbk < D / 16; ++cbk) dq_block(sb, dQ, cbk, row0, wr0, rend, dqv);
+                        for (int cbk = 0; cbk < D / 16; ++cbk) dq_block(sb, dQ, cbk, row0, wr0, rend, dqv, tx);
                     } else {
 #pragma unroll 1
-                        for (int cbk = 0; cbk < D / 16; ++cbk) dq_block(sb, dQ, cbk, row0, wr0, rend, dqv);
+                        for (int cbk = 0; cbk < D / 16; ++cbk) dq_block(sb, dQ, cbk, row0, wr0, rend, dqv, tx);
                     }
                 }
             }
@@ -397,6 +418,7 @@ struct TokenRules {
         }
 
         // ---- per-workgroup partial sums --------------------------------
+        const int lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
         constexpr TrLayout lay{G, D, LAM ? 1 : 0};
         float* P = a.part + (size_t)blockIdx.x * lay.stride();
 #pragma unroll
@@ -469,9 +491,10 @@ struct TokenRules {
     };
     // dq += W1^T dz1 for columns 16 cbk .. +15 of the wave's own rows (q^T
     // layout: the lane holds 4 consecutive columns of one row)
-    __device__ static void dq_block(const SmemB& sb, S* dQ, int cbk, int row0, int wr0, int rend, const DqRegs& dqv)
+    __device__ static void dq_block(const SmemB& sb, S* dQ, int cbk, int row0, int wr0, int rend, const DqRegs& dqv,
+                                    int tx)
     {
-        const int lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
+        const int lane = tx & 63, g = lane >> 4, rho = lane & 15;
         DqPiece old[2];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -482,11 +505,11 @@ struct TokenRules {
         f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int kn = 0; kn < G / 32; ++kn) {
-            const F ah = TQ::col8(sb.m.whi, 32 * kn, 16 * cbk);
-            const F al = SPLIT ? TQ::col8(sb.m.wlo, 32 * kn, 16 * cbk) : ah;
+            const F ah = TQ::col8(sb.m.whi, 32 * kn, 16 * cbk, tx);
+            const F al = SPLIT ? TQ::col8(sb.m.wlo, 32 * kn, 16 * cbk, tx) : ah;
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-                const F bz = TZ::col8(sb.zt, 32 * kn, wr0 + 16 * r);
+                const F bz = TZ::col8(sb.zt, 32 * kn, wr0 + 16 * r, tx);
                 acc[r] = T::mma(ah, bz, acc[r]);
                 if constexpr (SPLIT) acc[r] = T::mma(al, bz, acc[r]);
             }
@@ -498,9 +521,9 @@ struct TokenRules {
         }
     }
 
-    __device__ static void dq_load(const S* dQ, int row0, int wr0, int rend, DqRegs& q)
+    __device__ static void dq_load(const S* dQ, int row0, int wr0, int rend, DqRegs& q, int tx)
     {
-        const int lane = threadIdx.x & 63, g = lane >> 4, rho = lane & 15;
+        const int lane = tx & 63, g = lane >> 4, rho = lane & 15;
 #pragma unroll
         for (int cbk = 0; cbk < D / 16; ++cbk)
 #pragma unroll
@@ -531,7 +554,7 @@ __global__ __launch_bounds__(T::bytes == 2 ? 256 : 128, 1) void token_rules_fwd_
 }
 
 template <class T, int D, int G, bool LAM>
-__global__ __launch_bounds__(T::bytes == 2 ? 256 : 128, 1) void token_rules_bwd_kernel(TrArgs a)
+__global__ __launch_bounds__(T::bytes == 2 ? 256 : 128, T::bytes == 2 && D == 64 && G <= 64 ? 2 : 1) void token_rules_bwd_kernel(TrArgs a)
 {
     __shared__ __attribute__((aligned(16))) typename TokenRules<T, D, G, LAM>::SmemB sm;
     TokenRules<T, D, G, LAM>::bwd(a, sm);
@@ -553,7 +576,14 @@ __global__ __launch_bounds__(256) void token_rules_reduce_kernel(TrRedArgs r)
     float s = 0.f;
     for (int b = 0; b < r.B; ++b) {
         const float* p = r.part + ((size_t)(b * r.H + h) * r.nchunk) * L.stride() + e;
-        for (int c = 0; c < r.nchunk; ++c) s += p[(size_t)c * L.stride()];
+        for (int c0 = 0; c0 < r.nchunk; c0 += 8) {            // eight loads in flight, added in order
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = c0 + j < r.nchunk ? p[(size_t)(c0 + j) * L.stride()] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (c0 + j < r.nchunk) s += v[j];
+        }
     }
     const int G = L.G, D = L.D;
     if (e < L.lw()) { if (r.dW1) r.dW1[(size_t)h * G * D + e] = s; }
@@ -578,9 +608,13 @@ void plan_chunks(const Shape& s, int rt, int target, int& nchunk, int& chunk_row
     nchunk = (int)((s.N + chunk_rows - 1) / chunk_rows);
 }
 
-constexpr int kFwdTarget = 512, kBwdTarget = 256;
+constexpr int kFwdTarget = 512;
 
 int rt_of(const Shape& s) { return s.bf16 ? 128 : 64; }
+// the backward's workgroups in flight: two to a compute unit in bf16 storage
+// at d_h 64 with at most 64 hidden units (registers and LDS; 262144 rows 61 ->
+// 50 us), else one
+int bwd_target(const Shape& s, int G) { return s.bf16 && s.D == 64 && G <= 64 ? 512 : 256; }
 
 template <class T, int D, int G, bool LAM>
 hipError_t launch_fwd_t(const Shape& s, TrArgs a, hipStream_t st)
@@ -597,7 +631,7 @@ template <class T, int D, int G, bool LAM>
 hipError_t launch_bwd_t(const Shape& s, TrArgs a, const TrGrads& gr, hipStream_t st)
 {
     using C = TokenRules<T, D, G, LAM>;
-    plan_chunks(s, C::RT, kBwdTarget, a.nchunk, a.chunk_rows);
+    plan_chunks(s, C::RT, bwd_target(s, G), a.nchunk, a.chunk_rows);
     a.H = s.H; a.N = s.N;
     ELSAA_LAUNCH("token_rules_bwd", (token_rules_bwd_kernel<T, D, G, LAM>),
                  dim3(s.B * s.H * a.nchunk), dim3(C::NT), 0, st, a);
@@ -643,7 +677,7 @@ hipError_t dispatch_all(const Shape& s, int G, bool lam, bool bwd, const TrArgs&
 size_t token_rules_workspace_bytes(const Shape& s, int G, bool lam)
 {
     int nchunk, rows;
-    plan_chunks(s, rt_of(s), kBwdTarget, nchunk, rows);
+    plan_chunks(s, rt_of(s), bwd_target(s, G), nchunk, rows);
     const TrLayout L{G, s.D, lam ? 1 : 0};
     return (size_t)s.B * s.H * nchunk * L.stride() * sizeof(float);
 }
