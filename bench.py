@@ -67,7 +67,7 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
     u["lowrank_fwd"] = (bh * N * lr_tok_bytes, bh * N * lr_tok_flops,
                         ["race_state_fwd", "race_scan_fwd", "race_out"])
     u["lowrank_bwd"] = (2 * bh * N * lr_tok_bytes, int(2.25 * bh * N * lr_tok_flops),
-                        ["race_state_bwd", "race_scan_bwd", "race_bwd", "race_dv"])
+                        ["race_state_bwd", "race_rows_bwd", "race_scan_bwd", "race_bwd", "race_dv"])
     u["bwd_rows"] = (bh * N * (D * s + 8 * D + 12), bh * N * 4 * D, ["bwd_rows"])
     base_fwd = bh * (3 * N * D * s + 4 * N * D + 12 * N) + bh * N * (D * s + 4 * D + 8)
     base_bwd = bh * (4 * N * D * s + 12 * N * D + 8 * N)
@@ -151,7 +151,8 @@ KERNEL_SOURCES = {
     "race_out": ["race_fwd.hip", "race_common.hpp", "common.hpp"],
     "race_bwd": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
     "race_dv": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
-    "bwd_rows": ["bwd_rows.hip", "common.hpp"],
+    "race_rows_bwd": ["race_fwd.hip", "race_common.hpp", "bwd_rows.hpp", "common.hpp"],
+    "bwd_rows": ["bwd_rows.hip", "bwd_rows.hpp", "common.hpp"],
     "gemm": ["gemm.hip", "common.hpp"], "gemm_reduce": ["gemm.hip"],
     "token_rules_fwd": ["token_rules.hip", "tile.hpp", "common.hpp"],
     "token_rules_bwd": ["token_rules.hip", "tile.hpp", "common.hpp"],

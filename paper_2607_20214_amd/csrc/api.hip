@@ -7,6 +7,7 @@
 #include <string>
 
 #include "elsaa.h"
+#include "bwd_rows.hpp"
 #include "causal.hpp"
 #include "fork_join.hpp"
 #include "internal.hpp"
@@ -501,13 +502,19 @@ int elsaa_bwd(const elsaa_config* cfg, const void* Q, const void* K, const void*
     void* wt_lo = at<char>(workspace, W.wt_lo);
     void* dv_lr = at<uint8_t>(workspace, W.dv_lr);
     hipError_t e;
-    if ((e = launch_bwd_rows(s, dO, o_s, o_lr, m, lse, d_lr, gates, lambda_rows, rs, dgates, dlambda, stream)) !=
-        hipSuccess)
-        return hip_fail(e, "backward row scalars");
+    RowArgs rows;
+    rows.Os = o_s; rows.Olr = o_lr; rows.m = m; rows.lse = lse; rows.dlr = d_lr;
+    rows.gates = gates; rows.lam_rows = lambda_rows;
+    rows.rs = rs; rows.dg = dgates; rows.dlam = dlambda;
+    rows.BHN = (size_t)s.B * s.H * s.N; rows.lambda = s.lambda; rows.eps = s.eps; rows.m_one = s.m_one;
+    float* states_b = at<float>(workspace, W.states_b);
+    if ((e = launch_race_bwd_states(s, uq, dO, rows, states_b, stream)) != hipSuccess)
+        return hip_fail(e, "backward row scalars and states");
     void* part_dq = at<char>(workspace, W.part_dq);
     void* part_dk = at<char>(workspace, W.part_dk);
     void* part_dv = at<char>(workspace, W.part_dv);
-    // the causal levels' backward, then the low-rank backward, then the leaf
+    // the row scalars and low-rank states (above), the causal levels'
+    // backward, then the low-rank passes, then the leaf
     // (or sorted blocks), which add the level partials and low-rank
     // gradients (one kernel at a time: each kernel's time is its own)
     auto levels = [&](hipStream_t st) {
@@ -516,7 +523,7 @@ int elsaa_bwd(const elsaa_config* cfg, const void* Q, const void* K, const void*
     };
     auto race = [&](hipStream_t st) {
         return launch_race_bwd(s, uq, uk, V, dO, W_race, rs, at<float>(sv, SL.race_states),
-                               at<float>(workspace, W.states_b), wt_hi, wt_lo, du_q, du_k, dv_lr, st);
+                               states_b, wt_hi, wt_lo, du_q, du_k, dv_lr, st);
     };
     if ((e = levels(stream)) != hipSuccess) return hip_fail(e, "sparse levels backward");
     if ((e = race(stream)) != hipSuccess) return hip_fail(e, "race backward");

@@ -68,20 +68,23 @@ int race_proj_stride(const Shape& s);        // floats per row of U (padded 4 * 
 size_t race_state_floats(const Shape& s);    // floats of one set of segment states
 bool race_fwd_fits(const Shape& s);          // kernels' LDS fits for this dtype / d / r
 bool race_bwd_fits(const Shape& s);
-// segment states S = mul * sum phi(u) (scale * val)', A = mul * sum aw phi(u);
-// scan_mode 0: total in every segment, 1: exclusive prefix, 2: exclusive suffix
-hipError_t launch_race_states(const Shape& s, const float* U, const void* Val, const float* vscale,
-                              const float* aw, float mul, float* states, int scan_mode, hipStream_t st);
+struct RowArgs;                              // bwd_rows.hpp
 hipError_t launch_race_fwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
                            float* states, void* O_lr, float* d_lr, hipStream_t st);
 size_t race_wt_bytes(const Shape& s);       // one of the W' hi / lo buffers
 int race_wk(const Shape& s);                // columns of W' and of a du row (4 L padded to 32)
+// The backward's row scalars (rows.rs and the gate and lambda gradients) and
+// the suffix states of phi(q) dNum' / L and phi(q) dDen / L (non-causal: the
+// totals) of the segments
+hipError_t launch_race_bwd_states(const Shape& s, const float* Uq, const void* dO, const RowArgs& rows,
+                                  float* states_b, hipStream_t st);
 // states_f: the forward's segment prefix states (elsaa_fwd keeps them in saved);
+// states_b: launch_race_bwd_states;
 // du_q, du_k: gradients of the RACE projections of the Q / K rows, storage
 // dtype [BH][N][race_wk]; dv_lr: storage dtype [BH][N][D]; wt_hi / wt_lo receive W'
 hipError_t launch_race_bwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
                            const void* dO, const float* W_race, const float* rs,
-                           const float* states_f, float* states_b, void* wt_hi, void* wt_lo,
+                           const float* states_f, const float* states_b, void* wt_hi, void* wt_lo,
                            void* du_q, void* du_k, void* dv_lr, hipStream_t st);
 
 // which kernels of a sparse-branch pass to launch: the causal levels (they
@@ -105,11 +108,8 @@ hipError_t launch_sparse_fwd(const Shape& s, const void* Q, const void* K, const
                              void* O, float* lse, float* m, float* O_s, hipStream_t st,
                              int parts = kSparseAll);
 
-// backward: per-row scalars rs[5][BHN] (log2(d_s+eps), Delta, sc_s, sc_lr, dDen)
-hipError_t launch_bwd_rows(const Shape& s, const void* dO, const float* Os, const void* Olr,
-                           const float* m, const float* lse, const float* dlr, const float* gates,
-                           const float* lambda_rows, float* rs, float* dgates, float* dlambda,
-                           hipStream_t st);
+// backward: the per-row scalars as a pass of their own
+hipError_t launch_bwd_rows(const Shape& s, const void* dO, const RowArgs& a, hipStream_t st);
 // sparse backward; adds the low-rank parts (du W' for dQ and dK, the dV rows)
 // and writes dQ, dK, dV; the causal level partials part_dq / part_dk / part_dv
 // ([BH][Lv][N/2][D]) are kept in the storage dtype

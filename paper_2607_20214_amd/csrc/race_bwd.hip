@@ -703,15 +703,10 @@ int race_wk(const Shape& s)
 
 hipError_t launch_race_bwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
                            const void* dO, const float* W_race, const float* rs,
-                           const float* states_f, float* states_b, void* wt_hi, void* wt_lo,
+                           const float* states_f, const float* states_b, void* wt_hi, void* wt_lo,
                            void* du_q, void* du_k, void* dv_lr, hipStream_t st)
 {
     const size_t BHN = (size_t)s.B * s.H * s.N;
-    // backward suffix states of phi(q) dNum' / L and phi(q) dDen / L (the
-    // forward prefix states of phi(k) V' and phi(k) come from the forward)
-    hipError_t e = launch_race_states(s, Uq, dO, rs + 3 * BHN, rs + 4 * BHN, 1.f / (float)s.L, states_b,
-                                      s.causal ? 2 : 0, st);
-    if (e != hipSuccess) return e;
     LbArgs a;
     a.Uq = Uq; a.Uk = Uk; a.V = V; a.dO = dO; a.rs = rs;
     a.W = W_race; a.wt_hi = wt_hi; a.wt_lo = wt_lo; a.items = s.B * s.H * s.nseg;

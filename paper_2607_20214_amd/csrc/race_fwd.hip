@@ -18,6 +18,9 @@
 // Each of the 4 waves owns d/4 columns of S, held as float32 matrix-core
 // accumulators for the whole segment; the intra-chunk kernel matrix and every
 // contraction run on MFMA (bf16 or float32 operands, float32 accumulation).
+#include <type_traits>
+
+#include "bwd_rows.hpp"
 #include "internal.hpp"
 #include "race_common.hpp"
 
@@ -54,12 +57,96 @@ struct StateArgs {
     float* states;        // [BH][nseg][RP*D + RP]
     int H, N, L, seg_len, nseg;
     float two_beta, mul;
+    RowArgs rows;         // kStateRows
 };
 
-// BWD: the values are scaled per row (vscale) and A is weighted (aw).
-template <class T, int D, int RP, bool BWD>
-__global__ __launch_bounds__(kThreads) void race_state_kernel(StateArgs a)
+// What a state pass sums: the forward's key rows, the backward's query rows
+// with given scalars (vscale, aw), or the same with the rows' scalars formed on
+// the way from dO (Val), O_s and O_lr and written out.
+enum StateKind { kStateFwd = 0, kStateBwd = 1, kStateRows = 2 };
+
+// A chunk's rows of dO, O_s and O_lr and the row inputs of the scalars: loads
+// one chunk ahead (as StageRows), then the two dot products per row (CH lanes
+// cover a row), the row's scalars, and sc_lr dO into the value tile.
+template <class T, int D>
+struct StageDots {
+    using S = typename T::store_t;
+    static constexpr int PER = 16 / T::bytes, CH = D / PER, PT = kC * CH / kThreads;
+    static_assert(CH == 8 || CH == 16 || CH == 32, "lanes per row");
+    uint4 u[PT], ol[PT];
+    f32x4 os[PT][PER / 4];
+    RowIn in[PT];
+    __device__ __forceinline__ void load(const S* dO, const RowArgs& r, size_t bh, int t0, int N)
+    {
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int it = threadIdx.x + j * kThreads;
+            const size_t row = bh * N + min(t0 + it / CH, N - 1);
+            const size_t at = row * D + (it % CH) * PER;
+            u[j] = ldg16(dO + at);
+            ol[j] = ldg16((const S*)r.Olr + at);
+#pragma unroll
+            for (int e = 0; e < PER / 4; ++e) os[j][e] = *(const f32x4*)(r.Os + at + 4 * e);
+            in[j].load(r, row);
+        }
+    }
+    __device__ static __forceinline__ float dpp(float v, const int ctrl_sel)
+    {
+        const uint32_t x = __float_as_uint(v);
+        const uint32_t y = ctrl_sel == 0   ? __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true)     // lane ^ 1
+                           : ctrl_sel == 1 ? __builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, true)     // lane ^ 2
+                           : ctrl_sel == 2 ? __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true)    // the row half mirrored
+                                           : __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, true);   // the row mirrored
+        return v + __uint_as_float(y);
+    }
+    // sum over the CH consecutive lanes of a row, in each of them
+    __device__ static __forceinline__ float lanes_sum(float v)
+    {
+        v = dpp(dpp(dpp(v, 0), 1), 2);
+        if constexpr (CH >= 16) v = dpp(v, 3);
+        if constexpr (CH == 32) {
+            const LanePair p = xpair16(v);
+            v = p.lo + p.hi;
+        }
+        return v;
+    }
+    __device__ __forceinline__ void store(const RowArgs& r, size_t bh, int t0, int N, S* t, Parts<T, kC>& aw) const
+    {
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int it = threadIdx.x + j * kThreads, rl = it / CH, e0 = (it % CH) * PER;
+            const bool live = t0 + rl < N;
+            const S* ue = (const S*)&u[j];
+            const S* le = (const S*)&ol[j];
+            float x[PER], uos = 0.f, uol = 0.f;
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                x[e] = T::load(ue[e]);
+                uos += x[e] * os[j][e / 4][e % 4];
+                uol += x[e] * T::load(le[e]);
+            }
+            uos = lanes_sum(uos);
+            uol = lanes_sum(uol);
+            const float f = live ? in[j].gl * (1.f / (in[j].den + r.eps)) : 0.f;
+#pragma unroll
+            for (int e = 0; e < PER; ++e) x[e] *= f;
+            S* dst = t + RowTile<T, D>::row(rl) + e0;
+            if constexpr (T::bytes == 2) *(typename T::frag_t*)dst = T::pack(x);
+            else *(f32x4*)dst = f32x4{x[0], x[1], x[2], x[3]};
+            if (e0 == 0) {
+                float dden = 0.f;
+                if (live) dden = row_scalars(r, bh * N + t0 + rl, in[j], uos, uol);
+                aw.put(rl, dden);
+            }
+        }
+    }
+};
+
+template <class T, int D, int RP, int KIND>
+__global__ __launch_bounds__(kThreads, KIND == kStateRows && T::bytes == 2 ? 2 : 1) void race_state_kernel(StateArgs a)
 {
+    constexpr bool BWD = KIND != kStateFwd, ROWS = KIND == kStateRows;   // A is weighted; scalars formed here
+    static_assert(!ROWS || table_split<RP>() == 1, "one workgroup per row");
     using St = typename T::store_t;
     using F = typename T::frag_t;
     constexpr int DW = D / 64;
@@ -73,8 +160,8 @@ __global__ __launch_bounds__(kThreads) void race_state_kernel(StateArgs a)
     const size_t bh = (size_t)b * a.H + h;
     const float* U = a.U + bh * a.N * (RP / 4) + F0 / 4;
     const St* Vl = (const St*)a.Val + bh * a.N * D;
-    const float* vs = BWD ? a.vscale + bh * a.N : nullptr;
-    const float* aw = BWD ? a.aw + bh * a.N : nullptr;
+    const float* vs = KIND == kStateBwd ? a.vscale + bh * a.N : nullptr;
+    const float* aw = KIND == kStateBwd ? a.aw + bh * a.N : nullptr;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int g = lane >> 4, col = lane & 15;
 
@@ -94,18 +181,20 @@ __global__ __launch_bounds__(kThreads) void race_state_kernel(StateArgs a)
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     // projections, value rows and A weights of the chunk, loaded one chunk ahead
     URegs<RPW> ur;
-    StageRows<T, D, BWD> vr;
+    typename std::conditional<ROWS, StageDots<T, D>, StageRows<T, D, KIND == kStateBwd>>::type vr;
     float awv = 0.f;
     auto load_chunk = [&](int c0) {
         ur.load(U, c0, a.N, RP / 4);
-        vr.load(Vl, c0, a.N, vs);
-        if constexpr (BWD) awv = aw[min(c0 + (int)threadIdx.x, a.N - 1)];   // masked to the chunk's rows where stored
+        if constexpr (ROWS) vr.load((const St*)a.Val, a.rows, bh, c0, a.N);
+        else vr.load(Vl, c0, a.N, vs);
+        if constexpr (KIND == kStateBwd) awv = aw[min(c0 + (int)threadIdx.x, a.N - 1)];   // masked to the chunk's rows where stored
     };
     load_chunk(t_beg);
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
-        vr.store(sm.v);
-        if (BWD && threadIdx.x < kC) sm.aw.put(threadIdx.x, t0 + (int)threadIdx.x < a.N ? awv : 0.f);
+        if constexpr (ROWS) vr.store(a.rows, bh, t0, a.N, sm.v, sm.aw);
+        else vr.store(sm.v);
+        if (KIND == kStateBwd && threadIdx.x < kC) sm.aw.put(threadIdx.x, t0 + (int)threadIdx.x < a.N ? awv : 0.f);
         features_from<T, RPW>(ur, t0, a.N, L, a.two_beta, sm.ph);
         __syncthreads();
         load_chunk(t0 + kC < t_end ? t0 + kC : t0);   // the last chunk reloads its own (unconditional loads)
@@ -396,20 +485,38 @@ constexpr bool fits()
     return sizeof(StateSmem<T, D, RP / table_split<RP>()>) <= kMaxLds && sizeof(OutSmem<T, D, RP>) <= kMaxLds;
 }
 
+// The row scalars in the state pass: one launch and one reading of dO less,
+// which short calls gain by (65536 rows, d_h 64: 13 + 10 -> 14 us a call,
+// encoder step 123 -> 118; 25088 rows float32: step 140 -> 137).  Long ones
+// do not: the pass's registers leave two workgroups a compute unit, too few
+// to stream O_s at the row pass's rate (262144 rows, d_h 128, 128 features: 94
+// us against 54 + 34; 512000 rows, d_h 128, 64 features: 149 against 105 +
+// 49).  With the tables split over two workgroups every row would be read
+// twice.
+template <int RP>
+bool fused_rows(const Shape& s)
+{
+    return table_split<RP>() == 1 && (int64_t)s.B * s.H * s.N <= 131072;
+}
+
 template <class T, int D, int RP>
-hipError_t launch_states_t(const Shape& s, const StateArgs& a, int scan_mode, hipStream_t st)
+hipError_t launch_states_t(const Shape& s, const StateArgs& a, bool bwd, hipStream_t st)
 {
     if constexpr (!fits<T, D, RP>()) {
         return hipErrorInvalidConfiguration;
     } else {
         dim3 grid(s.nseg * table_split<RP>(), s.H, s.B);
-        // the forward sums key rows, the backward (vscale set) query rows
-        const bool bwd = a.vscale != nullptr;
-        if (bwd) ELSAA_LAUNCH("race_state_bwd", (race_state_kernel<T, D, RP, true>), grid, dim3(kThreads), 0, st, a);
-        else ELSAA_LAUNCH("race_state_fwd", (race_state_kernel<T, D, RP, false>), grid, dim3(kThreads), 0, st, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const int per = RP * D + RP;
+        hipError_t e;
+        if (!bwd) ELSAA_LAUNCH("race_state_fwd", (race_state_kernel<T, D, RP, kStateFwd>), grid, dim3(kThreads), 0, st, a);
+        else if (fused_rows<RP>(s)) {
+            if constexpr (table_split<RP>() == 1)
+                ELSAA_LAUNCH("race_rows_bwd", (race_state_kernel<T, D, RP, kStateRows>), grid, dim3(kThreads), 0, st, a);
+        } else {
+            if ((e = launch_bwd_rows(s, a.Val, a.rows, st)) != hipSuccess) return e;
+            ELSAA_LAUNCH("race_state_bwd", (race_state_kernel<T, D, RP, kStateBwd>), grid, dim3(kThreads), 0, st, a);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const int per = RP * D + RP, scan_mode = !s.causal ? 0 : bwd ? 2 : 1;
         ELSAA_LAUNCH(bwd ? "race_scan_bwd" : "race_scan_fwd", race_scan_kernel, dim3((per + 255) / 256, s.B * s.H), dim3(256), 0, st,
                            a.states, s.nseg, per, scan_mode);
         return hipGetLastError();
@@ -450,9 +557,9 @@ hipError_t dispatch(const Shape& s, A&&... args)
 
 template <class T, int D, int RP>
 struct StatesFn {
-    static hipError_t run(const Shape& s, const StateArgs& a, int mode, hipStream_t st)
+    static hipError_t run(const Shape& s, const StateArgs& a, bool bwd, hipStream_t st)
     {
-        return launch_states_t<T, D, RP>(s, a, mode, st);
+        return launch_states_t<T, D, RP>(s, a, bwd, st);
     }
 };
 
@@ -481,20 +588,25 @@ bool race_fwd_fits(const Shape& s) { return dispatch<FitsFn>(s) == hipSuccess; }
 
 int race_proj_stride(const Shape& s) { return race_padded_features(s.r) / 4; }
 
-hipError_t launch_race_states(const Shape& s, const float* U, const void* Val, const float* vscale,
-                              const float* aw, float mul, float* states, int scan_mode, hipStream_t st)
+hipError_t launch_race_bwd_states(const Shape& s, const float* Uq, const void* dO, const RowArgs& rows,
+                                  float* states_b, hipStream_t st)
 {
     StateArgs a;
-    a.U = U; a.Val = Val; a.vscale = vscale; a.aw = aw; a.states = states;
+    a.U = Uq; a.Val = dO; a.vscale = rows.rs + 3 * rows.BHN; a.aw = rows.rs + 4 * rows.BHN; a.states = states_b;
     a.H = s.H; a.N = s.N; a.L = s.L; a.seg_len = s.seg_len; a.nseg = s.nseg;
-    a.two_beta = 2.f * s.beta; a.mul = mul;
-    return dispatch<StatesFn>(s, a, scan_mode, st);
+    a.two_beta = 2.f * s.beta; a.mul = 1.f / (float)s.L;
+    a.rows = rows;
+    return dispatch<StatesFn>(s, a, true, st);
 }
 
 hipError_t launch_race_fwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
                            float* states, void* O_lr, float* d_lr, hipStream_t st)
 {
-    hipError_t e = launch_race_states(s, Uk, V, nullptr, nullptr, 1.f, states, s.causal ? 1 : 0, st);
+    StateArgs sa = {};
+    sa.U = Uk; sa.Val = V; sa.states = states;
+    sa.H = s.H; sa.N = s.N; sa.L = s.L; sa.seg_len = s.seg_len; sa.nseg = s.nseg;
+    sa.two_beta = 2.f * s.beta; sa.mul = 1.f;
+    hipError_t e = dispatch<StatesFn>(s, sa, false, st);
     if (e != hipSuccess) return e;
     OutArgs a;
     a.Uq = Uq; a.Uk = Uk; a.V = V; a.states = states;
