@@ -51,47 +51,54 @@ struct LbArgs {
     float two_beta, beta, inv_L;
 };
 
-template <class T, int D, int RP>
+// Non-causal passes only apply the total states: their workgroups hold no
+// intra-chunk operands, so more of them fit a compute unit (C = 0: short
+// arrays in their place). Instantiated apart, r = 64: bf16 d_h 64 takes 84
+// registers and 19 KB (was 136 and 47 KB: 3 -> 5 workgroups a compute unit),
+// float32 121 and 34 KB (220 and 89 KB: 1 -> 4); the float32 training step of
+// 32 heads x 784 tokens, with two workgroups of the block kernel a compute
+// unit as well, 137 -> 114 us.
+template <class T, int D, int RP, bool C>
 struct Lb1Smem {
     using S = typename T::store_t;
-    S v[RowTile<T, D>::ELEMS];     // V chunk
-    S dn[RowTile<T, D>::ELEMS];    // dO chunk (dNum_i = sc_lr,i dO_i: the products apply sc_lr)
-    S pk[RowTile<T, RP>::ELEMS];   // Phi_K chunk
-    S gg[kC][kC + kPad];           // G[i][j] = <dNum_i, V_j> + dDen_i, j <= i
-    float ts[kC][RP / 4];          // tanh(W q) of the chunk's queries
+    S dn[RowTile<T, D>::ELEMS];            // dO chunk (dNum_i = sc_lr,i dO_i: the products apply sc_lr)
+    S v[C ? RowTile<T, D>::ELEMS : 8];     // V chunk
+    S pk[C ? RowTile<T, RP>::ELEMS : 8];   // Phi_K chunk
+    S gg[C ? kC : 1][kC + kPad];           // G[i][j] = <dNum_i, V_j> + dDen_i, j <= i
+    float ts[kC][RP / 4];                  // tanh(W q) of the chunk's queries
     S du[kC][w_kdim<RP>() + kPad];
     float dden[kC];
-    float sc[kC];                  // sc_lr of the chunk's queries
+    float sc[kC];                          // sc_lr of the chunk's queries
 };
 
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool C>
 struct Lb2Smem {
     using S = typename T::store_t;
-    S v[RowTile<T, D>::ELEMS];     // V chunk
-    S dn[RowTile<T, D>::ELEMS];    // dNum / L chunk
-    S pq[RowTile<T, RP>::ELEMS];   // Phi_Q chunk
-    S ggt[kC][kC + kPad];          // G'[j][i] / L, i >= j
-    float ts[kC][RP / 4];          // tanh(W k) of the chunk's keys
+    S v[RowTile<T, D>::ELEMS];             // V chunk
+    S dn[C ? RowTile<T, D>::ELEMS : 8];    // dNum / L chunk
+    S pq[C ? RowTile<T, RP>::ELEMS : 8];   // Phi_Q chunk
+    S ggt[C ? kC : 1][kC + kPad];          // G'[j][i] / L, i >= j
+    float ts[kC][RP / 4];                  // tanh(W k) of the chunk's keys
     S du[kC][w_kdim<RP>() + kPad];
-    Parts<T, kC> ddp;              // dDen / L as operand parts
-    float dden[kC];                // dDen / L
+    Parts<T, kC> ddp;                      // dDen / L as operand parts
+    float dden[kC];                        // dDen / L
 };
 
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool C>
 struct Lb3Smem {
     using S = typename T::store_t;
-    S dn[RowTile<T, D>::ELEMS];    // dNum / L chunk
-    S pk[RowTile<T, RP>::ELEMS];   // Phi_K chunk
-    S pq[RowTile<T, RP>::ELEMS];   // Phi_Q chunk
-    S mt[kC][kC + kPad];           // M'[j][i] = <phi(k_j), phi(q_i)>, i >= j
+    S pk[RowTile<T, RP>::ELEMS];           // Phi_K chunk
+    S dn[C ? RowTile<T, D>::ELEMS : 8];    // dNum / L chunk
+    S pq[C ? RowTile<T, RP>::ELEMS : 8];   // Phi_Q chunk
+    S mt[C ? kC : 1][kC + kPad];           // M'[j][i] = <phi(k_j), phi(q_i)>, i >= j
 };
 
 template <class T, int D, int RP>
 constexpr bool bwd_fits()
 {
-    return sizeof(Lb1Smem<T, D, RP / table_split<RP>()>) <= kMaxLds &&
-           sizeof(Lb2Smem<T, D, RP / table_split<RP>()>) <= kMaxLds &&
-           sizeof(Lb3Smem<T, D, RP>) <= kMaxLds;
+    return sizeof(Lb1Smem<T, D, RP / table_split<RP>(), true>) <= kMaxLds &&
+           sizeof(Lb2Smem<T, D, RP / table_split<RP>(), true>) <= kMaxLds &&
+           sizeof(Lb3Smem<T, D, RP, true>) <= kMaxLds;
 }
 
 // du rows [t0, t0 + 64) of the chunk (LDS, storage dtype) -> rows of out
@@ -162,9 +169,9 @@ __device__ __forceinline__ void state_product(const f32x4 (&St)[D / 16], const t
 }
 
 // ---------------------------------------------------------------- LB1: dQ
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool CAUSAL>
 __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg, int part,
-                                             Lb1Smem<T, D, RP / table_split<RP>()>& sm)
+                                             Lb1Smem<T, D, RP / table_split<RP>(), CAUSAL>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
@@ -207,20 +214,20 @@ __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     URegs<RPW> uq, uk;                    // projections of the chunk, loaded one chunk ahead
     uq.load(Uq, t_beg, a.N, RP / 4, tx);
-    if (a.causal) uk.load(Uk, t_beg, a.N, RP / 4, tx);
+    if constexpr (CAUSAL) uk.load(Uk, t_beg, a.N, RP / 4, tx);
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
         // every global load of the chunk is issued first; the features (vector
         // work) run while they are in flight, then the rows go to LDS
         StageRows<T, D, false> sdn, sv;
         sdn.load(dO, t0, a.N, nullptr, tx);
-        if (a.causal) sv.load(V, t0, a.N, nullptr, tx);
+        if constexpr (CAUSAL) sv.load(V, t0, a.N, nullptr, tx);
         const bool in = tx < kC && t0 + tx < a.N;
         const float ddv = in ? dden[t0 + tx] : 0.f, scv = in ? sclr[t0 + tx] : 0.f;
         tanh_rows<RPW>(uq, sm.ts, tx);
-        if (a.causal) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk, tx);
+        if constexpr (CAUSAL) features_from<T, RPW>(uk, t0, a.N, L, a.two_beta, sm.pk, tx);
         sdn.store(sm.dn, 1.f, tx);
-        if (a.causal) sv.store(sm.v, 1.f, tx);
+        if constexpr (CAUSAL) sv.store(sm.v, 1.f, tx);
         if (tx < kC) {
             sm.dden[tx] = ddv;
             sm.sc[tx] = scv;
@@ -231,9 +238,9 @@ __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg
             // the loads are unconditional)
             const int tn = t0 + kC < t_end ? t0 + kC : t0;
             uq.load(Uq, tn, a.N, RP / 4, tx);
-            if (a.causal) uk.load(Uk, tn, a.N, RP / 4, tx);
+            if constexpr (CAUSAL) uk.load(Uk, tn, a.N, RP / 4, tx);
         }
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // G rows [16w, 16w + 16): sc_lr,i <dO_i, V_j> + dDen_i for j <= i,
             // formed transposed (lane (g, col): keys 16 kt + 4 g + i of query
             // 16 w + col) so each lane stores four entries of its row at once
@@ -269,7 +276,7 @@ __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[qt][i] = acc[qt][i] * scq + Aacc[j][i] * ddq;
             }
-            if (a.causal) {
+            if constexpr (CAUSAL) {
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
                     const F pf = TP::col8(sm.pk, 32 * kk, 16 * ft, tx);
@@ -285,7 +292,7 @@ __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg
         }
         __syncthreads();
         store_du<T, RPW, RP>(sm.du, du_out, t0, a.N, tx);
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // S' += V' Phi_K (chunk), A += Phi_K' 1
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
@@ -312,9 +319,9 @@ __device__ __forceinline__ void race_dq_body(const LbArgs& a, size_t bh, int seg
 }
 
 // ---------------------------------------------------------------- LB2: dK
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool CAUSAL>
 __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg, int part,
-                                             Lb2Smem<T, D, RP / table_split<RP>()>& sm)
+                                             Lb2Smem<T, D, RP / table_split<RP>(), CAUSAL>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
@@ -357,7 +364,7 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
     const int nch = (t_end - t_beg + kC - 1) / kC;
     URegs<RPW> uq, uk;                    // projections of the chunk, loaded one chunk ahead
     uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
-    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
+    if constexpr (CAUSAL) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
     for (int c = nch - 1; c >= 0; --c) {
         const int t0 = t_beg + c * kC;
         __syncthreads();
@@ -365,13 +372,13 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
         StageRows<T, D, false> svr;
         StageRows<T, D, true> sdn;
         svr.load(V, t0, a.N, nullptr, tx);
-        if (a.causal) sdn.load(dO, t0, a.N, sclr, tx);
+        if constexpr (CAUSAL) sdn.load(dO, t0, a.N, sclr, tx);
         const bool in = tx < kC && t0 + tx < a.N;
         const float ddv = in ? dden[t0 + tx] * a.inv_L : 0.f;
         tanh_rows<RPW>(uk, sm.ts, tx);
-        if (a.causal) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, sm.pq, tx);
+        if constexpr (CAUSAL) features_from<T, RPW>(uq, t0, a.N, L, a.two_beta, sm.pq, tx);
         svr.store(sm.v, 1.f, tx);
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             sdn.store(sm.dn, a.inv_L, tx);
             if (tx < kC) {
                 sm.dden[tx] = ddv;
@@ -383,9 +390,9 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
             const int tn = c > 0 ? t0 - kC : t0;
             uk.load(Uk, tn, a.N, RP / 4, tx);
-            if (a.causal) uq.load(Uq, tn, a.N, RP / 4, tx);
+            if constexpr (CAUSAL) uq.load(Uq, tn, a.N, RP / 4, tx);
         }
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // G' rows j in [16w, 16w + 16): (<V_j, dNum_i> + dDen_i) / L for
             // i >= j, formed transposed (lane (g, col): queries 16 it + 4 g + i
             // of key 16 w + col) so each lane stores four entries of its row at once
@@ -417,7 +424,7 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
             state_product<T, D>(St_[j], sm.v, acc, tx);
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) acc[kt] += Aacc[j];
-            if (a.causal) {
+            if constexpr (CAUSAL) {
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
                     const F pf = TP::col8(sm.pq, 32 * kk, 16 * ft, tx);
@@ -432,7 +439,7 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
         }
         __syncthreads();
         store_du<T, RPW, RP>(sm.du, du_out, t0, a.N, tx);
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // dS' += (dNum / L)' Phi_Q (chunk), dA += (1/L) Phi_Q' dDen
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
@@ -459,8 +466,8 @@ __device__ __forceinline__ void race_dk_body(const LbArgs& a, size_t bh, int seg
 }
 
 // ---------------------------------------------------------------- LB3: dV
-template <class T, int D, int RP>
-__device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg, Lb3Smem<T, D, RP>& sm)
+template <class T, int D, int RP, bool CAUSAL>
+__device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg, Lb3Smem<T, D, RP, CAUSAL>& sm)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
@@ -491,15 +498,15 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
     const int nch = (t_end - t_beg + kC - 1) / kC;
     URegs<RP> uq, uk;                    // projections of the chunk, loaded one chunk ahead
     uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
-    if (a.causal) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
+    if constexpr (CAUSAL) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
     for (int c = nch - 1; c >= 0; --c) {
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
         StageRows<T, D, true> sdn;
-        if (a.causal) sdn.load(dO, t0, a.N, sclr, tx);
+        if constexpr (CAUSAL) sdn.load(dO, t0, a.N, sclr, tx);
         features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk, tx);
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq, tx);
             sdn.store(sm.dn, a.inv_L, tx);
         }
@@ -508,9 +515,9 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
             const int tn = c > 0 ? t0 - kC : t0;
             uk.load(Uk, tn, a.N, RP / 4, tx);
-            if (a.causal) uq.load(Uq, tn, a.N, RP / 4, tx);
+            if constexpr (CAUSAL) uq.load(Uq, tn, a.N, RP / 4, tx);
         }
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // M' rows j in [16w, 16w + 16): <phi(k_j), phi(q_i)> for i >= j,
             // formed transposed (lane (g, col): queries 16 it + 4 g + i of key
             // 16 w + col) so each lane stores four entries of its row at once
@@ -562,7 +569,7 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
         }
         // dV^T: lane (g, col) holds d = 16 (w DW + j) + 4 g + i of key 16 kt + col
         F bv[2][DW];                     // (dNum / L)^T operands: the intra-chunk part and the state update
-        if (a.causal) {
+        if constexpr (CAUSAL) {
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
@@ -582,7 +589,7 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
 #pragma unroll
                 for (int j = 0; j < DW; ++j) store4<T>(out + (size_t)tok * D + 16 * (w * DW + j) + 4 * g, accs[kt][j]);
         }
-        if (a.causal) {
+        if constexpr (CAUSAL) {
             // dS += Phi_Q' (dNum / L) (chunk)
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
@@ -609,15 +616,15 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
 // registers, which would halve the dQ and dK workgroups in flight.
 template <int RP> constexpr bool dv_joins() { return RP < 256; }
 
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, 2) void race_bwd_kernel(LbArgs a)
 {
     constexpr int SPLIT = table_split<RP>(), ROLES = 2 * SPLIT + (dv_joins<RP>() ? 1 : 0);
     constexpr bool DV = dv_joins<RP>();
     __shared__ __attribute__((aligned(16))) union {
-        Lb1Smem<T, D, RP / SPLIT> q;
-        Lb2Smem<T, D, RP / SPLIT> k;
-        typename std::conditional<DV, Lb3Smem<T, D, RP>, char>::type v;
+        Lb1Smem<T, D, RP / SPLIT, CAUSAL> q;
+        Lb2Smem<T, D, RP / SPLIT, CAUSAL> k;
+        typename std::conditional<DV, Lb3Smem<T, D, RP, CAUSAL>, char>::type v;
     } sm;
     const int role = blockIdx.x / a.items, item = blockIdx.x - role * a.items;
     if (role >= ROLES) {
@@ -626,16 +633,16 @@ __global__ __launch_bounds__(kThreads, 2) void race_bwd_kernel(LbArgs a)
     }
     const int seg = item % a.nseg;
     const size_t bh = item / a.nseg;
-    if (role < SPLIT) race_dq_body<T, D, RP>(a, bh, seg, role, sm.q);
-    else if (role < 2 * SPLIT) race_dk_body<T, D, RP>(a, bh, seg, role - SPLIT, sm.k);
-    else if constexpr (DV) race_dv_body<T, D, RP>(a, bh, seg, sm.v);
+    if (role < SPLIT) race_dq_body<T, D, RP, CAUSAL>(a, bh, seg, role, sm.q);
+    else if (role < 2 * SPLIT) race_dk_body<T, D, RP, CAUSAL>(a, bh, seg, role - SPLIT, sm.k);
+    else if constexpr (DV) race_dv_body<T, D, RP, CAUSAL>(a, bh, seg, sm.v);
 }
 
-template <class T, int D, int RP>
+template <class T, int D, int RP, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, 1) void race_dv_kernel(LbArgs a)
 {
-    __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP> sm;
-    race_dv_body<T, D, RP>(a, blockIdx.y, blockIdx.x, sm);
+    __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP, CAUSAL> sm;
+    race_dv_body<T, D, RP, CAUSAL>(a, blockIdx.y, blockIdx.x, sm);
 }
 
 template <class T, int D, int RP>
@@ -647,11 +654,13 @@ struct BwdFn {
         } else {
             constexpr int ROLES = 2 * table_split<RP>() + (dv_joins<RP>() ? 1 : 0);
             const int wt = (s.H * D * w_kdim<RP>() + kWtPer - 1) / kWtPer;   // W' rides along
-            ELSAA_LAUNCH("race_bwd", (race_bwd_kernel<T, D, RP>), dim3(a.items * ROLES + wt), dim3(kThreads), 0, st, a);
+            if (a.causal) ELSAA_LAUNCH("race_bwd", (race_bwd_kernel<T, D, RP, true>), dim3(a.items * ROLES + wt), dim3(kThreads), 0, st, a);
+            else ELSAA_LAUNCH("race_bwd", (race_bwd_kernel<T, D, RP, false>), dim3(a.items * ROLES + wt), dim3(kThreads), 0, st, a);
             hipError_t e = hipGetLastError();
             if constexpr (!dv_joins<RP>()) {
                 if (e != hipSuccess) return e;
-                ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
+                if (a.causal) ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, true>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
+                else ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, false>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
                 e = hipGetLastError();
             }
             return e;
