@@ -828,12 +828,15 @@ __global__ __launch_bounds__(kThreads, (two_pass_waves<T, D>())) void sparse_lea
 // one dQ partial row.
 //
 // waves per SIMD: three for 64-key blocks at d_h 64, two otherwise (a
-// 128-key block is 8 waves, two per SIMD)
-template <int D, int BQ>
-constexpr int block_waves() { return BQ == 64 && D == 64 ? 3 : 2; }
+// 128-key block is 8 waves, two per SIMD); float32 storage takes two at d_h
+// 64 (left to itself the compiler uses 260 registers, one too many for a
+// second workgroup: 416 blocks of 784 tokens x 32 heads 37 -> 31 us) and one
+// at d_h 128 (350 to 376 registers)
+template <class T, int D, int BQ>
+constexpr int block_waves() { return T::bytes == 4 ? (D == 64 ? 2 : 1) : BQ == 64 && D == 64 ? 3 : 2; }
 
 template <class T, int D, int BQ, int MODE, int QB = BQ, bool FULL = MODE == kLevels>
-__global__ __launch_bounds__(BQ * 4, (block_waves<D, BQ>())) void sparse_bwd_block_kernel(BArgs a)
+__global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_block_kernel(BArgs a)
 {
     using S = typename T::store_t;
     using F = typename T::frag_t;
