@@ -471,7 +471,8 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
-    constexpr int DW = D / 64, FS = RP / 32;
+    constexpr int NW = state_waves<D, RP>(), WS = NW / 4, RW = RP / WS;   // as in race_out
+    constexpr int DW = D / (16 * NW), FS = RP / 32;
     using TV = RowTile<T, D>;
     using TP = RowTile<T, RP>;
     const float* Uq = a.Uq + bh * a.N * (RP / 4);
@@ -483,6 +484,7 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
     asm volatile("" : "+v"(tx));                                  // this body's own copy (race_common.hpp)
     const int lane = tx & 63, w = __builtin_amdgcn_readfirstlane(tx >> 6);
     const int g = lane >> 4, col = lane & 15;
+    const int grp = WS > 1 ? w >> 2 : 0, wq = w - 4 * grp, tg = tx - kThreads * grp;   // group, place in it
 
     const float* st_in = a.states_b + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
     f32x4 S[RP / 16][DW];
@@ -496,38 +498,38 @@ __device__ __forceinline__ void race_dv_body(const LbArgs& a, size_t bh, int seg
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
     const int nch = (t_end - t_beg + kC - 1) / kC;
-    URegs<RP> uq, uk;                    // projections of the chunk, loaded one chunk ahead
-    uk.load(Uk, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
-    if constexpr (CAUSAL) uq.load(Uq, t_beg + (nch - 1) * kC, a.N, RP / 4, tx);
+    URegs<RW> uq, uk;                    // projections of the chunk, loaded one chunk ahead
+    uk.load(Uk + grp * (RW / 4), t_beg + (nch - 1) * kC, a.N, RP / 4, tg);
+    if constexpr (CAUSAL) uq.load(Uq + grp * (RW / 4), t_beg + (nch - 1) * kC, a.N, RP / 4, tg);
     for (int c = nch - 1; c >= 0; --c) {
         const int t0 = t_beg + c * kC;
         __syncthreads();
         // loads first, features under them, then the LDS stores
-        StageRows<T, D, true> sdn;
+        StageRows<T, D, true, NW * 64> sdn;
         if constexpr (CAUSAL) sdn.load(dO, t0, a.N, sclr, tx);
-        features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.pk, tx);
+        features_from<T, RW, RP>(uk, t0, a.N, a.L - grp * (RW / 16), a.two_beta, sm.pk + grp * RW, tg);
         if constexpr (CAUSAL) {
-            features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.pq, tx);
+            features_from<T, RW, RP>(uq, t0, a.N, a.L - grp * (RW / 16), a.two_beta, sm.pq + grp * RW, tg);
             sdn.store(sm.dn, a.inv_L, tx);
         }
         __syncthreads();
         {
             // previous chunk's projections (unconditional: chunk 0 reloads its own)
             const int tn = c > 0 ? t0 - kC : t0;
-            uk.load(Uk, tn, a.N, RP / 4, tx);
-            if constexpr (CAUSAL) uq.load(Uq, tn, a.N, RP / 4, tx);
+            uk.load(Uk + grp * (RW / 4), tn, a.N, RP / 4, tg);
+            if constexpr (CAUSAL) uq.load(Uq + grp * (RW / 4), tn, a.N, RP / 4, tg);
         }
         if constexpr (CAUSAL) {
-            // M' rows j in [16w, 16w + 16): <phi(k_j), phi(q_i)> for i >= j,
+            // M' rows j in [16wq, 16wq + 16): <phi(k_j), phi(q_i)> for i >= j,
             // formed transposed (lane (g, col): queries 16 it + 4 g + i of key
-            // 16 w + col) so each lane stores four entries of its row at once
-            const int kj = 16 * w + col;
+            // 16 wq + col) so each lane stores four entries of its row at once
+            const int kj = 16 * wq + col;
             F kf[FS];
 #pragma unroll
             for (int fs = 0; fs < FS; ++fs) kf[fs] = TP::row8(sm.pk, kj, 32 * fs + 8 * g);
-            for (int it = 0; it < 4; ++it) {
+            for (int it = grp; it < 4; it += WS) {
                 f32x4 acc = {0, 0, 0, 0};
-                if (it >= w) {
+                if (it >= wq) {
 #pragma unroll
                     for (int fs = 0; fs < FS; ++fs)
                         acc = T::mma(TP::row8(sm.pq, 16 * it + col, 32 * fs + 8 * g), kf[fs], acc);
@@ -639,7 +641,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_bwd_kernel(LbArgs a)
 }
 
 template <class T, int D, int RP, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, 1) void race_dv_kernel(LbArgs a)
+__global__ __launch_bounds__((state_waves<D, RP>() * 64), (state_waves<D, RP>() / 4)) void race_dv_kernel(LbArgs a)
 {
     __shared__ __attribute__((aligned(16))) Lb3Smem<T, D, RP, CAUSAL> sm;
     race_dv_body<T, D, RP, CAUSAL>(a, blockIdx.y, blockIdx.x, sm);
@@ -659,8 +661,8 @@ struct BwdFn {
             hipError_t e = hipGetLastError();
             if constexpr (!dv_joins<RP>()) {
                 if (e != hipSuccess) return e;
-                if (a.causal) ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, true>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
-                else ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, false>), dim3(s.nseg, s.H * s.B), dim3(kThreads), 0, st, a);
+                if (a.causal) ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, true>), dim3(s.nseg, s.H * s.B), dim3(state_waves<D, RP>() * 64), 0, st, a);
+                else ELSAA_LAUNCH("race_dv", (race_dv_kernel<T, D, RP, false>), dim3(s.nseg, s.H * s.B), dim3(state_waves<D, RP>() * 64), 0, st, a);
                 e = hipGetLastError();
             }
             return e;

@@ -134,20 +134,30 @@ template <int RP> constexpr int w_kdim() { return RP / 4 < 32 ? 32 : RP / 4; }
 // so a workgroup's registers and LDS are those of the 128-feature passes.
 template <int RP> constexpr int table_split() { return RP == 256 ? 2 : 1; }
 
+// Waves of the passes that hold a segment's whole state (race_out, race_dv):
+// each keeps the state's 16 * (D / 16 / waves) columns in registers.  At 256
+// features four waves of D = 128 hold 128 state registers each and one wave
+// fits a SIMD, so nothing covers its waits; eight hold 64 and two fit
+// (8 heads x 65536: race_out 285 -> 239 us, race_dv 251 -> 217).  At 128
+// features four waves already fit twice and eight are slower (16384 tokens x
+// 16 heads: forward 450 against 465 us).
+template <int D, int RP> constexpr int state_waves() { return RP == 256 && D == 128 ? 8 : 4; }
+
 // Rows [t0, t0 + 64) of X (zero past N) into a RowTile, each multiplied by
 // scale[row] * mul when SCALED.  load() issues every global load of the
 // thread into registers (16 or 8 consecutive lanes cover a row) and store()
 // writes them to LDS, so the loads fly while the chunk's features are formed.
 // Rows past N are loaded clamped to row N - 1 and zeroed in store(), so the
 // loads carry no per-lane branches and later waits count exactly.
-template <class T, int D, bool SCALED>
+// THREADS: threads that share the chunk (tx in [0, THREADS)).
+template <class T, int D, bool SCALED, int THREADS = kThreads>
 struct StageRows {
     using S = typename T::store_t;
     using Tl = RowTile<T, D>;
     static constexpr int PER = 16 / T::bytes;
     static constexpr int CH = D / PER;
-    static constexpr int ITEMS = kC * CH, PT = ITEMS / kThreads;
-    static_assert(ITEMS % kThreads == 0, "staging split");
+    static constexpr int ITEMS = kC * CH, PT = ITEMS / THREADS;
+    static_assert(ITEMS % THREADS == 0, "staging split");
     uint4 v[PT];
     float sc[SCALED ? PT : 1];
     int t0_, n_;
@@ -157,7 +167,7 @@ struct StageRows {
         n_ = N;
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int it = tx + j * kThreads;
+            const int it = tx + j * THREADS;
             const int r = min(t0 + it / CH, N - 1);
             v[j] = ldg16(X + (size_t)r * D + (it % CH) * PER);
             if constexpr (SCALED) sc[j] = scale[r];
@@ -167,7 +177,7 @@ struct StageRows {
     {
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int it = tx + j * kThreads;
+            const int it = tx + j * THREADS;
             const int r = it / CH;
             if (t0_ + r >= n_) v[j] = make_uint4(0, 0, 0, 0);
             S* dst = t + Tl::row(r) + (it % CH) * PER;
@@ -213,8 +223,10 @@ struct URegs {
 
 // Features of chunk tokens [t0 + 16w, t0 + 16w + 16) for every table, from
 // the projections t = tanh(u) in ur (URegs::load of the same chunk), into a
-// feature RowTile (zero for padded tables and rows past N).
-template <class T, int RP>
+// feature RowTile (zero for padded tables and rows past N).  W: row width of
+// that tile (RP, or more when ur holds some of the tables, ph then pointing
+// at their first column).
+template <class T, int RP, int W = RP>
 __device__ __forceinline__ void features_from(const URegs<RP>& ur, int t0, int N, int L, float two_beta,
                                               typename T::store_t* ph, int tx = threadIdx.x)
 {
@@ -238,7 +250,7 @@ __device__ __forceinline__ void features_from(const URegs<RP>& ur, int t0, int N
             phi[c] = (((c & 1) ? sp[0] : sn[0]) * ((c & 2) ? sp[1] : sn[1])) *
                      (((c & 4) ? sp[2] : sn[2]) * ((c & 8) ? sp[3] : sn[3]));
         using F = typename T::frag_t;
-        typename T::store_t* dst = ph + RowTile<T, RP>::row(tl) + 16 * tb;
+        typename T::store_t* dst = ph + RowTile<T, W>::row(tl) + 16 * tb;
         *(F*)dst = T::pack(phi);
         *(F*)(dst + 8) = T::pack(phi + 8);
     }

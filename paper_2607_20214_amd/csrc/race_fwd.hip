@@ -46,7 +46,7 @@ struct OutSmem {
     S phk[RowTile<T, RP>::ELEMS]; // Phi_K chunk
     S mm[kC][kC + kPad];          // tril(Phi_Q Phi_K') / L
     Parts<T, RP> a_state;
-    float den[kC];
+    float den[state_waves<D, RP>() / 4][kC];  // parts of Den
 };
 
 struct StateArgs {
@@ -287,11 +287,14 @@ struct OutArgs {
 };
 
 template <class T, int D, int RP>
-__global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
+__global__ __launch_bounds__((state_waves<D, RP>() * 64), 2) void race_out_kernel(OutArgs a)
 {
     using St = typename T::store_t;
     using F = typename T::frag_t;
-    constexpr int DW = D / 64;
+    // WS groups of four waves: a chunk's feature tables and the key tiles of
+    // its kernel matrix are dealt over the groups
+    constexpr int NW = state_waves<D, RP>(), WS = NW / 4, RW = RP / WS;
+    constexpr int DW = D / (16 * NW);
     constexpr int FS = RP / 32;
     using TV = RowTile<T, D>;
     using TP = RowTile<T, RP>;
@@ -305,6 +308,7 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
     float* dlr = a.d_lr + bh * a.N;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // wave-uniform, as in race_state
     const int g = lane >> 4, col = lane & 15;
+    const int grp = WS > 1 ? w >> 2 : 0, wq = w - 4 * grp, tx = threadIdx.x - kThreads * grp;   // group, place in it
 
     const float* st_in = a.states + (bh * a.nseg + seg) * (size_t)(RP * D + RP);
     f32x4 S[RP / 16][DW];
@@ -315,65 +319,65 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 S[ft][j][i] = st_in[(size_t)(16 * ft + 4 * g + i) * D + 16 * (w * DW + j) + col];
-    for (int f = threadIdx.x; f < RP; f += kThreads) sm.a_state.put(f, st_in[RP * D + f]);
+    for (int f = threadIdx.x; f < RP; f += NW * 64) sm.a_state.put(f, st_in[RP * D + f]);
     // A runs on the matrix cores (causal): wave w keeps the feature tiles
-    // ft = w, w + 4, ... in accumulator tiles (every column holds the sums;
+    // ft = w, w + NW, ... in accumulator tiles (every column holds the sums;
     // column 0 starts from the segment's prefix state and is published to
     // a_state after each chunk)
-    constexpr int FT = RP / 16, NFA = (FT + 3) / 4;
+    constexpr int FT = RP / 16, NFA = (FT + NW - 1) / NW;
     f32x4 Aacc[NFA];
 #pragma unroll
     for (int j = 0; j < NFA; ++j) {
-        const int ft = w + 4 * j;
+        const int ft = w + NW * j;
 #pragma unroll
         for (int i = 0; i < 4; ++i) Aacc[j][i] = ft < FT && col == 0 ? st_in[RP * D + 16 * ft + 4 * g + i] : 0.f;
     }
 
     const int t_beg = seg * a.seg_len, t_end = min(a.N, t_beg + a.seg_len);
-    URegs<RP> uq, uk;                    // projections and V rows of the chunk, loaded one chunk ahead
-    StageRows<T, D, false> vr;
-    uq.load(Uq, t_beg, a.N);
+    URegs<RW> uq, uk;                    // projections and V rows of the chunk, loaded one chunk ahead
+    StageRows<T, D, false, NW * 64> vr;
+    uq.load(Uq + grp * (RW / 4), t_beg, a.N, RP / 4, tx);
     if (a.causal) {
-        uk.load(Uk, t_beg, a.N);
+        uk.load(Uk + grp * (RW / 4), t_beg, a.N, RP / 4, tx);
         vr.load(V, t_beg, a.N);
     }
     for (int t0 = t_beg; t0 < t_end; t0 += kC) {
         __syncthreads();
-        features_from<T, RP>(uq, t0, a.N, a.L, a.two_beta, sm.phq);
+        features_from<T, RW, RP>(uq, t0, a.N, a.L - grp * (RW / 16), a.two_beta, sm.phq + grp * RW, tx);
         if (a.causal) {
             vr.store(sm.v);
-            features_from<T, RP>(uk, t0, a.N, a.L, a.two_beta, sm.phk);
+            features_from<T, RW, RP>(uk, t0, a.N, a.L - grp * (RW / 16), a.two_beta, sm.phk + grp * RW, tx);
         }
         __syncthreads();
         {
             // next chunk's rows (the last chunk reloads its own: unconditional loads)
             const int tn = t0 + kC < t_end ? t0 + kC : t0;
-            uq.load(Uq, tn, a.N);
+            uq.load(Uq + grp * (RW / 4), tn, a.N, RP / 4, tx);
             if (a.causal) {
-                uk.load(Uk, tn, a.N);
+                uk.load(Uk + grp * (RW / 4), tn, a.N, RP / 4, tx);
                 vr.load(V, tn, a.N);
             }
         }
-        // the wave's 16 queries: Den, inter part (1/L) Phi_Q . A (every row of
-        // the product tile alike), and the rows [16w, 16w + 16) of the
+        // the wave's 16 queries: Den (with two groups, the group's half of it), inter part (1/L) Phi_Q . A (every row of
+        // the product tile alike), and the rows [16wq, 16wq + 16) of the
         // intra-chunk kernel matrix (causal), formed transposed: lane (g, col)
-        // holds keys 16 kt + 4 g + i of query 16 w + col, so a row's four
+        // holds keys 16 kt + 4 g + i of query 16 wq + col, so a row's four
         // entries leave in one store and its sum is in-lane plus one exchange
         // over the lane groups
         {
-            const int qi = 16 * w + col;
+            const int qi = 16 * wq + col;
             F qf[FS];
             f32x4 da = {0, 0, 0, 0};
 #pragma unroll
             for (int fs = 0; fs < FS; ++fs) {
                 qf[fs] = TP::row8(sm.phq, qi, 32 * fs + 8 * g);
-                da = sm.a_state.mma_a(32 * fs + 8 * g, qf[fs], da);
+                if (fs / (FS / WS) == grp) da = sm.a_state.mma_a(32 * fs + 8 * g, qf[fs], da);
             }
             float rs = 0.f;
             if (a.causal) {
-                for (int kt = 0; kt < 4; ++kt) {
+                for (int kt = grp; kt < 4; kt += WS) {
                     f32x4 mt = {0, 0, 0, 0};
-                    if (kt <= w) {
+                    if (kt <= wq) {
 #pragma unroll
                         for (int fs = 0; fs < FS; ++fs)
                             mt = T::mma(TP::row8(sm.phk, 16 * kt + col, 32 * fs + 8 * g), qf[fs], mt);
@@ -391,8 +395,8 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
             }
             if (g == 0) {
                 const float den = da[0] * a.inv_L + rs;
-                sm.den[qi] = den;
-                if (t0 + qi < a.N) dlr[t0 + qi] = den;
+                sm.den[grp][qi] = den;
+                if (WS == 1 && t0 + qi < a.N) dlr[t0 + qi] = den;
             }
         }
         __syncthreads();
@@ -448,7 +452,12 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
         for (int qt = 0; qt < 4; ++qt) {
             const int ql = 16 * qt + col;
             const int tok = t0 + ql;
-            const float inv = 1.f / (sm.den[ql] + a.eps);
+            float den = sm.den[0][ql];
+            if constexpr (WS > 1) {
+                den += sm.den[WS - 1][ql];
+                if (w == 0 && g == 0 && tok < a.N) dlr[tok] = den;
+            }
+            const float inv = 1.f / (den + a.eps);
             if (tok < a.N) {
 #pragma unroll
                 for (int j = 0; j < DW; ++j)
@@ -464,13 +473,13 @@ __global__ __launch_bounds__(kThreads, 2) void race_out_kernel(OutArgs a)
                     const F af = TP::col8(sm.phk, 32 * kk, 16 * ft);
 #pragma unroll
                     for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[kk][j], S[ft][j]);
-                    if (ft % 4 == w) Aacc[ft / 4] = token_sums<T>(af, Aacc[ft / 4]);
+                    if (ft % NW == w) Aacc[ft / NW] = token_sums<T>(af, Aacc[ft / NW]);
                 }
             }
             // the den of the next chunk reads a_state after its first barrier
 #pragma unroll
             for (int j = 0; j < NFA; ++j) {
-                const int ft = w + 4 * j;
+                const int ft = w + NW * j;
                 if (ft < FT && col == 0)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) sm.a_state.put(16 * ft + 4 * g + i, Aacc[j][i]);
@@ -530,7 +539,7 @@ hipError_t launch_out_t(const Shape& s, const OutArgs& a, hipStream_t st)
         return hipErrorInvalidConfiguration;
     } else {
         dim3 grid(s.nseg, s.H, s.B);
-        ELSAA_LAUNCH("race_out", (race_out_kernel<T, D, RP>), grid, dim3(kThreads), 0, st, a);
+        ELSAA_LAUNCH("race_out", (race_out_kernel<T, D, RP>), grid, dim3(state_waves<D, RP>() * 64), 0, st, a);
         return hipGetLastError();
     }
 }
