@@ -159,6 +159,57 @@ __host__ __device__ constexpr size_t dq_lds_bytes(int wk)
            (MODE == kLevels ? 0 : WtStage<T, D>::bytes(wk));
 }
 
+// The last part of dQ for 64 query rows (their float32 sums as LDS rows eq):
+// the rows' level partials (leaf) are added, and the nq rows that exist stored.
+template <class T, int D, int MODE>
+__device__ __forceinline__ void dq_rows(const BArgs& a, size_t bh, int leaf, int qrow0, int nq, const float* eq)
+{
+    using S = typename T::store_t;
+    const int N = a.N;
+    if (nq <= 0) return;
+    constexpr int RS = D + 4;                     // LDS row stride (floats)
+    constexpr int PPR = D / 8, RPP = kThreads / PPR, NPASS = 64 / RPP;
+    const int c8 = 8 * ((int)threadIdx.x % PPR);
+    // rows past the tile's queries read the first query's rows (loads
+    // without a branch) and store nothing
+    const int tok0 = MODE == kLeaf ? qrow0 : a.perm_q[bh * N + qrow0];
+    int tokr[NPASS], tokl[NPASS];
+    float s8[NPASS][8];
+#pragma unroll
+    for (int ps = 0; ps < NPASS; ++ps) {
+        const int r = ps * RPP + (int)threadIdx.x / PPR;
+        tokr[ps] = r < nq ? (MODE == kLeaf ? qrow0 + r : a.perm_q[bh * N + qrow0 + r]) : -1;
+        tokl[ps] = tokr[ps] >= 0 ? tokr[ps] : tok0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s8[ps][e] = eq[r * RS + c8 + e];
+    }
+    unsigned lmask = MODE == kLeaf ? leaf_levels(a.lt, leaf, true) : 0u;
+    while (lmask) {
+        int64_t base[2];
+        bool use[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            use[j] = lmask != 0;
+            base[j] = 0;
+            if (use[j]) {
+                const int l = __builtin_ctz(lmask);
+                lmask &= lmask - 1;
+                base[j] = seg_slot_base(a.lt, bh, l, leaf >> (a.Lv - l), true);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (use[j])
+#pragma unroll
+                for (int ps = 0; ps < NPASS; ++ps) {
+                    add8<T>((const S*)a.part_dq + (size_t)(base[j] + tokl[ps]) * D + c8, s8[ps]);
+                }
+    }
+#pragma unroll
+    for (int ps = 0; ps < NPASS; ++ps)
+        if (tokr[ps] >= 0) store8<T>((S*)a.dQ + (bh * N + tokr[ps]) * D + c8, s8[ps]);
+}
+
 template <class T, int D, int MODE>
 __device__ __forceinline__ void sparse_dq_body(const BArgs& a, int tile, int h, int b, char* smem)
 {
@@ -365,48 +416,163 @@ __device__ __forceinline__ void sparse_dq_body(const BArgs& a, int tile, int h, 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *(f32x4*)&eq[(16 * w + qq) * RS + 16 * dt + 4 * g] = tot[dt];
     __syncthreads();
-    if (nq <= 0) return;
-    constexpr int PPR = D / 8, RPP = kThreads / PPR, NPASS = 64 / RPP;
-    const int c8 = 8 * ((int)threadIdx.x % PPR);
-    // rows past the tile's queries read the first query's rows (loads
-    // without a branch) and store nothing
-    const int tok0 = MODE == kLeaf ? qrow0 : a.perm_q[bh * N + qrow0];
-    int tokr[NPASS], tokl[NPASS];
-    float s8[NPASS][8];
+    dq_rows<T, D, MODE>(a, bh, tile / a.lt.per_leaf, qrow0, nq, eq);
+}
+
+// ------------------------------------------------------------------------
+// Wide form of the leaf's dQ (bf16): 128 queries per workgroup, 32 per wave,
+// on the 32 x 32 x 16 matrix instruction.  The 64-query form is bound by LDS
+// reads (each K, V or K^T fragment serves 16 queries: about 3000 cycles of
+// LDS per tile and compute unit against 1500 of matrix products); here each
+// serves 32, and a tile is staged once for 128 queries.  Operand layouts as in
+// the forward's wide form: lane l (h = l / 32) holds for query l % 32 the keys
+// 8 b + 4 h + i of a 32-key sub-tile in accumulator register 4 b + i; row rho
+// of a dQ^T tile is d = 16 dt + rho % 16 + (rho / 16) D / 2.
+// ------------------------------------------------------------------------
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int D>
+__device__ __forceinline__ void leaf_dq_wide_body(const BArgs& a, int tile, int hd, int b, char* smem)
+{
+    using T = BF16;
+    using S = T::store_t;
+    using F = T::frag_t;
+    constexpr int QT = kWideTile, QW = QT / 4;   // queries per workgroup, per wave
+    constexpr int KS = D / 16, DT = D / 32;
+    using TD = tile::Tile<T, D, kThreads>;
+    constexpr int PT = TD::PER_THREAD;
+    S* const sk = (S*)smem;
+    S* const sv = sk + TD::elems(kT);
+    S* const swt = sv + TD::elems(kT);           // W'
+    const size_t bh = (size_t)b * a.H + hd;
+    const int N = a.N;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int h = lane >> 5, qq = lane & 31;
+    const S* Q = (const S*)a.Q + bh * N * D;
+    const S* K = (const S*)a.K + bh * N * D;
+    const S* V = (const S*)a.V + bh * N * D;
+    const S* dO = (const S*)a.dO + bh * N * D;
+
+    int leaf, kbeg, q0, lend;
+    leaf_tile<QT>(a.lt, tile, leaf, kbeg, q0, lend);
+    const int qpos = q0 + QW * w + qq, qtok = qpos < lend ? qpos : -1;
+    const int kend = q0 < lend ? min(q0 + QT, lend) : kbeg;   // a tile past the leaf's real tokens has no work
+    const int nq = max(0, min(QT, lend - q0));
+
+    auto tokens = [&](int k0, int (&tok)[PT]) {   // (positions past the range repeat its last key, masked)
 #pragma unroll
-    for (int ps = 0; ps < NPASS; ++ps) {
-        const int r = ps * RPP + (int)threadIdx.x / PPR;
-        tokr[ps] = r < nq ? (MODE == kLeaf ? qrow0 + r : a.perm_q[bh * N + qrow0 + r]) : -1;
-        tokl[ps] = tokr[ps] >= 0 ? tokr[ps] : tok0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s8[ps][e] = eq[r * RS + c8 + e];
+        for (int j = 0; j < PT; ++j) tok[j] = min(k0 + TD::row_of(j), kend - 1);
+    };
+    const int ntiles = (kend - kbeg + kT - 1) / kT;
+    int tok[PT];
+    uint4 rk[PT], rv[PT];
+    const size_t wh = (size_t)hd * D * a.wk;
+    WtStage<T, D>::issue((const S*)a.wt_hi + wh, (const S*)a.wt_lo + wh, a.wk, swt);
+    if (ntiles > 0) {
+        tokens(kbeg, tok);
+        TD::load_all(K, tok, rk);
+        TD::load_all(V, tok, rv);
     }
-    const int leaf = tile / a.lt.per_leaf;
-    unsigned lmask = MODE == kLeaf ? leaf_levels(a.lt, leaf, true) : 0u;
-    while (lmask) {
-        int64_t base[2];
-        bool use[2];
+    // this lane's query (no query: row 0, masked and not stored)
+    const size_t row = bh * N + max(qtok, 0);
+    const float lse2 = a.rs[row], delta = a.rs[a.BHN + row], scs = a.rs[2 * a.BHN + row];
+    F qf[KS], df[KS];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            use[j] = lmask != 0;
-            base[j] = 0;
-            if (use[j]) {
-                const int l = __builtin_ctz(lmask);
-                lmask &= lmask - 1;
-                base[j] = seg_slot_base(a.lt, bh, l, leaf >> (a.Lv - l), true);
+    for (int ks = 0; ks < KS; ++ks) {
+        qf[ks] = T::ld8(Q + (size_t)max(qtok, 0) * D + 16 * ks + 8 * h);
+        df[ks] = T::ld8(dO + (size_t)max(qtok, 0) * D + 16 * ks + 8 * h);
+    }
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+
+    if (ntiles == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    for (int t = 0; t < ntiles; ++t) {
+        const int k0 = kbeg + t * kT;
+        if (t > 0) __syncthreads();
+        TD::store(sk, rk);
+        TD::store(sv, rv);
+        if (t == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // W' in LDS
+        __syncthreads();
+        if (t + 1 < ntiles) {
+            tokens(k0 + kT, tok);
+            TD::load_all(K, tok, rk);
+            TD::load_all(V, tok, rv);
+        }
+        // a wave none of whose queries sees a key of the tile skips it; one
+        // whose queries all see it whole skips the mask
+        if (!__any(k0 <= qtok)) continue;
+        const bool full = __all(k0 + kT - 1 <= qtok);          // (then k0 + kT <= kend as well)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            f32x16 st, dp;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { st[i] = 0.f; dp[i] = 0.f; }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TD::row8(sk, 32 * s + qq, 16 * ks + 8 * h), qf[ks], st, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TD::row8(sv, 32 * s + qq, 16 * ks + 8 * h), df[ks], dp, 0, 0, 0);
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                float v8[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int e = 8 * m + j;
+                    float P = fast_exp2(fmaf(st[e], a.tau2, -lse2));
+                    if (!full) {
+                        const int p = k0 + 32 * s + 8 * (e >> 2) + 4 * h + (e & 3);
+                        P = p <= qtok ? P : 0.f;
+                    }
+                    v8[j] = P * fmaf(scs, dp[e], -delta);
+                }
+                const F bf = T::pack(v8);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const int i = lane & 15, r = 32 * s + 16 * m + 4 * h + (i >> 2);
+                    const int c = 16 * dt + (D / 2) * ((lane >> 4) & 1) + 4 * (i & 3);
+                    const bf16x4 lo = lds_read_tr4(&sk[TD::row(r) + c]), hi = lds_read_tr4(&sk[TD::row(r + 8) + c]);
+                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        F{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, bf, acc[dt], 0, 0, 0);
+                }
             }
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (use[j])
-#pragma unroll
-                for (int ps = 0; ps < NPASS; ++ps) {
-                    add8<T>((const S*)a.part_dq + (size_t)(base[j] + tokl[ps]) * D + c8, s8[ps]);
-                }
     }
+    // plus the low-rank part (du W')^T, W' from LDS, in the same row order
+    const S* du = (const S*)a.du_q + row * a.wk;
+    const int wkp = a.wk + 8;
 #pragma unroll
-    for (int ps = 0; ps < NPASS; ++ps)
-        if (tokr[ps] >= 0) store8<T>((S*)a.dQ + (bh * N + tokr[ps]) * D + c8, s8[ps]);
+    for (int dt = 0; dt < DT; ++dt) acc[dt] *= a.tau;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (16 * j < a.wk) {
+            const F duf = T::ld8(du + 16 * j + 8 * h);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const S* p = swt + (16 * dt + (qq & 15) + (D / 2) * (qq >> 4)) * wkp + 16 * j + 8 * h;
+                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(T::ld8(p), duf, acc[dt], 0, 0, 0);
+                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(T::ld8(p + D * wkp), duf, acc[dt], 0, 0, 0);
+            }
+        }
+    // whole rows through LDS
+    constexpr int RS = D + 4;
+    static_assert(QT * RS * 4 <= dq_lds_bytes<T, D, kLeaf>(WtStage<T, D>::kMaxWk), "row sums fit in the pass's LDS");
+    float* const eq = (float*)smem;
+    __syncthreads();                              // every wave is done with the tiles and W'
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(f32x4*)&eq[(QW * w + qq) * RS + 16 * dt + (D / 2) * (q >> 1) + 8 * (q & 1) + 4 * h] =
+                f32x4{acc[dt][4 * q], acc[dt][4 * q + 1], acc[dt][4 * q + 2], acc[dt][4 * q + 3]};
+    __syncthreads();
+    for (int p = 0; 64 * p < nq; ++p)
+        dq_rows<T, D, kLeaf>(a, bh, leaf, q0 + 64 * p, min(64, nq - 64 * p), eq + 64 * p * RS);
 }
 
 // ------------------------------------------------------------------------
@@ -781,17 +947,19 @@ __global__ __launch_bounds__(kThreads, (two_pass_waves<T, D>())) void sparse_dkv
 // for dQ, then its key tiles for dK, dV) are consecutive, so they run on one
 // XCD at about the same time and the leaf's Q, K, V, dO rows, read by both
 // passes, come from that XCD's L2 the second time.
-template <class T, int D>
+template <class T, int D, bool WIDE>
 __global__ __launch_bounds__(kThreads, (two_pass_waves<T, D>())) void sparse_leaf_bwd_kernel(BArgs a)
 {
     int t2, h, b;
     xcd_tile(t2, h, b);
-    const int per = a.lt.per_leaf, leaf = t2 / (2 * per), r = t2 - leaf * 2 * per;
+    const int perk = a.lt.per_leaf, perq = WIDE ? a.lt.wper_leaf : perk, per = perq + perk;
+    const int leaf = t2 / per, r = t2 - leaf * per;
     // the two passes share one LDS region (a workgroup runs one of them)
     constexpr size_t q = dq_lds<T, D, kLeaf>(), kv = dkv_lds<T, D, kLeaf>();
     __shared__ __attribute__((aligned(16))) char smem[q > kv ? q : kv];
-    if (r < per) sparse_dq_body<T, D, kLeaf>(a, leaf * per + r, h, b, smem);
-    else sparse_dkv_body<T, D, kLeaf>(a, leaf * per + r - per, h, b, smem);
+    if (r >= perq) sparse_dkv_body<T, D, kLeaf>(a, leaf * perk + r - perq, h, b, smem);
+    else if constexpr (WIDE) leaf_dq_wide_body<D>(a, leaf * perq + r, h, b, smem);
+    else sparse_dq_body<T, D, kLeaf>(a, leaf * perq + r, h, b, smem);
 }
 
 // ------------------------------------------------------------------------
@@ -1273,6 +1441,20 @@ void launch_level_blocks(const Shape& s, const BArgs& a, hipStream_t st)
     else launch_blocks<T, D, BQ, kLevels, QB, false>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
 }
 
+// Where the leaf's wide dQ is the faster one (whole backwards, d_h 128, us):
+// leaves from 1024 tokens once its tiles give every compute unit one (16
+// heads, one leaf of 2000: 167 -> 154; 32000 tokens, leaves of 4000: step
+// 4820 -> 4606; 24 and 128 tiles: 77 -> 90, 70 -> 74, slower),
+// shorter ones from 448 only where there are many (4096 tiles, leaves of 500:
+// 2199 -> 2166, of 1000: 2271 -> 2207; 256 tiles, leaves of 512: 137 -> 145).
+// Leaves of 256 gain nothing (853 both) and of 174 lose (639 -> 647): half of
+// a 128-query tile is the diagonal.
+bool wide_leaf_dq(const Shape& s)
+{
+    const long tiles = (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H;
+    return s.bf16 && (s.n_leaf >= 1024 ? tiles >= 256 : s.n_leaf >= 448 && tiles >= 2048);
+}
+
 template <class T, int D>
 hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
 {
@@ -1325,8 +1507,12 @@ hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
         }
     }
     if ((parts & kSparseFinal) == kSparseFinal) {
-        dim3 grid(2 * a.lt.leaf_tiles(), s.H, s.B);
-        ELSAA_LAUNCH("sparse_leaf_bwd", (sparse_leaf_bwd_kernel<T, D>), grid, dim3(kThreads), 0, st, a);
+        const bool wide = wide_leaf_dq(s);
+        dim3 grid(a.lt.leaf_tiles() + (wide ? a.lt.wper_leaf * a.lt.leaves : a.lt.leaf_tiles()), s.H, s.B);
+        if constexpr (T::bytes == 2) {
+            if (wide) ELSAA_LAUNCH("sparse_leaf_bwd", (sparse_leaf_bwd_kernel<T, D, true>), grid, dim3(kThreads), 0, st, a);
+        }
+        if (!wide) ELSAA_LAUNCH("sparse_leaf_bwd", (sparse_leaf_bwd_kernel<T, D, false>), grid, dim3(kThreads), 0, st, a);
         return hipGetLastError();
     }
     dim3 grid(a.lt.leaf_tiles(), s.H, s.B);

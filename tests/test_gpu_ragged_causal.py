@@ -99,15 +99,30 @@ WIDE_CASES = [
     (_w("c-bf16-d128-k160-1500", 1, 2, 1500, 128, 160, 64, "bf16", 0), 0),
     (_w("c-bf16-d64-k200-1111-padded", 2, 1, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0),
     (_w("c-bf16-d64-k128-1300-nbr1", 1, 1, 1300, 64, 128, 64, "bf16", 0), 1),
-    (_w("c-bf16-d128-leaf1025", 1, 1, 2049, 128, 128, 64, "bf16", 1100), 0),
-    (_w("c-bf16-d64-leaf1110", 1, 2, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0),
-    (_w("c-bf16-d128-leaf1152-k64", 1, 1, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0),
+    (_w("c-bf16-d128-leaf1025", 1, 32, 2049, 128, 128, 64, "bf16", 1100), 0),
+    (_w("c-bf16-d64-leaf1110", 3, 20, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0),
+    (_w("c-bf16-d128-leaf1152-k64", 2, 29, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0),
 ]
 
 
 @pytest.mark.parametrize("w,nbr", WIDE_CASES, ids=[w.name for w, _ in WIDE_CASES])
 def test_ragged_causal_wide_tiles(w, nbr):
-    _check(w, neighbors=nbr)
+    _check(w, neighbors=nbr, heads={(0, 0), (w.B - 1, w.H - 1)})
+
+
+# the leaf's dQ in 128-query tiles (from 256 tiles; leaves under 1024 from 2048
+# tiles): W' of 64 columns (r > 128), leaves of one query past a tile, a leaf
+# whose last tiles hold no token, d_h 64 and 128
+WIDE_LEAF_BWD_CASES = [
+    _w("c-bf16-d128-r256-leaf1153", 1, 26, 1153, 128, 128, 256, "bf16", 1200),
+    _w("c-bf16-d64-r192-leaf1024", 2, 16, 2047, 64, 64, 192, "bf16", 1030, recipe="clustered"),
+    _w("c-bf16-d128-r16-leaf513", 3, 22, 4099, 128, 64, 16, "bf16", 520),
+]
+
+
+@pytest.mark.parametrize("w", WIDE_LEAF_BWD_CASES, ids=[w.name for w in WIDE_LEAF_BWD_CASES])
+def test_ragged_causal_wide_leaf_backward(w):
+    _check(w, heads={(0, 0), (w.B - 1, w.H - 1)})
 
 
 def test_ragged_causal_with_neighbours():
