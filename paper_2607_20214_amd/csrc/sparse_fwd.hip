@@ -657,7 +657,12 @@ __global__ __launch_bounds__(kThreads, 2) void sparse_fwd_wide_kernel(Args a)
 
 // where the wide form is the faster one (see there)
 bool wide_levels(const Shape& s) { return s.bf16 && s.k >= 128; }
-bool wide_leaf(const Shape& s) { return s.bf16 && s.n_leaf >= 1024; }
+// (the leaf also needs two workgroups a compute unit: 512 tiles 179 -> 170 us,
+// 256 tiles 97 -> 103, 128 tiles 56 -> 71)
+bool wide_leaf(const Shape& s)
+{
+    return s.bf16 && s.n_leaf >= 1024 && (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H >= 512;
+}
 
 template <class T, int D>
 hipError_t launch_t(const Shape& s, const Args& a, hipStream_t st, int parts)
