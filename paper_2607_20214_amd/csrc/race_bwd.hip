@@ -2,15 +2,15 @@
 //
 // With dNum_i = g_lr dO_i / (Den_i + eps) and dDen_i (row scalars of the
 // backward preprocess), and V~_j = [V_j, 1], dN~_i = [dNum_i, dDen_i]:
-//   dphi(q_i) = (1/L) sum_{j <= i} <dN~_i, V~_j> phi(k_j)          (kernel LB1, forward time)
-//   dphi(k_j) = (1/L) sum_{i >= j} <dN~_i, V~_j> phi(q_i)          (kernel LB2, reverse time)
-//   dV_j      = (1/L) sum_{i >= j} <phi(q_i), phi(k_j)> dNum_i      (kernel LB3, reverse time)
+//   dphi(q_i) = (1/L) sum_{j <= i} <dN~_i, V~_j> phi(k_j)          (pass LB1, forward time)
+//   dphi(k_j) = (1/L) sum_{i >= j} <dN~_i, V~_j> phi(q_i)          (pass LB2, reverse time)
+//   dV_j      = (1/L) sum_{i >= j} <phi(q_i), phi(k_j)> dNum_i      (pass LB3, reverse time)
 // (non-causal: all i, j).  Each is a linear-attention pass over 64-token
 // chunks with a running state: LB1 reads S = sum phi(k) V', A = sum phi(k)
 // (the forward's segment prefix states); LB2 and LB3 read the suffix states
 // dS = (1/L) sum phi(q) dNum', dA = (1/L) sum phi(q) dDen.  LB1 and LB2
 // contract their state over d, so each wave owns a quarter of the features;
-// LB3 contracts over the features, so each wave owns a quarter of d.
+// LB3 contracts over the features, so each wave owns a share of d.
 // dphi is chained through phi = prod sigmoid(2 beta v t), t = tanh(W x) to
 // du, the gradient of the projections u = W x.  LB1 and LB2 store du (storage
 // dtype, [BH][N][wk], wk = 4L padded to 32) and the sparse backward forms

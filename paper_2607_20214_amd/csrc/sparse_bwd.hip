@@ -10,8 +10,10 @@
 // where Delta_i = <dO_s,i, O_s,i> - dm_i m_i (1 - m_i)(d_s,i + eps)/d_s,i also
 // carries the gradient through the denominator-aware multiplier m.
 //
-// Two passes, no atomics: a query-centric pass (dQ; one workgroup per 64
-// queries, keys streamed through LDS) and a key-centric pass (dK, dV; one
+// No atomics.  Sorted blocks of 64 or 128 keys (256 at the levels) run whole,
+// one workgroup a block (sparse_bwd_block_kernel).  The causal leaves, other
+// block sizes and neighbouring blocks take two passes: a query-centric pass (dQ; one workgroup per 64
+// queries, or 128 in long leaves, keys streamed through LDS) and a key-centric pass (dK, dV; one
 // workgroup per 64 keys, queries streamed through LDS).  Both have the three
 // modes of the forward (non-causal blocks, causal levels, causal leaf).  The
 // level passes write per-level partials by natural token index in the

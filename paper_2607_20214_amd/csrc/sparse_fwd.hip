@@ -1,6 +1,7 @@
 // sparse_fwd.hip -- sortLSH sparse branch forward and the fusion epilogue.
 //
-// One workgroup = 4 waves = 64 queries (16 per wave); keys stream through
+// One workgroup = 4 waves = 64 queries (16 per wave; the wide form below: 128
+// queries, 32 per wave); keys stream through
 // LDS in tiles of 64 rows gathered by the sorted index lists (tile.hpp: K
 // and V row-major, chunk-swizzled; V^T operands come from transposed LDS
 // reads).  The rows of the next tile are loaded into registers while the
