@@ -61,7 +61,7 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
     C = 64
     u = {}
     u["project"] = (bh * (2 * N * D * s + 2 * N), bh * N * 2 * 2 * D * gs, ["project"])
-    u["sort"] = (bh * (4 * N * Lv if w.causal else 8 * N), 0, ["sort"])
+    u["sort"] = (bh * (4 * N * Lv if w.causal else 8 * N), 0, ["sort", "sort_scan"])
     lr_tok_bytes = 3 * D * s + 4 * D + 4
     lr_tok_flops = 4 * r * (D + 1) + 4 * D * L * g + (2 * C * (r + D + 1) if w.causal else 0)
     u["lowrank_fwd"] = (bh * N * lr_tok_bytes, bh * N * lr_tok_flops,
@@ -145,6 +145,7 @@ def source_digest(names) -> str:
 
 KERNEL_SOURCES = {
     "project": ["select.hip", "common.hpp"], "sort": ["select.hip", "causal.hpp"],
+    "sort_scan": ["select.hip", "causal.hpp", "race_common.hpp"],
     "race_state_fwd": ["race_fwd.hip", "race_common.hpp", "common.hpp"],
     "race_state_bwd": ["race_fwd.hip", "race_common.hpp", "common.hpp"],
     "race_scan_fwd": ["race_fwd.hip"], "race_scan_bwd": ["race_fwd.hip"],

@@ -230,16 +230,12 @@ hipError_t clear_error() { return hipGetLastError(); }
 const StreamOps kHipStreamOps = {record_event, hipStreamWaitEvent, hipStreamSynchronize, clear_error};
 
 // first(side) on the device's side stream beside second(main) (fork_join.hpp);
-// without a side stream, or when a fork does not pay, both run on `main` in
-// order.
-template <class A, class B>
-hipError_t fork_join(bool pays, hipStream_t main, A first, B second)
+// without a side stream, or when a fork does not pay, in_order(main) instead.
+template <class A, class B, class C>
+hipError_t fork_join(bool pays, hipStream_t main, A first, B second, C in_order)
 {
     Side* sd = side_stream();        // created by the first call whatever its sizes, so a later call can be captured
-    if (!sd || !pays) {
-        hipError_t e = first(main);
-        return e != hipSuccess ? e : second(main);
-    }
+    if (!sd || !pays) return in_order(main);
     std::lock_guard<std::mutex> lk(sd->mu);
     return elsaa::fork_join(kHipStreamOps, main, sd->stream, sd->fork, sd->join, first, second);
 }
@@ -381,7 +377,7 @@ int elsaa_select(const elsaa_config* cfg, const void* Q, const void* K, const fl
     hipError_t e;
     if ((e = launch_project(s, Q, K, W_sort, nullptr, kq, kk, nullptr, nullptr, stream)) != hipSuccess)
         return hip_fail(e, "hash");
-    if ((e = launch_sort(s, kq, kk, perm_q, perm_k, stream)) != hipSuccess) return hip_fail(e, "sort");
+    if ((e = launch_sort(s, SortJob{kq, kk, perm_q, perm_k}, ScanJob(), stream)) != hipSuccess) return hip_fail(e, "sort");
     return ELSAA_OK;
 }
 
@@ -406,7 +402,7 @@ int elsaa_select_noalloc(const elsaa_config* cfg, const void* Q, const void* K, 
     // every key the sort reads is written by the hash pass first: nothing to clear
     if ((e = launch_project(s, Q, K, W_sort, nullptr, kq, kk, nullptr, nullptr, stream)) != hipSuccess)
         return hip_fail(e, "hash");
-    if ((e = launch_sort(s, kq, kk, perm_q, perm_k, stream)) != hipSuccess) return hip_fail(e, "sort");
+    if ((e = launch_sort(s, SortJob{kq, kk, perm_q, perm_k}, ScanJob(), stream)) != hipSuccess) return hip_fail(e, "sort");
     return ELSAA_OK;
 }
 
@@ -453,9 +449,14 @@ int elsaa_fwd(const elsaa_config* cfg, const void* Q, const void* K, const void*
     // 65 -> 54 in order; a longest list of 16 steps gains by the fork (16384
     // x 8 heads 79 us against 83, causal 7919 x 16 heads 202 against 209),
     // one of 8 steps is equal (causal 4096 x 8 heads, 80 us).
+    // There the sort shares a launch with the RACE scan.
+    const SortJob sort = {kq, kk, pq, pk};
+    auto race = [&](const SortJob* beside_scan, hipStream_t st) {
+        return launch_race_fwd(s, uq, uk, V, at<float>(saved, SL.race_states), o_lr, d_lr, beside_scan, st);
+    };
     e = fork_join(
-        sort_steps(s) >= 12, stream, [&](hipStream_t st) { return launch_sort(s, kq, kk, pq, pk, st); },
-        [&](hipStream_t st) { return launch_race_fwd(s, uq, uk, V, at<float>(saved, SL.race_states), o_lr, d_lr, st); });
+        sort_steps(s) >= 12, stream, [&](hipStream_t st) { return launch_sort(s, sort, ScanJob(), st); },
+        [&](hipStream_t st) { return race(nullptr, st); }, [&](hipStream_t st) { return race(&sort, st); });
     if (e == hipSuccess)
         e = launch_sparse_fwd(s, Q, K, V, pq, pk, gates, lambda_rows, o_lr, d_lr, part_o, part_lse, O, lse, m, o_s,
                               stream, kSparseLevels);

@@ -58,8 +58,19 @@ private:
 hipError_t launch_project(const Shape& s, const void* Q, const void* K, const float* W_sort,
                           const float* W_race, uint8_t* keyq, uint8_t* keyk, float* Uq, float* Uk,
                           hipStream_t st);
-hipError_t launch_sort(const Shape& s, const uint8_t* keyq, const uint8_t* keyk, int32_t* perm_q,
-                       int32_t* perm_k, hipStream_t st);
+struct SortJob {
+    const uint8_t* keyq;
+    const uint8_t* keyk;
+    int32_t* perm_q;
+    int32_t* perm_k;
+};
+// RACE segment states for the scan (race_common.hpp) that may share the sort's launch
+struct ScanJob {
+    float* states = nullptr;                // none
+    int nseg = 0, per = 0, mode = 0;
+};
+int sort_tasks(const Shape& s);             // lists per (b, h); 0: nothing to sort
+hipError_t launch_sort(const Shape& s, const SortJob& job, const ScanJob& scan, hipStream_t st);
 int sort_steps(const Shape& s);             // 64-key steps of a wave in the longest list (about 0.8 us each)
 
 // RACE low-rank branch
@@ -69,8 +80,9 @@ size_t race_state_floats(const Shape& s);    // floats of one set of segment sta
 bool race_fwd_fits(const Shape& s);          // kernels' LDS fits for this dtype / d / r
 bool race_bwd_fits(const Shape& s);
 struct RowArgs;                              // bwd_rows.hpp
+// sort: lists to be sorted beside the scan (null: not here)
 hipError_t launch_race_fwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
-                           float* states, void* O_lr, float* d_lr, hipStream_t st);
+                           float* states, void* O_lr, float* d_lr, const SortJob* sort, hipStream_t st);
 size_t race_wt_bytes(const Shape& s);       // one of the W' hi / lo buffers
 int race_wk(const Shape& s);                // columns of W' and of a du row (4 L padded to 32)
 // The backward's row scalars (rows.rs and the gate and lambda gradients) and

@@ -313,5 +313,31 @@ __device__ __forceinline__ void chain_rule_t(f32x4 dphi, int qt, int tb, int L, 
     du[row][4 * tb + g] = T::store(tb < L ? v : 0.f);
 }
 
+// One element of the segment states (base: its address in segment 0, per
+// elements apart): mode 0: the total in every segment; 1: exclusive prefix; 2:
+// exclusive suffix.  The segments are walked in batches of independent loads.
+__device__ __forceinline__ void scan_states(float* base, int nseg, int per, int mode)
+{
+    constexpr int kBatch = 16;
+    float run = 0.f;
+    for (int s0 = 0; s0 < nseg; s0 += kBatch) {
+        float v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int s = mode == 2 ? nseg - 1 - (s0 + j) : s0 + j;
+            v[j] = (s0 + j < nseg) ? base[(size_t)s * per] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (s0 + j >= nseg) break;
+            const int s = mode == 2 ? nseg - 1 - (s0 + j) : s0 + j;
+            if (mode != 0) base[(size_t)s * per] = run;
+            run += v[j];
+        }
+    }
+    if (mode == 0)
+        for (int s = 0; s < nseg; ++s) base[(size_t)s * per] = run;
+}
+
 }  // namespace race
 }  // namespace elsaa

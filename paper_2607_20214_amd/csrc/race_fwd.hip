@@ -245,34 +245,10 @@ __global__ __launch_bounds__(kThreads, KIND == kStateRows && T::bytes == 2 ? 2 :
     }
 }
 
-// mode 0: total in every segment; 1: exclusive prefix; 2: exclusive suffix.
-// Each thread owns one element of the state and walks the segments in
-// batches of kBatch independent loads.
 __global__ __launch_bounds__(256) void race_scan_kernel(float* states, int nseg, int per, int mode)
 {
-    constexpr int kBatch = 16;
-    const size_t bh = blockIdx.y;
     const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= per) return;
-    float* base = states + bh * (size_t)nseg * per + e;
-    float run = 0.f;
-    for (int s0 = 0; s0 < nseg; s0 += kBatch) {
-        float v[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int s = mode == 2 ? nseg - 1 - (s0 + j) : s0 + j;
-            v[j] = (s0 + j < nseg) ? base[(size_t)s * per] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (s0 + j >= nseg) break;
-            const int s = mode == 2 ? nseg - 1 - (s0 + j) : s0 + j;
-            if (mode != 0) base[(size_t)s * per] = run;
-            run += v[j];
-        }
-    }
-    if (mode == 0)
-        for (int s = 0; s < nseg; ++s) base[(size_t)s * per] = run;
+    if (e < per) scan_states(states + blockIdx.y * (size_t)nseg * per + e, nseg, per, mode);
 }
 
 struct OutArgs {
@@ -509,7 +485,7 @@ bool fused_rows(const Shape& s)
 }
 
 template <class T, int D, int RP>
-hipError_t launch_states_t(const Shape& s, const StateArgs& a, bool bwd, hipStream_t st)
+hipError_t launch_states_t(const Shape& s, const StateArgs& a, bool bwd, const SortJob* sort, hipStream_t st)
 {
     if constexpr (!fits<T, D, RP>()) {
         return hipErrorInvalidConfiguration;
@@ -526,6 +502,7 @@ hipError_t launch_states_t(const Shape& s, const StateArgs& a, bool bwd, hipStre
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int per = RP * D + RP, scan_mode = !s.causal ? 0 : bwd ? 2 : 1;
+        if (sort && sort_tasks(s) > 0) return launch_sort(s, *sort, ScanJob{a.states, s.nseg, per, scan_mode}, st);
         ELSAA_LAUNCH(bwd ? "race_scan_bwd" : "race_scan_fwd", race_scan_kernel, dim3((per + 255) / 256, s.B * s.H), dim3(256), 0, st,
                            a.states, s.nseg, per, scan_mode);
         return hipGetLastError();
@@ -566,9 +543,9 @@ hipError_t dispatch(const Shape& s, A&&... args)
 
 template <class T, int D, int RP>
 struct StatesFn {
-    static hipError_t run(const Shape& s, const StateArgs& a, bool bwd, hipStream_t st)
+    static hipError_t run(const Shape& s, const StateArgs& a, bool bwd, const SortJob* sort, hipStream_t st)
     {
-        return launch_states_t<T, D, RP>(s, a, bwd, st);
+        return launch_states_t<T, D, RP>(s, a, bwd, sort, st);
     }
 };
 
@@ -605,17 +582,17 @@ hipError_t launch_race_bwd_states(const Shape& s, const float* Uq, const void* d
     a.H = s.H; a.N = s.N; a.L = s.L; a.seg_len = s.seg_len; a.nseg = s.nseg;
     a.two_beta = 2.f * s.beta; a.mul = 1.f / (float)s.L;
     a.rows = rows;
-    return dispatch<StatesFn>(s, a, true, st);
+    return dispatch<StatesFn>(s, a, true, (const SortJob*)nullptr, st);
 }
 
 hipError_t launch_race_fwd(const Shape& s, const float* Uq, const float* Uk, const void* V,
-                           float* states, void* O_lr, float* d_lr, hipStream_t st)
+                           float* states, void* O_lr, float* d_lr, const SortJob* sort, hipStream_t st)
 {
     StateArgs sa = {};
     sa.U = Uk; sa.Val = V; sa.states = states;
     sa.H = s.H; sa.N = s.N; sa.L = s.L; sa.seg_len = s.seg_len; sa.nseg = s.nseg;
     sa.two_beta = 2.f * s.beta; sa.mul = 1.f;
-    hipError_t e = dispatch<StatesFn>(s, sa, false, st);
+    hipError_t e = dispatch<StatesFn>(s, sa, false, sort, st);
     if (e != hipSuccess) return e;
     OutArgs a;
     a.Uq = Uq; a.Uk = Uk; a.V = V; a.states = states;

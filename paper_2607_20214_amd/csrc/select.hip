@@ -239,7 +239,8 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_kernel(const uint8_t* __re
                                                              const uint8_t* __restrict__ keyk,
                                                              int32_t* __restrict__ perm_q,
                                                              int32_t* __restrict__ perm_k, int H,
-                                                             int N, int causal, LevelTiles lt, int bits)
+                                                             int N, int causal, LevelTiles lt, int bits,
+                                                             int tasks, ScanJob scan)
 {
     constexpr int kSortWaves = WAVES, kSortThreads = WAVES * kWave;
     __shared__ int hist[kSortWaves][256];   // per part; then its running output positions
@@ -248,6 +249,11 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_kernel(const uint8_t* __re
     const int task = blockIdx.x;
     const int nb = 1 << bits;
     const size_t bh = (size_t)b * H + h;
+    if (task >= tasks) {
+        const int e = (task - tasks) * kSortThreads + threadIdx.x;
+        if (e < scan.per) race::scan_states(scan.states + bh * (size_t)scan.nseg * scan.per + e, scan.nseg, scan.per, scan.mode);
+        return;
+    }
 
     int start, len, nreal, is_k;             // list entries [0, len): tokens start + i for i < nreal
     size_t out_off;
@@ -357,18 +363,22 @@ int sort_steps(const Shape& s)
     return (longest + sort_waves(s) * kWave - 1) / (sort_waves(s) * kWave);
 }
 
-hipError_t launch_sort(const Shape& s, const uint8_t* keyq, const uint8_t* keyk, int32_t* perm_q,
-                       int32_t* perm_k, hipStream_t st)
+int sort_tasks(const Shape& s) { return s.causal ? (1 << (s.Lv + 1)) - 2 : 2; }
+
+hipError_t launch_sort(const Shape& s, const SortJob& job, const ScanJob& scan, hipStream_t st)
 {
-    const int tasks = s.causal ? (1 << (s.Lv + 1)) - 2 : 2;
+    const int tasks = sort_tasks(s), threads = sort_waves(s) * kWave;
     if (tasks <= 0) return hipSuccess;
-    dim3 grid(tasks, s.H, s.B);
+    // the scan's workgroups follow the lists': both are short chains of
+    // dependent steps that leave the device mostly idle (9 + 8 us apart; 2 x
+    // 8 heads x 4096 step 116 -> 112 us, 512-token forward 27 -> 26)
+    dim3 grid(tasks + (scan.states ? (scan.per + threads - 1) / threads : 0), s.H, s.B);
     // non-causal: two long lists per (b, h), so few workgroups: sixteen waves
     // each (30720 tokens 121 -> 36 us, 4096: 13 -> 5); causal levels have
     // 2^(l + 1) lists, most of them short, and fill the device with four
 #define ELSAA_SORT(W_)                                                                                       \
-    ELSAA_LAUNCH("sort", sort_kernel<W_>, grid, dim3(W_ * kWave), 0, st, keyq, keyk, perm_q, perm_k, s.H, s.N, \
-                 s.causal, s.lt, s.sort_bits)
+    ELSAA_LAUNCH(scan.states ? "sort_scan" : "sort", sort_kernel<W_>, grid, dim3(W_ * kWave), 0, st, job.keyq, \
+                 job.keyk, job.perm_q, job.perm_k, s.H, s.N, s.causal, s.lt, s.sort_bits, tasks, scan)
     if (sort_waves(s) == 4) ELSAA_SORT(4);
     else ELSAA_SORT(16);
 #undef ELSAA_SORT
