@@ -1450,10 +1450,14 @@ void launch_level_blocks(const Shape& s, const BArgs& a, hipStream_t st)
 // shorter ones from 448 only where there are many (4096 tiles, leaves of 500:
 // 2199 -> 2166, of 1000: 2271 -> 2207; 256 tiles, leaves of 512: 137 -> 145).
 // Leaves of 256 gain nothing (853 both) and of 174 lose (639 -> 647): half of
-// a 128-query tile is the diagonal.
+// a 128-query tile is the diagonal.  At d_h 64 a tile's loads and epilogue
+// weigh more and the line is lower (leaves of 200: 392 -> 385, of 250, 256
+// tiles: 66 -> 61, of 256, 512 tiles: 94 -> 92; 174: 321 -> 322, 131: 267 ->
+// 270; 64 tiles: 44 -> 46).
 bool wide_leaf_dq(const Shape& s)
 {
     const long tiles = (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H;
+    if (s.D == 64) return s.bf16 && s.n_leaf >= 192 && tiles >= 256;
     return s.bf16 && (s.n_leaf >= 1024 ? tiles >= 256 : s.n_leaf >= 448 && tiles >= 2048);
 }
 

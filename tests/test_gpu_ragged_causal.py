@@ -110,12 +110,13 @@ def test_ragged_causal_wide_tiles(w, nbr):
     _check(w, neighbors=nbr, heads={(0, 0), (w.B - 1, w.H - 1)})
 
 
-# the leaf's dQ in 128-query tiles (from 256 tiles; leaves under 1024 from 2048
-# tiles): W' of 64 columns (r > 128), leaves of one query past a tile, a leaf
+# the leaf's dQ in 128-query tiles (d_h 64: leaves from 192 and 256 tiles; d_h
+# 128: from 1024 and 256 tiles, or 448 and 2048 tiles): W' of 64 columns (r > 128), leaves of one query past a tile, a leaf
 # whose last tiles hold no token, d_h 64 and 128
 WIDE_LEAF_BWD_CASES = [
     _w("c-bf16-d128-r256-leaf1153", 1, 26, 1153, 128, 128, 256, "bf16", 1200),
     _w("c-bf16-d64-r192-leaf1024", 2, 16, 2047, 64, 64, 192, "bf16", 1030, recipe="clustered"),
+    _w("c-bf16-d64-r32-leaf193", 2, 16, 772, 64, 64, 32, "bf16", 200, recipe="clustered"),
     _w("c-bf16-d128-r16-leaf513", 3, 22, 4099, 128, 64, 16, "bf16", 520),
 ]
 
