@@ -154,7 +154,7 @@ KERNEL_SOURCES = {
     "race_dv": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
     "race_rows_bwd": ["race_fwd.hip", "race_common.hpp", "bwd_rows.hpp", "common.hpp"],
     "bwd_rows": ["bwd_rows.hip", "bwd_rows.hpp", "common.hpp"],
-    "gemm": ["gemm.hip", "common.hpp"], "gemm_reduce": ["gemm.hip"],
+    "gemm": ["gemm.hip", "gemm_index.hpp", "common.hpp"], "gemm_reduce": ["gemm.hip", "gemm_index.hpp"],
     "token_rules_fwd": ["token_rules.hip", "tile.hpp", "common.hpp"],
     "token_rules_bwd": ["token_rules.hip", "tile.hpp", "common.hpp"],
     "token_rules_reduce": ["token_rules.hip"],

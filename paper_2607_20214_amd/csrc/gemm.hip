@@ -6,10 +6,11 @@
 // registers; see the large-tile section) and gemm_kernel (workgroup tile
 // 128 x 128 x 64, four waves in a 2 x 2 grid, each wave a 64 x 64 block of
 // 4 x 4 accumulators of v_mfma_f32_16x16x32_bf16); plan_of chooses.  Both
-// take any M, N, K (multiples of 8): rows and columns past the matrix repeat
-// its last ones and are not stored, and a K range that is no multiple of 64
-// starts with its short K-tile, filled up with zeros, so the loop runs on
-// whole K-tiles without masks.  Both compute C^T tiles (the B operand feeds
+// take any M, N, K (multiples of 8; gemm_big_kernel K from 64): rows and
+// columns past the matrix repeat its last ones and are not stored, and a K
+// range that is no multiple of 64 starts with its short K-tile, filled up
+// with zeros, so the loop runs on whole K-tiles without masks
+// (gemm_index.hpp: addresses and plan).  Both compute C^T tiles (the B operand feeds
 // the MFMA's first input) so that every lane ends with four consecutive
 // columns of one C row, which makes the stores 8- or 16-byte vectors.
 //
@@ -24,40 +25,25 @@
 // workgroups; float32 partials go to the workspace and a second kernel sums
 // them in split order.  Workgroup ids are remapped so that each of the
 // eight XCDs (own L2) works on a contiguous group of tiles.
-#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
 #include "common.hpp"
 #include "elsaa.h"
+#include "gemm_index.hpp"
 #include "internal.hpp"
 
 namespace elsaa {
 
+using namespace gemm;
+
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 64;
-constexpr int kThreads = 256;
 constexpr int kLdD = BK + 8;      // row stride of a tile stored [rows][k]
 constexpr int kLdT = BM + 16;     // row stride of a tile stored [k][rows]
 constexpr int kTileElems = 128 * kLdD;
 static_assert(128 * kLdD == 64 * kLdT, "both tile orientations use the same LDS size");
 constexpr int kGroupM = 8;        // M tiles per launch-order group
-
-// One stored matrix: plain row-major (heads == 0) or head-major.
-struct Mat {
-    void* p;
-    int64_t ld;
-    int heads, seq, dh_shift;
-};
-
-__device__ __forceinline__ int64_t mat_offset(const Mat& m, int r, int c)
-{
-    if (m.heads == 0) return (int64_t)r * m.ld + c;
-    const int b = r / m.seq, n = r - b * m.seq;
-    const int h = c >> m.dh_shift, e = c & ((1 << m.dh_shift) - 1);
-    return ((((int64_t)b * m.heads + h) * m.seq + n) << m.dh_shift) + e;
-}
 
 // 16 bytes at the uniform address q plus a per-lane byte offset < 2^31.
 __device__ __forceinline__ uint4 ldb16(const char* q, uint32_t off)
@@ -66,20 +52,6 @@ __device__ __forceinline__ uint4 ldb16(const char* q, uint32_t off)
     const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(q), (short)0, 0x7fffffff, 0x00027000);
     const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
     return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-// mat_offset as a row part plus a column part.
-__device__ __forceinline__ int64_t row_part(const Mat& m, int r)
-{
-    if (m.heads == 0) return (int64_t)r * m.ld;
-    const int b = r / m.seq;
-    return ((int64_t)r + (int64_t)b * (m.heads - 1) * m.seq) << m.dh_shift;
-}
-__device__ __forceinline__ int64_t row_stride(const Mat& m) { return m.heads == 0 ? m.ld : ((int64_t)1 << m.dh_shift); }
-__device__ __forceinline__ int64_t col_part(const Mat& m, int c)
-{
-    if (m.heads == 0) return c;
-    return (((int64_t)(c >> m.dh_shift) * m.seq) << m.dh_shift) + (c & ((1 << m.dh_shift) - 1));
 }
 
 struct GArgs {
@@ -108,40 +80,24 @@ __device__ __forceinline__ void tile_of(const GArgs& a, int& sp, int& tm, int& t
     tn = r / gm;
 }
 
-// Global loads of one operand's K-tiles, rows (or columns) [x0, x0 + XT).
-// KMAJOR: the operand is stored [k][x] (x = m or n contiguous), thread tx
-// loads k-rows tx / TPR + RPC c at columns x0 + 8 (tx % TPR); else [x][k],
-// rows x0 + tx / 8 + 32 c at columns k0 + 8 (tx % 8).  x positions past xlim
-// repeat the last ones.  The byte offsets from the tile's first element are
-// formed once per thread (32 bits; an address in the K loop is then a scalar
-// base plus one register, no vector instruction), which needs a K-tile's
-// k-rows in one sequence (KMAJOR) or its columns in one head: fast_operand.
+// Global loads of one operand's K-tiles (StreamIndex).  An address in the K
+// loop is a scalar base plus one register, no vector instruction.
 template <bool KMAJOR, int XT>
 struct Stream {
-    static constexpr int C = XT * BK / 8 / kThreads;                    // 16-byte chunks per thread
-    static constexpr int TPR = KMAJOR ? XT / 8 : 8, RPC = kThreads / TPR;
+    using Ix = StreamIndex<KMAJOR, XT>;
+    static constexpr int C = Ix::C;
+    Ix ix;
     const char* p;       // element (x0, 0) or (0, x0)
-    uint32_t off[C];
     __device__ __forceinline__ void init(const Mat& m, int x0, int xlim)
     {
-        const int r = threadIdx.x / TPR, c8 = 8 * (threadIdx.x % TPR);
-        p = (const char*)((const uint16_t*)m.p + (KMAJOR ? col_part(m, x0) : row_part(m, x0)));
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            if (KMAJOR)
-                off[c] = (uint32_t)(((r + RPC * c) * row_stride(m) + col_part(m, min(x0 + c8, xlim - 8)) - col_part(m, x0)) * 2);
-            else
-                off[c] = (uint32_t)((row_part(m, min(x0 + r + RPC * c, xlim - 1)) - row_part(m, x0) + c8) * 2);
-        }
+        ix.init(m, x0, xlim, threadIdx.x);
+        p = (const char*)m.p + ix.base;
     }
     // first element of the K-tile at k0 (uniform)
-    __device__ __forceinline__ const char* tile(const Mat& m, int k0) const
-    {
-        return p + 2 * (KMAJOR ? row_part(m, k0) : col_part(m, k0));
-    }
+    __device__ __forceinline__ const char* tile(const Mat& m, int k0) const { return p + Ix::tile(m, k0); }
     // (as a buffer load: scalar base, one offset register; written as pointer
     // arithmetic the compiler keeps 64-bit offsets and adds in the loop)
-    __device__ __forceinline__ uint4 chunk(const char* q, int c) const { return ldb16(q, off[c]); }
+    __device__ __forceinline__ uint4 chunk(const char* q, int c) const { return ldb16(q, ix.off[c]); }
     __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[C]) const
     {
         const char* q = tile(m, k0);
@@ -153,10 +109,7 @@ struct Stream {
     {
         const char* q = tile(m, k0);
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int k = KMAJOR ? (int)threadIdx.x / TPR + RPC * c : 8 * ((int)threadIdx.x % TPR);
-            r[c] = k < kn ? chunk(q, c) : make_uint4(0, 0, 0, 0);
-        }
+        for (int c = 0; c < C; ++c) r[c] = Ix::k_in_tile(c, threadIdx.x) < kn ? chunk(q, c) : make_uint4(0, 0, 0, 0);
     }
 };
 
@@ -217,9 +170,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
     int sp, tm, tn;
     tile_of(a, sp, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
-    const int kb = sp * a.kper, ke = min(a.K, kb + a.kper);
-    const int nkt = (ke - kb + BK - 1) / BK;
-    const int kfirst = ke - kb - (nkt - 1) * BK;          // the first K-tile's values of k
+    const KTiles kt(a.K, a.kper, sp);
+    const int nkt = kt.n;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w & 1, wn = w >> 1;
     const int g = lane >> 4, col = lane & 15;
@@ -237,15 +189,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
     // LDS buffer t & 1 holds K-tile t, register set (t + 1) & 1 K-tile t + 1,
     // and iteration t requests K-tile t + 2: a load has two iterations to
     // arrive, which is what bounds short products (few workgroups, each
-    // K-tile's 32 products a fifth of a memory round trip).  Tile indices
-    // past the end repeat the last tile (never read).
+    // K-tile's 32 products a fifth of a memory round trip).
     uint4 ra[2][4], rb[2][4];
-    auto k_of = [&](int t) { return kb + (t > 0 ? kfirst + (min(t, nkt - 1) - 1) * BK : 0); };
-    gA.load_short(a.A, kb, kfirst, ra[0]);
-    gB.load_short(a.B, kb, kfirst, rb[0]);
+    gA.load_short(a.A, kt.kb, kt.first, ra[0]);
+    gB.load_short(a.B, kt.kb, kt.first, rb[0]);
     if (nkt > 1) {
-        gA.load(a.A, k_of(1), ra[1]);
-        gB.load(a.B, k_of(1), rb[1]);
+        gA.load(a.A, kt.whole(1), ra[1]);
+        gB.load(a.B, kt.whole(1), rb[1]);
     }
     store_tile<TA>(sa[0], ra[0]);
     store_tile<BKN>(sb[0], rb[0]);
@@ -254,8 +204,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
     auto step = [&](int t, auto parity) {
         constexpr int P = decltype(parity)::value;        // t & 1
         if (t + 2 < nkt) {
-            gA.load(a.A, k_of(t + 2), ra[P]);
-            gB.load(a.B, k_of(t + 2), rb[P]);
+            gA.load(a.A, kt.whole(t + 2), ra[P]);
+            gB.load(a.B, kt.whole(t + 2), rb[P]);
         }
         const uint16_t* A_ = sa[P];
         const uint16_t* B_ = sb[P];
@@ -315,7 +265,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GArgs a)
 // matrix cores busy long enough to cover the next tile's global loads.
 namespace big {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = kBig, BN = kBig;
 constexpr int kLdD = BK + 8;       // [rows][k] row stride
 constexpr int kLdT = BM + 16;      // [k][rows] row stride
 constexpr int kTile = BM * kLdD;   // elements of one operand tile (either orientation)
@@ -375,9 +325,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     int sp, tm, tn;
     tile_of(a, sp, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
-    const int kb = sp * a.kper, ke = min(a.K, kb + a.kper);
-    const int nkt = (ke - kb + BK - 1) / BK;
-    const int kfirst = ke - kb - (nkt - 1) * BK;          // the first K-tile's values of k
+    const KTiles kt(a.K, a.kper, sp);
+    const int nkt = kt.n;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w & 1, wn = w >> 1;
     const int g = lane >> 4, col = lane & 15;
@@ -392,7 +341,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     Stream<BKN, BN> gB;
     gA.init(a.A, m0, a.M);
     gB.init(a.B, n0, a.N);
-    auto k_of = [&](int t) { return kb + (t > 0 ? kfirst + (min(t, nkt - 1) - 1) * BK : 0); };
     // Pipeline: LDS buffer t & 1 holds K-tile t, the registers K-tile t + 1.
     // The first half of an iteration runs k-step 0 of tile t (fragments
     // already read) in eight groups of eight operations; before group i it
@@ -402,19 +350,19 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
     // the same way, reading k-step 0 of tile t + 1.  Spreading the loads and
     // stores keeps the in-order wave from stalling on a burst of memory
     // instructions while the matrix cores idle, and each load has a whole
-    // iteration to arrive.  Tile indices past the end are clamped to the
-    // last tile (the redundant loads and stores are never read), so the
+    // iteration to arrive.  Past the end the loads repeat the range's last 64
+    // values of k (KTiles::whole; what they bring is never read), so the
     // groups carry no branches.
     uint4 ra[kChunks], rb[kChunks];
-    gA.load_short(a.A, kb, kfirst, ra);
-    gB.load_short(a.B, kb, kfirst, rb);
+    gA.load_short(a.A, kt.kb, kt.first, ra);
+    gB.load_short(a.B, kt.kb, kt.first, rb);
     store<TA>(sa[0], ra);
     store<BKN>(sb[0], rb);
     {
         // same issue order as the loop's loads (A and B chunks alternating),
         // so the stores' waits count exactly across the loop entry
-        const char* qa = gA.tile(a.A, k_of(min(1, nkt - 1)));
-        const char* qb = gB.tile(a.B, k_of(min(1, nkt - 1)));
+        const char* qa = gA.tile(a.A, kt.whole(1));
+        const char* qb = gB.tile(a.B, kt.whole(1));
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) {
             ra[i] = gA.chunk(qa, i);
@@ -434,7 +382,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_big_kernel(GArgs a)
         const uint16_t* B_ = sb[t & 1];
         uint16_t* An = sa[(t + 1) & 1];
         uint16_t* Bn = sb[(t + 1) & 1];
-        const int k2 = k_of(min(t + 2, nkt - 1));
+        const int k2 = kt.whole(t + 2);
         const char* qa = gA.tile(a.A, k2);
         const char* qb = gB.tile(a.B, k2);
 #pragma unroll
@@ -544,82 +492,6 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* part, Mat
     } else {
         *(f32x4*)((float*)C.p + mat_offset(C, m, n)) = v;
     }
-}
-
-struct Plan {
-    bool big;                 // 256 x 256 tiles (gemm_big_kernel)
-    bool any;                 // 128 x 128 tiles with StreamAny
-    int tiles_m, tiles_n, splits, kper;
-    size_t ws_bytes;
-};
-
-// Whether Stream can read an operand stored as rows x cols: `kmajor` ones
-// need every K-tile's 64 rows in one sequence (a single sequence, or whole
-// 64-row pieces of several), the others its 64 columns in one head; offsets
-// within a 256-row tile and a K-tile must fit 32 bits.
-bool fast_operand(bool kmajor, int rows, int cols, int64_t ld, int heads, int seq)
-{
-    const int64_t lim = (int64_t)1 << 31;
-    if (heads <= 0) return ld >= 0 && ld < lim / 512;
-    if (seq < 1 || cols / heads < 8) return false;                     // (refused by check_mat)
-    const int64_t dh = cols / heads, plane = (int64_t)seq * dh * 2;     // bytes of one head's rows
-    if (kmajor) return (seq >= rows || seq % BK == 0) && (256 / dh + 2) * plane < lim;
-    return dh % BK == 0 && (256 / (int64_t)seq + 2) * heads * plane < lim;
-}
-
-Plan plan_of(const elsaa_gemm_desc* d)
-{
-    Plan p;
-    const int ar = d->trans_a ? d->K : d->M, ac = d->trans_a ? d->M : d->K;
-    const int br = d->trans_b ? d->N : d->K, bc = d->trans_b ? d->K : d->N;
-    p.any = !fast_operand(d->trans_a != 0, ar, ac, d->lda, d->a_heads, d->seq) ||
-            !fast_operand(d->trans_b == 0, br, bc, d->ldb, d->b_heads, d->seq);
-    const int ktiles = (d->K + BK - 1) / BK;
-    // Estimated microseconds of a tile size and split count.  A round is the
-    // workgroups resident at once on 256 compute units (256 large tiles or
-    // 512 small ones); measured per K-tile 1.55 us for a round of large
-    // tiles (1040 - 1140 TFLOP/s at M 9000 .. 32768), 1.05 us for a full and
-    // 0.8 of that for an at most half full round of small ones (870 TFLOP/s
-    // at M 9000 x N 6144 x K 2048; one workgroup a compute unit at M 1000),
-    // 1.25 where both operands are read transposed (dW: 670 TFLOP/s), about
-    // 2.5 us for a round's first loads and last stores.  Splitting K costs
-    // a launch and the partials' way to memory and back (6 TB/s: mostly the
-    // memory-side cache).  The lines this
-    // draws: M 9000, d_model 2048: QKV 219 us large against 272 small, dX
-    // (288 large tiles, a second round of 32) 284 against 273; M 1000 small
-    // throughout (16 - 22 us against 28 - 34).
-    const double small_us = d->trans_a && !d->trans_b ? 1.25 : 1.05;
-    auto estimate = [&](bool big, int splits) {
-        const int t = big ? big::BM : BM, fill = big ? 256 : 512;
-        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
-        const int per = (ktiles + splits - 1) / splits;
-        const int wgs = tiles * ((ktiles + per - 1) / per), rem = wgs % fill;
-        const double rounds = wgs / fill + (rem == 0 ? 0. : !big && 2 * rem <= fill ? 0.8 : 1.);
-        const double reduce = splits > 1 ? 5. + 2e-6 * splits * (double)d->M * d->N * 4 / 6. : 0.;
-        return rounds * (per * (big ? 1.55 : small_us) + 2.5) + reduce;
-    };
-    double best = 0.;
-    for (int kind = 0; kind < (p.any ? 1 : 2); ++kind) {
-        const int t = kind ? big::BM : BM, fill = kind ? 256 : 512;
-        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
-        // at least 8 K-tiles per split, at most one round of workgroups
-        const int most = tiles < fill ? std::max(1, std::min(fill / tiles, ktiles / 8)) : 1;
-        for (int splits = 1; splits <= most; ++splits) {
-            const double e = estimate(kind == 1, splits);
-            if ((kind == 0 && splits == 1) || e < best) {
-                best = e;
-                p.big = kind == 1;
-                p.splits = splits;
-            }
-        }
-    }
-    const int t = p.big ? big::BM : BM;
-    p.tiles_m = (d->M + t - 1) / t;
-    p.tiles_n = (d->N + t - 1) / t;
-    p.kper = (ktiles + p.splits - 1) / p.splits * BK;
-    p.splits = (d->K + p.kper - 1) / p.kper;
-    p.ws_bytes = p.splits > 1 ? (size_t)p.splits * d->M * d->N * sizeof(float) : 0;
-    return p;
 }
 
 int log2_exact(int v)

@@ -1,0 +1,41 @@
+"""Host test of the GEMM's operand addresses (csrc/gemm_index.hpp), compiled
+with g++: every load of every planned kernel lies inside its operand, the
+ones past a range's end too, and those that matter are at their values."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM_INC = "/opt/rocm/include"
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM_INC),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("gemm_index") / "gemm_index_check")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wno-unknown-pragmas", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INC,
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2607_20214_amd", "csrc"),
+                    os.path.join(HERE, "host", "gemm_index_check.cpp"), "-o", out], check=True)
+    return out
+
+
+def test_every_load_lies_inside_its_operand(exe):
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and "ALL OK" in r.stdout, r.stdout + r.stderr
+
+
+def plan(exe, M, N, K, ta, tb, heads=(0, 0, 0), seq=0):
+    r = subprocess.run([exe, *map(str, (M, N, K, int(ta), int(tb), *heads, seq))], capture_output=True, text=True, check=True)
+    kind, splits, kper = r.stdout.split()
+    return kind, int(splits), int(kper)
+
+
+def test_walk_reaches_a_last_split_of_less_than_a_k_tile(exe):
+    """dW_O of a block of d_model 1024 over 13448 tokens: the large kernel's last split holds 8 values of k."""
+    kind, splits, kper = plan(exe, 1024, 1024, 13448, 1, 0, (16, 0, 0), 13448)
+    assert kind == "large" and 0 < 13448 - (splits - 1) * kper < 64

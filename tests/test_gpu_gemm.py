@@ -91,6 +91,26 @@ def test_gemm_large_tiles_ragged(shape, ta, tb, od):
     _check(got, oracle.gemm(A, B, ta, tb), od, f"{shape}")
 
 
+# a K below one K-tile, and a last split of 8 values of k (dW_O of 13448 tokens, A head-major)
+@pytest.mark.parametrize("ta,tb", itertools.product([0, 1], repeat=2))
+def test_gemm_many_tiles_short_k(ta, tb):
+    M, N, K = 4096, 4096, 40
+    A = W.random_matrix(47, 1, (K, M) if ta else (M, K))
+    B = W.random_matrix(47, 2, (N, K) if tb else (K, N))
+    got = E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    _check(got, oracle.gemm(A, B, ta, tb), torch.float32, f"K {K}")
+
+
+def test_gemm_short_last_split():
+    n, H, dh = 13448, 16, 64
+    O = W.random_matrix(48, 1, (1, H, n, dh))
+    dY = W.random_matrix(48, 2, (n, H * dh))
+    got = E.gemm(_t(O), _t(dY), trans_a=True, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    _check(got, oracle.gemm(oracle.heads_to_matrix(O), dY, True, False), torch.float32, "dW_O")
+
+
 # head-major operands whose sequences are not whole tiles: K-tiles and row
 # tiles that cross sequences (72, 200 tokens), 64-row pieces of several
 # sequences (192), one ragged sequence (1000)
