@@ -1468,14 +1468,18 @@ hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
     // whole-block kernel: b in {64, 128}; b = 128 only where its registers
     // fit without spilling (bf16 storage; non-causal blocks, which also form
     // the low-rank parts, only at d_h 64); causal b = 256 in bf16 as two
-    // 128-key halves per block.  Level lists that end in a short block or
-    // hold zero tokens take it too: its one pass reads each row once where
-    // the dQ and dK / dV pair reads them twice (16 heads, d_h 128, N = 11111,
-    // lists of 174 to 5556 entries: b = 128 backward 822 -> 709 us, of which
-    // the levels 328 -> 272; b = 256 838 -> 764; N = 30000, b = 256 2455 -> 2137)
+    // 128-key halves per block, unless the recursion is padded: the halves
+    // keep the first half's dQ as bf16, and padded lists (any odd length)
+    // keep the two passes' float32 sum over the 256 keys instead.  Level
+    // lists that end in a short block take the whole-block kernel too, and
+    // those of b = 64 and 128 that hold zero tokens: its one pass reads each
+    // row once where the dQ and dK / dV pair reads them twice (16 heads, d_h
+    // 128, N = 11111, lists of 174 to 5556 entries: b = 128 backward 822 ->
+    // 709 us, of which the levels 328 -> 272)
     const int bq = s.k;
     const bool fits128 = T::bytes == 2 && (s.causal || D == 64);
-    const bool whole = (bq == 64 || (bq == 128 && fits128) || (bq == 256 && s.causal && T::bytes == 2)) && s.neighbors == 0;
+    const bool halves256 = T::bytes == 2 && s.causal && !s.lt.padded;
+    const bool whole = (bq == 64 || (bq == 128 && fits128) || (bq == 256 && halves256)) && s.neighbors == 0;
     if (!s.causal) {
         if (whole) {
             if (!(parts & kSparseFinalQ)) return hipSuccess;

@@ -71,8 +71,9 @@ def test_ragged_causal(w):
 
 
 # the whole-block level backward on lists that end in a short block and on
-# padded ones (zero tokens in the query lists): every block size it takes,
-# halves shorter than a block, a last block of one entry, several zero tokens
+# (b = 64, 128) on padded ones (zero tokens in the query lists), and the two
+# passes that padded lists of b = 256 take: halves shorter than a block, a last
+# block of one entry, several zero tokens
 BLOCK_CASES = [
     _w("c-bf16-d128-k64-777-padded", 1, 2, 777, 128, 64, 64, "bf16", 0),
     _w("c-bf16-d64-k64-1155-padded", 1, 1, 1155, 64, 64, 32, "bf16", 0, recipe="clustered"),
@@ -89,6 +90,23 @@ BLOCK_CASES = [
 @pytest.mark.parametrize("w", BLOCK_CASES, ids=[w.name for w in BLOCK_CASES])
 def test_ragged_causal_whole_blocks(w):
     _check(w)
+
+
+# 256-key blocks of a padded recursion keep a dQ summed over the block's keys in
+# float32 (the two passes); the whole-block kernel's two halves, which round the
+# first half's sum to bf16, take unpadded lists only
+@pytest.mark.parametrize("N,halves", [(2051, False), (1001, False), (2048, True), (1040, True)])
+def test_padded_256_key_blocks_keep_float32_sums(N, halves):
+    w = _w(f"c-bf16-d64-k256-{N}", 1, 1, N, 64, 256, 32, "bf16", 130)
+    inp = W.make_inputs(w, with_grad=True)
+    E.profile_enable(True)
+    try:
+        run_gpu_fwd_bwd(cfg_of(w), inp)
+        names = set(E.profile_read())
+    finally:
+        E.profile_enable(False)
+    assert ("sparse_bwd_levels" in names) == halves, names
+    assert ({"sparse_dq_levels", "sparse_dkv_levels"} <= names) == (not halves), names
 
 
 # the forward's 128-query tiles: levels of b >= 128 whose lists end anywhere in
