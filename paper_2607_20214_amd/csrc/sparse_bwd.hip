@@ -660,14 +660,14 @@ __device__ __forceinline__ void sparse_dkv_body(const BArgs& a, int tile, int h,
 
     // query rows of the tile at q0 that this thread stages, and the scalars
     // of query q0 + threadIdx.x (threads < 64).  Staged rows past the
-    // scanned range repeat its last entry and a zero token's entry (-1)
-    // reads row 0: real rows whose scores the mask drops (the scalars mark
-    // them), so the loads need no per-row branch.
+    // scanned range repeat its last entry, whose scores the mask drops, so
+    // the loads need no per-row branch, except in a padded recursion, where
+    // a zero token (-1) is a row of zeros.
     auto tokens = [&](int q0, int (&tok)[PT], int& qt) {
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
             const int p = min(q0 + TD::row_of(j), qend - 1);
-            tok[j] = (MODE == kLeaf) ? p : max(qlist[p], 0);
+            tok[j] = (MODE == kLeaf) ? p : qlist[p];
         }
         qt = -1;
         if (threadIdx.x < kT) {
@@ -688,6 +688,15 @@ __device__ __forceinline__ void sparse_dkv_body(const BArgs& a, int tile, int h,
     const int ntiles = (qend - qbeg + kT - 1) / kT;
     int tok[PT], qt_cur, qt_next = -1;
     uint4 rq[PT], ro[PT];
+    auto qrows = [&](const int (&t)[PT]) {
+        if (MODE == kLevels && a.lt.padded) {
+            TD::load(Q, t, rq);
+            TD::load(dO, t, ro);
+        } else {
+            TD::load_all(Q, t, rq);
+            TD::load_all(dO, t, ro);
+        }
+    };
     if (MODE != kLevels) {
         const size_t wh = (bh % a.H) * D * a.wk;
         WtStage<T, D>::issue((const S*)a.wt_hi + wh, (const S*)a.wt_lo + wh, a.wk, swt);
@@ -695,8 +704,7 @@ __device__ __forceinline__ void sparse_dkv_body(const BArgs& a, int tile, int h,
     qt_cur = -1;
     if (ntiles > 0) {
         tokens(qbeg, tok, qt_cur);
-        TD::load_all(Q, tok, rq);
-        TD::load_all(dO, tok, ro);
+        qrows(tok);
     }
     scalars(qt_cur);
     if (ntiles > 1) tokens(qbeg + kT, tok, qt_next);
@@ -737,8 +745,7 @@ __device__ __forceinline__ void sparse_dkv_body(const BArgs& a, int tile, int h,
         if (MODE != kLevels && t == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // W' in LDS
         __syncthreads();
         if (t + 1 < ntiles) {
-            TD::load_all(Q, tok, rq);
-            TD::load_all(dO, tok, ro);
+            qrows(tok);
             scalars(qt_next);
             qt_cur = qt_next;
             if (t + 2 < ntiles) tokens(q0 + 2 * kT, tok, qt_next);
@@ -1005,6 +1012,10 @@ __global__ __launch_bounds__(kThreads, (two_pass_waves<T, D>())) void sparse_lea
 template <class T, int D, int BQ>
 constexpr int block_waves() { return T::bytes == 4 ? (D == 64 ? 2 : 1) : BQ == 64 && D == 64 ? 3 : 2; }
 
+// marks a missing query among the log denominators (a quiet NaN that no
+// arithmetic produces); its probabilities are selected to zero
+constexpr uint32_t kNoQuery = 0x7fc0d0d0u;
+
 template <class T, int D, int BQ, int MODE, int QB = BQ, bool FULL = MODE == kLevels>
 __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_block_kernel(BArgs a)
 {
@@ -1025,7 +1036,7 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_
     constexpr bool kFull = FULL;
     static_assert(!FULL || MODE == kLevels, "full blocks: levels only");
     // levels: rows past a short block's entries are loaded from its last
-    // entry (a real row, masked out), so the row loads carry no branch
+    // entry and masked out, so the row loads carry no branch
     constexpr bool kClamp = MODE == kLevels;
     static_assert(TS::elems(BQ) <= 2 * TD::elems(64), "dS^T fits in the query tiles");
     __shared__ __attribute__((aligned(16))) S sk[TD::elems(BQ)];
@@ -1071,8 +1082,8 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_
         if (MODE == kLevels && !FULL) {
             // level lists of any length: ceil(h / QB) blocks per list of h
             // entries, the last one short; a padded recursion's query lists
-            // hold zero tokens (-1), which are masked like a short block's
-            // missing queries
+            // hold zero tokens (-1): rows and scalars of zeros, masked like a
+            // short block's missing queries
             int level = 0, first = 0;
             for (;;) {
                 const int cnt = ((a.lt.len[level + 1] + QB - 1) / QB) << level;
@@ -1168,7 +1179,8 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_
     uint4 rq[PT], ro[PT];
     float l2 = 0.f, de = 0.f, sc = 0.f;
     // rows and row scalars of query tile qt (every thread reads the scalars
-    // of query 64 qt + tx % 64; threads < 64 publish them)
+    // of query 64 qt + tx % 64; threads < 64 publish them).  Levels: a zero
+    // token's row is loaded as row 0 and cleared when it is staged.
     auto qload = [&](size_t bh, const Idx& ix, int qt) {
         const S* Q = (const S*)a.Q + bh * N * D;
         const S* dO = (const S*)a.dO + bh * N * D;
@@ -1255,13 +1267,24 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_
         for (int qt = 0; qt < NQT; ++qt) {
             const bool last = qt + 1 == NQT;
             if (qt > 0) __syncthreads();                 // previous dS^T / dQ phase done
+            // (each wave's lanes hold the tile's 64 queries)
+            const bool gaps = !kFull && __any(ix.qt1[qt] < 0 || ktok < 0);
+            if constexpr (kClamp && !kFull) {
+                // rows without a query (a short block's end, zero tokens) are
+                // zeros: row 0 may hold anything
+                if (gaps) {
+#pragma unroll
+                    for (int j = 0; j < PT; ++j)
+                        if (__shfl(ix.qt1[qt], TD::row_of(j, tx)) < 0) rq[j] = ro[j] = make_uint4(0, 0, 0, 0);
+                }
+            }
             TD::store(sq, rq, 0, tx);
             TD::store(so, ro, 0, tx);
             if (threadIdx.x < 64) {
-                // (a short block's missing query: an infinite log denominator, P = 0)
-                s_l2[tx] = (kFull || ix.qt1[qt] >= 0) ? l2 : (kClamp ? INFINITY : 0.f);
-                s_de[tx] = de;
-                s_sc[tx] = sc;
+                const bool live = kFull || ix.qt1[qt] >= 0;
+                s_l2[tx] = live ? l2 : __uint_as_float(kNoQuery);
+                s_de[tx] = live ? de : 0.f;
+                s_sc[tx] = live ? sc : 0.f;
                 s_qt[tx] = ix.qt1[qt];
             }
             __syncthreads();
@@ -1302,8 +1325,8 @@ __global__ __launch_bounds__(BQ * 4, (block_waves<T, D, BQ>())) void sparse_bwd_
                                 dev = *(const f32x4*)&s_de[q4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const bool ok = kFull || (kClamp ? ktok >= 0 : (ktok >= 0 && s_qt[q4 + i] >= 0));
-                        const float P = ok ? fast_exp2(fmaf(st[i], a.tau2, -l2v[i])) : 0.f;
+                        float P = fast_exp2(fmaf(st[i], a.tau2, -l2v[i]));
+                        if (gaps) P = ktok >= 0 && __float_as_uint(l2v[i]) != kNoQuery ? P : 0.f;
                         p8[4 * h2 + i] = P * scv[i];
                         z8[4 * h2 + i] = P * fmaf(scv[i], dp[i], -dev[i]);
                     }
