@@ -223,7 +223,8 @@ struct URegs {
 
 // Features of chunk tokens [t0 + 16w, t0 + 16w + 16) for every table, from
 // the projections t = tanh(u) in ur (URegs::load of the same chunk), into a
-// feature RowTile (zero for padded tables and rows past N).  W: row width of
+// feature RowTile (zero for padded tables, whose t is 0, and rows past N,
+// which repeat row N - 1).  W: row width of
 // that tile (RP, or more when ur holds some of the tables, ph then pointing
 // at their first column).
 template <class T, int RP, int W = RP>

@@ -156,8 +156,10 @@ __global__ __launch_bounds__(kProjThreads) void proj_kernel(ProjIO io, const flo
                 const int p0 = 16 * pt + 4 * g;
                 if (tl < rows && p0 < UP) {
                     // the RACE passes use u only through t = tanh(u): store t
+                    // (0 for padded tables, whose product is 0 x NaN where
+                    // the row holds an infinity)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] = race::tanh_abs(acc[i]);
+                    for (int i = 0; i < 4; ++i) acc[i] = p0 < 4 * L ? race::tanh_abs(acc[i]) : 0.f;
                     *(f32x4*)(U + (bh * N + row0 + tl) * UP + p0) = acc;
                 }
             }

@@ -4,9 +4,8 @@ runs the same inputs twice, clean and poisoned, and compares bit for bit the
 rows that do not depend on the poisoned values."""
 import numpy as np
 import pytest
-import torch
 
-from gpu_util import cfg_of, run_gpu_fwd_bwd, say
+from gpu_util import cfg_of, run_gpu_fwd, run_gpu_fwd_bwd, say
 import paper_2607_20214_amd as E
 from paper_2607_20214_amd import workloads as W
 
@@ -57,3 +56,20 @@ def test_zero_tokens_do_not_read_token_0(w, poison):
         assert np.isfinite(clean[name]).all(), name
         bad = ~(got[name][:, :, t0:] == clean[name][:, :, t0:])
         assert not bad.any(), f"{name}: {bad.sum()} of {bad.size} differ"
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,r", [(64, 16), (64, 48), (128, 48), (64, 80)])
+def test_padded_feature_tables_stay_zero(d, r, causal):
+    """float32, a feature count that fills no padded size: an infinite entry
+    of a key saturates its features like a huge one, and the tables that pad
+    the count stay out of the low-rank branch."""
+    w = _w(f"f32-d{d}-r{r}", 2, 200, d, 64, r, "f32", causal=causal)
+    cfg, inp = cfg_of(w), W.make_inputs(w)
+    inp["K"][..., 17, 5] = 1e30
+    huge, _ = run_gpu_fwd(cfg, inp)
+    inp["K"][..., 17, 5] = np.inf
+    inf, _ = run_gpu_fwd(cfg, inp)
+    for name in ("d_lr", "O_lr"):
+        assert np.isfinite(huge[name]).all(), name
+        assert np.array_equal(huge[name], inf[name]), name
