@@ -4,6 +4,7 @@
 // address of a plan (tests/host/gemm_index_check.cpp).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -58,7 +59,7 @@ struct KTiles {
     ELSAA_HD KTiles(int K, int kper, int sp)
     {
         kb = sp * kper;
-        ke = at_most(K, kb + kper);
+        ke = kb + at_most(K - kb, kper);
         n = (ke - kb + BK - 1) / BK;
         first = ke - kb - (n - 1) * BK;
     }
@@ -131,7 +132,10 @@ inline Plan plan_of(const elsaa_gemm_desc* d)
     const int br = d->trans_b ? d->N : d->K, bc = d->trans_b ? d->K : d->N;
     p.any = !fast_operand(d->trans_a != 0, ar, ac, d->lda, d->a_heads, d->seq) ||
             !fast_operand(d->trans_b == 0, br, bc, d->ldb, d->b_heads, d->seq);
-    const int ktiles = (d->K + BK - 1) / BK;
+    // (64-bit counts: M, N and K may each be any int)
+    auto parts = [](int64_t n, int64_t per) { return (n + per - 1) / per; };
+    auto tiles_of = [&](int t) { return parts(d->M, t) * parts(d->N, t); };
+    const int64_t ktiles = parts(d->K, BK);
     // Estimated microseconds of a tile size and split count.  A round is the
     // workgroups resident at once on 256 compute units (256 large tiles or
     // 512 small ones); measured per K-tile 1.55 us for a round of large
@@ -147,10 +151,9 @@ inline Plan plan_of(const elsaa_gemm_desc* d)
     // throughout (16 - 22 us against 28 - 34).
     const double small_us = d->trans_a && !d->trans_b ? 1.25 : 1.05;
     auto estimate = [&](bool big, int splits) {
-        const int t = big ? kBig : BM, fill = big ? 256 : 512;
-        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
-        const int per = (ktiles + splits - 1) / splits;
-        const int wgs = tiles * ((ktiles + per - 1) / per), rem = wgs % fill;
+        const int fill = big ? 256 : 512;
+        const int64_t per = parts(ktiles, splits);
+        const int64_t wgs = tiles_of(big ? kBig : BM) * parts(ktiles, per), rem = wgs % fill;
         const double rounds = wgs / fill + (rem == 0 ? 0. : !big && 2 * rem <= fill ? 0.8 : 1.);
         const double reduce = splits > 1 ? 5. + 2e-6 * splits * (double)d->M * d->N * 4 / 6. : 0.;
         return rounds * (per * (big ? 1.55 : small_us) + 2.5) + reduce;
@@ -158,10 +161,9 @@ inline Plan plan_of(const elsaa_gemm_desc* d)
     double best = 0.;
     // (the large kernel's unmasked loads need 64 values of k: KTiles::whole)
     for (int kind = 0; kind < (p.any || d->K < BK ? 1 : 2); ++kind) {
-        const int t = kind ? kBig : BM, fill = kind ? 256 : 512;
-        const int tiles = ((d->M + t - 1) / t) * ((d->N + t - 1) / t);
+        const int64_t tiles = tiles_of(kind ? kBig : BM), fill = kind ? 256 : 512;
         // at least 8 K-tiles per split, at most one round of workgroups
-        const int most = tiles < fill ? std::max(1, std::min(fill / tiles, ktiles / 8)) : 1;
+        const int64_t most = tiles < fill ? std::max<int64_t>(1, std::min(fill / tiles, ktiles / 8)) : 1;
         for (int splits = 1; splits <= most; ++splits) {
             const double e = estimate(kind == 1, splits);
             if ((kind == 0 && splits == 1) || e < best) {
@@ -172,10 +174,10 @@ inline Plan plan_of(const elsaa_gemm_desc* d)
         }
     }
     const int t = p.big ? kBig : BM;
-    p.tiles_m = (d->M + t - 1) / t;
-    p.tiles_n = (d->N + t - 1) / t;
-    p.kper = (ktiles + p.splits - 1) / p.splits * BK;
-    p.splits = (d->K + p.kper - 1) / p.kper;
+    p.tiles_m = (int)parts(d->M, t);
+    p.tiles_n = (int)parts(d->N, t);
+    p.kper = (int)std::min<int64_t>(parts(ktiles, p.splits) * BK, INT_MAX - BK + 1);
+    p.splits = (int)parts(d->K, p.kper);
     p.ws_bytes = p.splits > 1 ? (size_t)p.splits * d->M * d->N * sizeof(float) : 0;
     return p;
 }

@@ -39,3 +39,12 @@ def test_walk_reaches_a_last_split_of_less_than_a_k_tile(exe):
     """dW_O of a block of d_model 1024 over 13448 tokens: the large kernel's last split holds 8 values of k."""
     kind, splits, kper = plan(exe, 1024, 1024, 13448, 1, 0, (16, 0, 0), 13448)
     assert kind == "large" and 0 < 13448 - (splits - 1) * kper < 64
+
+
+@pytest.mark.parametrize("M,N,K", [(8388608, 8388608, 8), (2147483640, 2147483640, 8), (2147483640, 8, 2147483640),
+                                   (8, 8, 2147483640), (2147483640, 2147483640, 2147483640)])
+def test_plan_of_any_size(exe, M, N, K):
+    """A workspace query may name any sizes: tile counts past 2^31 (and 2^32
+    exactly, which an int count held as 0 and divided by) are planned."""
+    kind, splits, kper = plan(exe, M, N, K, 0, 0)
+    assert kper > 0 and kper % 64 == 0 and 0 <= (splits - 1) * kper < K <= splits * kper
