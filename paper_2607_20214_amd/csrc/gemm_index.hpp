@@ -111,18 +111,26 @@ struct Plan {
     size_t ws_bytes;
 };
 
-// Whether StreamIndex can address an operand stored as rows x cols: `kmajor` ones
-// need every K-tile's 64 rows in one sequence (a single sequence, or whole
-// 64-row pieces of several), the others its 64 columns in one head; offsets
-// within a 256-row tile and a K-tile must fit 32 bits.
+// Whether StreamIndex can address an operand stored as rows x cols: `kmajor`
+// ones need every K-tile's 64 rows in one sequence (a single sequence, or
+// whole 64-row pieces of several), the others its 64 columns in one head; the
+// offsets from a tile's first element (tiles of up to 256 rows or columns
+// start at a multiple of their size) must fit 31 bits.  A [x][k] tile spans
+// further sequences only where several meet inside 256 rows, a [k][x] one the
+// planes of 256 / dh heads (out of reach from 5.6 million tokens a sequence
+// at dh 64 and 8.4 million at 128).
 inline bool fast_operand(bool kmajor, int rows, int cols, int64_t ld, int heads, int seq)
 {
     const int64_t lim = (int64_t)1 << 31;
     if (heads <= 0) return ld >= 0 && ld < lim / 512;
     if (seq < 1 || cols / heads < 8) return false;                     // (refused by check_mat)
     const int64_t dh = cols / heads, plane = (int64_t)seq * dh * 2;     // bytes of one head's rows
-    if (kmajor) return (seq >= rows || seq % BK == 0) && (256 / dh + 2) * plane < lim;
-    return dh % BK == 0 && (256 / (int64_t)seq + 2) * heads * plane < lim;
+    if (kmajor) {
+        const int64_t span = dh < kBig ? (kBig / dh - 1) * plane : 0;
+        return (seq >= rows || seq % BK == 0) && span + (BK + 1) * dh * 2 + 2 * kBig < lim;
+    }
+    const int64_t crossings = seq >= rows || seq % kBig == 0 ? 0 : kBig / seq + 1;
+    return dh % BK == 0 && crossings * (heads - 1) * plane + kBig * dh * 2 + 2 * BK < lim;
 }
 
 inline Plan plan_of(const elsaa_gemm_desc* d)

@@ -167,6 +167,20 @@ int main(int argc, char** argv)
                 check(desc(n, dm, 3 * dm, 0, 1, 3 * H, 0, 0, seq));
                 check(desc(dm, 3 * dm, n, 1, 0, 0, 3 * H, 0, seq));
             }
+    // operands of several GiB, up to the offsets' limits, and just past them
+    for (int seq : {262144, 1048576, 2097152, 5592320, 5592448, 8388480, 8388736, 16777216})
+        for (int nseq : {1, 3})
+            for (int dh : {64, 128}) {
+                const int64_t rows = (int64_t)seq * nseq;
+                if (rows > 33000000) continue;
+                const int n = (int)rows, H = 2048 / dh, dm = 2048;
+                check(desc(n, dm, dm, 0, 0, H, 0, 0, seq));                // O W_O
+                check(desc(dm, dm, n, 1, 0, H, 0, 0, seq));                // dW_O
+                check(desc(n, dm, 3 * dm, 0, 1, 3 * H, 0, 0, seq));        // dQKV W'
+                check(desc(dm, 3 * dm, n, 1, 0, 0, 3 * H, 0, seq));        // dW_QKV
+            }
+    for (int seq : {200, 1000, 100000, 524280, 2097160})                   // tiles that cross sequences
+        for (int heads : {2, 16, 48}) check(desc(4 * seq, 1024, 64 * heads, 0, 1, heads, 0, 0, seq));
     std::printf("%ld loads\n", g_loads);
     std::printf(g_fail ? "%d FAILED\n" : "ALL OK\n", g_fail);
     return g_fail != 0;

@@ -48,3 +48,14 @@ def test_plan_of_any_size(exe, M, N, K):
     exactly, which an int count held as 0 and divided by) are planned."""
     kind, splits, kper = plan(exe, M, N, K, 0, 0)
     assert kper > 0 and kper % 64 == 0 and 0 <= (splits - 1) * kper < K <= splits * kper
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("seq,nseq", [(262144, 1), (262144, 3), (2097152, 1)])
+def test_large_head_major_products_keep_the_large_kernel(exe, seq, nseq, dh):
+    """O W_O, dQKV W_QKV', dW_O and dW_QKV of d_model 2048 over sequences whose
+    rows of all heads are past 2^31 bytes: no tile spans them."""
+    n, dm, H = seq * nseq, 2048, 2048 // dh
+    for shape, ta, tb, heads in [((n, dm, dm), 0, 0, (H, 0, 0)), ((n, dm, 3 * dm), 0, 1, (3 * H, 0, 0)),
+                                 ((dm, dm, n), 1, 0, (H, 0, 0)), ((dm, 3 * dm, n), 1, 0, (0, 3 * H, 0))]:
+        assert plan(exe, *shape, ta, tb, heads, seq)[0] == "large", (shape, heads)
