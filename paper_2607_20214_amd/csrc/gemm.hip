@@ -113,28 +113,24 @@ struct Stream {
     }
 };
 
-// The same K-tiles element by element (any layout): 128-row tiles of operands
-// that Stream does not take.
+// The same for operands that Stream does not take (StreamIndexAny).
 template <bool KMAJOR>
 struct StreamAny {
-    static constexpr int C = 4;
-    int x0, xlim;
-    __device__ __forceinline__ void init(const Mat&, int x0_, int xlim_)
+    using Ix = StreamIndexAny<KMAJOR>;
+    static constexpr int C = Ix::C;
+    Ix ix;
+    __device__ __forceinline__ void init(const Mat& m, int x0, int xlim) { ix.init(m, x0, xlim, threadIdx.x); }
+    __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[C]) const
     {
-        x0 = x0_;
-        xlim = xlim_;
+#pragma unroll
+        for (int c = 0; c < C; ++c) r[c] = ldg16((const uint16_t*)m.p + ix.at(m, k0, c, threadIdx.x));
     }
-    __device__ __forceinline__ void load(const Mat& m, int k0, uint4 (&r)[C]) const { load_short(m, k0, BK, r); }
     __device__ __forceinline__ void load_short(const Mat& m, int k0, int kn, uint4 (&r)[C]) const
     {
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int id = threadIdx.x + kThreads * c;
-            const int k = KMAJOR ? id >> 4 : (id & 7) * 8, x = x0 + (KMAJOR ? (id & 15) * 8 : id >> 3);
-            const bool ok = k < kn && x < xlim;
-            const uint16_t* q = (const uint16_t*)m.p + (ok ? (KMAJOR ? mat_offset(m, k0 + k, x) : mat_offset(m, x, k0 + k)) : 0);
-            r[c] = ok ? ldg16(q) : make_uint4(0, 0, 0, 0);
-        }
+        for (int c = 0; c < C; ++c)
+            r[c] = Ix::k_in_tile(c, threadIdx.x) < kn ? ldg16((const uint16_t*)m.p + ix.at(m, k0, c, threadIdx.x))
+                                                      : make_uint4(0, 0, 0, 0);
     }
 };
 

@@ -102,6 +102,32 @@ struct StreamIndex {
     ELSAA_HD static int k_in_tile(int c, int tx) { return KMAJOR ? tx / TPR + RPC * c : 8 * (tx % TPR); }
 };
 
+// The same for 128-row tiles of operands that StreamIndex does not take: 64-bit
+// offsets, and a K-tile's rows or columns each in a sequence or head of its
+// own.  What does not depend on k is formed once per thread.
+template <bool KMAJOR>
+struct StreamIndexAny {
+    static constexpr int C = BM * BK / 8 / kThreads;
+    static constexpr int TPR = KMAJOR ? BM / 8 : 8, RPC = kThreads / TPR;
+    int64_t fixed[KMAJOR ? 1 : C];   // elements
+    ELSAA_HD void init(const Mat& m, int x0, int xlim, int tx)
+    {
+        if (KMAJOR) {
+            fixed[0] = col_part(m, at_most(x0 + 8 * (tx % TPR), xlim - 8));
+        } else {
+#pragma unroll
+            for (int c = 0; c < C; ++c) fixed[KMAJOR ? 0 : c] = row_part(m, at_most(x0 + tx / TPR + RPC * c, xlim - 1));
+        }
+    }
+    // element offset of chunk c of the K-tile at k0
+    ELSAA_HD int64_t at(const Mat& m, int k0, int c, int tx) const
+    {
+        const int k = k0 + k_in_tile(c, tx);
+        return fixed[KMAJOR ? 0 : c] + (KMAJOR ? row_part(m, k) : col_part(m, k));
+    }
+    ELSAA_HD static int k_in_tile(int c, int tx) { return KMAJOR ? tx / TPR + RPC * c : 8 * (tx % TPR); }
+};
+
 #undef ELSAA_HD
 
 struct Plan {

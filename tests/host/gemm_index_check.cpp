@@ -64,18 +64,22 @@ void fail(const elsaa_gemm_desc& d, char op, const char* what, int64_t at, int64
 // The loads of one operand's K-tile at k0 with kn valid values of k (masked
 // when `mask`), for the tile of rows (or columns) [x0, x0 + XT).
 template <bool KMAJOR, int XT>
-void check_tile(const elsaa_gemm_desc& d, char op, const Operand& o, int x0, int xlim, int k0, int kn, bool mask, bool used)
+void check_tile(const elsaa_gemm_desc& d, char op, const Operand& o, int x0, int xlim, int k0, int kn, bool mask, bool used,
+                bool any)
 {
     using Ix = StreamIndex<KMAJOR, XT>;
+    using Any = StreamIndexAny<KMAJOR>;
     for (int tx = 0; tx < kThreads; tx += tx < 64 || tx >= kThreads - 64 ? 1 : 7) {
         Ix ix;
-        ix.init(o.m, x0, xlim, tx);
+        Any ax;
+        if (any) ax.init(o.m, x0, xlim, tx);
+        else ix.init(o.m, x0, xlim, tx);
         for (int c = 0; c < Ix::C; ++c) {
-            const int k = Ix::k_in_tile(c, tx);
+            const int k = any ? Any::k_in_tile(c, tx) : Ix::k_in_tile(c, tx);
             if (mask && k >= kn) continue;
             ++g_loads;
-            if (ix.off[c] > 0x7fffffffu - 15u) fail(d, op, "offset past the buffer range", ix.off[c], o.bytes);
-            const int64_t at = ix.base + Ix::tile(o.m, k0) + ix.off[c];
+            if (!any && ix.off[c] > 0x7fffffffu - 15u) fail(d, op, "offset past the buffer range", ix.off[c], o.bytes);
+            const int64_t at = any ? 2 * ax.at(o.m, k0, c, tx) : ix.base + Ix::tile(o.m, k0) + ix.off[c];
             if (at < 0 || at + 16 > o.bytes) fail(d, op, "load outside the operand", at, o.bytes);
             const int x = KMAJOR ? x0 + 8 * (tx % Ix::TPR) : x0 + tx / Ix::TPR + Ix::RPC * c;
             if (!used || x >= xlim) continue;
@@ -95,10 +99,10 @@ void check_operand(const elsaa_gemm_desc& d, char op, const Plan& p, const Opera
         const std::set<int> steps = {1, 2, kt.n / 2, kt.n - 2, kt.n - 1, kt.n, kt.n + 1};
         for (int x : xt) {
             const int x0 = x * XT;
-            check_tile<KMAJOR, XT>(d, op, o, x0, xlim, kt.kb, kt.first, true, true);
+            check_tile<KMAJOR, XT>(d, op, o, x0, xlim, kt.kb, kt.first, true, true, p.any);
             // the large kernel loads tiles 1 .. n + 1, the small one 1 .. n - 1
             for (int t : steps)
-                if (t >= 1 && (p.big || t < kt.n)) check_tile<KMAJOR, XT>(d, op, o, x0, xlim, kt.whole(t), BK, false, t < kt.n);
+                if (t >= 1 && (p.big || t < kt.n)) check_tile<KMAJOR, XT>(d, op, o, x0, xlim, kt.whole(t), BK, false, t < kt.n, p.any);
         }
         // the K-tiles cover the split: one short, then whole ones up to ke
         int k = kt.kb + kt.first;
@@ -118,7 +122,6 @@ void check_operand(const elsaa_gemm_desc& d, char op, const Plan& p, const Opera
 void check(const elsaa_gemm_desc& d)
 {
     const Plan p = plan_of(&d);
-    if (p.any) return;                                    // element by element, each with its own bounds
     const Operand A = operand(d.trans_a ? d.K : d.M, d.trans_a ? d.M : d.K, d.lda, d.a_heads, d.seq);
     const Operand B = operand(d.trans_b ? d.N : d.K, d.trans_b ? d.K : d.N, d.ldb, d.b_heads, d.seq);
     if (d.trans_a) check_operand<true>(d, 'A', p, A, d.M, p.tiles_m);
