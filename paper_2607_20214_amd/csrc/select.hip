@@ -356,7 +356,19 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_kernel(const uint8_t* __re
 }
 
 namespace {
-int sort_waves(const Shape& s) { return s.causal || s.N < 1024 ? 4 : 16; }
+// Waves of a list.  Causal levels have 2^(l + 1) lists, most of them short, and
+// fill the device with four.  Non-causal calls have two long lists per (b, h):
+// sixteen waves where they leave compute units idle (up to one workgroup
+// each) or are longer than eight steps of four waves (30720 tokens 121 -> 36
+// us, 4096: 13 -> 5).  Shorter lists that fill the device take four, whose
+// workgroup costs less to start and to scan: with the RACE scan beside them
+// 192 heads x 1536 tokens 11.4 us against 12.0, 512 x 2048 17.9 against 21.8,
+// 1024 x 1024 19.7 against 31.2; 128 heads x 2048 11.5 against 9.7.
+int sort_waves(const Shape& s)
+{
+    if (s.causal || s.N < 1024) return 4;
+    return 2 * (int64_t)s.B * s.H <= 256 || s.N > 2048 ? 16 : 4;
+}
 }  // namespace
 
 int sort_steps(const Shape& s)
@@ -375,9 +387,6 @@ hipError_t launch_sort(const Shape& s, const SortJob& job, const ScanJob& scan, 
     // dependent steps that leave the device mostly idle (9 + 8 us apart; 2 x
     // 8 heads x 4096 step 116 -> 112 us, 512-token forward 27 -> 26)
     dim3 grid(tasks + (scan.states ? (scan.per + threads - 1) / threads : 0), s.H, s.B);
-    // non-causal: two long lists per (b, h), so few workgroups: sixteen waves
-    // each (30720 tokens 121 -> 36 us, 4096: 13 -> 5); causal levels have
-    // 2^(l + 1) lists, most of them short, and fill the device with four
 #define ELSAA_SORT(W_)                                                                                       \
     ELSAA_LAUNCH(scan.states ? "sort_scan" : "sort", sort_kernel<W_>, grid, dim3(W_ * kWave), 0, st, job.keyq, \
                  job.keyk, job.perm_q, job.perm_k, s.H, s.N, s.causal, s.lt, s.sort_bits, tasks, scan)

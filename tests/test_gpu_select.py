@@ -39,6 +39,11 @@ CASES = [
     _w("nc-bf16-d64-1024-bits8", 1, 2, 1024, 64, 64, False, "bf16", sort_bits=8),
     _w("nc-f32-d64-1030", 1, 1, 1030, 64, 64, False, "f32", recipe="clustered", centres=2),
     _w("nc-bf16-d64-16385-bits8", 1, 1, 16385, 64, 64, False, "bf16", sort_bits=8),
+    # four waves a list where the lists fill the device (more than 128 heads, up
+    # to 2048 tokens), and the first length past it
+    _w("nc-bf16-d64-129x1025", 3, 43, 1025, 64, 64, False, "bf16"),
+    _w("nc-bf16-d64-129x2048", 3, 43, 2048, 64, 64, False, "bf16", recipe="clustered", centres=4),
+    _w("nc-bf16-d64-129x2049", 3, 43, 2049, 64, 64, False, "bf16"),
 ]
 
 
