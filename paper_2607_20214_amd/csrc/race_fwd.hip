@@ -470,18 +470,25 @@ constexpr bool fits()
     return sizeof(StateSmem<T, D, RP / table_split<RP>()>) <= kMaxLds && sizeof(OutSmem<T, D, RP>) <= kMaxLds;
 }
 
-// The row scalars in the state pass: one launch and one reading of dO less,
-// which short calls gain by (65536 rows, d_h 64: 13 + 10 -> 14 us a call,
-// encoder step 123 -> 118; 25088 rows float32: step 140 -> 137).  Long ones
-// do not: the pass's registers leave two workgroups a compute unit, too few
-// to stream O_s at the row pass's rate (262144 rows, d_h 128, 128 features: 94
-// us against 54 + 34; 512000 rows, d_h 128, 64 features: 149 against 105 +
-// 49).  With the tables split over two workgroups every row would be read
-// twice.
-template <int RP>
+// The row scalars in the state pass: one launch and one reading of dO less.
+// At d_h 64 that is a gain for short calls (whole steps: 65536 rows, 64
+// features 112 -> 106 us, encoder step 123 -> 118; float32 25088 rows 140 ->
+// 137, 65536 rows 189 -> 185; 262144 rows, past the line, 324 -> 314).  At d_h 128 the pass's registers leave two
+// workgroups a compute unit in bf16 and one in float32, too few to stream O_s
+// at the row pass's rate: up to 64 features and 65536 rows it is still the
+// faster one or equal (32768 rows 128 -> 126, 65536 175 -> 174; 131072 rows
+// 312 -> 315), at 128 features (32768 rows 164 -> 166, 131072 368 -> 378) and
+// in float32 (4096 rows 87 -> 91, 65536 341 -> 354) it loses throughout.
+// With the tables split over two workgroups every row would be read twice.
+template <class T, int D, int RP>
+constexpr bool rows_can_fuse()
+{
+    return table_split<RP>() == 1 && (D == 64 || (T::bytes == 2 && RP <= 64));
+}
+template <class T, int D, int RP>
 bool fused_rows(const Shape& s)
 {
-    return table_split<RP>() == 1 && (int64_t)s.B * s.H * s.N <= 131072;
+    return rows_can_fuse<T, D, RP>() && (int64_t)s.B * s.H * s.N <= (D == 64 ? 131072 : 65536);
 }
 
 template <class T, int D, int RP>
@@ -493,8 +500,8 @@ hipError_t launch_states_t(const Shape& s, const StateArgs& a, bool bwd, const S
         dim3 grid(s.nseg * table_split<RP>(), s.H, s.B);
         hipError_t e;
         if (!bwd) ELSAA_LAUNCH("race_state_fwd", (race_state_kernel<T, D, RP, kStateFwd>), grid, dim3(kThreads), 0, st, a);
-        else if (fused_rows<RP>(s)) {
-            if constexpr (table_split<RP>() == 1)
+        else if (fused_rows<T, D, RP>(s)) {
+            if constexpr (rows_can_fuse<T, D, RP>())
                 ELSAA_LAUNCH("race_rows_bwd", (race_state_kernel<T, D, RP, kStateRows>), grid, dim3(kThreads), 0, st, a);
         } else {
             if ((e = launch_bwd_rows(s, a.Val, a.rows, st)) != hipSuccess) return e;
