@@ -76,12 +76,12 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
         n_leaf = N >> Lv
         lvl_inter = bh * Lv * half * min(k, half)
         leaf_inter = bh * (N // n_leaf) * (n_leaf * (n_leaf + 1) // 2)
-        u["sparse_fwd_levels"] = (bh * Lv * (3 * half * D * s + 4 * N), lvl_inter * 4 * D, ["sparse_fwd_levels"])
-        u["sparse_fwd_leaf"] = (base_fwd, leaf_inter * 4 * D, ["sparse_fwd_leaf"])
+        u["sparse_fwd_levels"] = (bh * Lv * (3 * half * D * s + 4 * N), lvl_inter * 4 * D, ["sparse_fwd_levels", "sparse_fwd_levels_wide"])
+        u["sparse_fwd_leaf"] = (base_fwd, leaf_inter * 4 * D, ["sparse_fwd_leaf", "sparse_fwd_leaf_wide"])
         u["sparse_bwd_levels"] = (bh * Lv * (2 * N * D * s + 4 * N), lvl_inter * 10 * D,
                                   ["sparse_bwd_levels", "sparse_dq_levels", "sparse_dkv_levels"])
         u["sparse_bwd_leaf"] = (base_bwd, leaf_inter * 10 * D,
-                                ["sparse_leaf_bwd", "sparse_dq_leaf", "sparse_dkv_leaf"])
+                                ["sparse_leaf_bwd", "sparse_leaf_bwd_wide", "sparse_dq_leaf", "sparse_dkv_leaf"])
     else:
         inter = bh * N * min(k, N)
         u["sparse_fwd_blocks"] = (base_fwd, inter * 4 * D, ["sparse_fwd_blocks"])
@@ -126,13 +126,14 @@ def kernel_model(w, Lv: int) -> dict:
     ps = s                          # level partials are kept in the storage dtype
     lvl_pos = Lv * bh * half        # (level, position) slots of the partials
     wk = max(32, 4 * w.L)
-    return {
+    m = {
         "sparse_fwd_levels": lvl_pos * (3 * D * s + 8 + D * ps + 4),
         "sparse_fwd_leaf": bh * N * (3 * D * s + 4 * D + D * s + 4 + D * s + 8) + lvl_pos * (D * ps + 4),
         "sparse_bwd_levels": lvl_pos * (4 * D * s + 20 + 3 * D * ps),
         "sparse_leaf_bwd": bh * N * (4 * D * s + 12 + 2 * wk * s + D * s + 3 * D * s) + lvl_pos * 3 * D * ps,
     }
-
+    # the 128-query forms move what the 64-query forms do
+    return {**m, **{k + "_wide": m[k] for k in ("sparse_fwd_levels", "sparse_fwd_leaf", "sparse_leaf_bwd")}}
 
 
 def source_digest(names) -> str:

@@ -1543,7 +1543,7 @@ hipError_t launch_t(const Shape& s, const BArgs& a, hipStream_t st, int parts)
         const bool wide = wide_leaf_dq(s);
         dim3 grid(a.lt.leaf_tiles() + (wide ? a.lt.wper_leaf * a.lt.leaves : a.lt.leaf_tiles()), s.H, s.B);
         if constexpr (T::bytes == 2) {
-            if (wide) ELSAA_LAUNCH("sparse_leaf_bwd", (sparse_leaf_bwd_kernel<T, D, true>), grid, dim3(kThreads), 0, st, a);
+            if (wide) ELSAA_LAUNCH("sparse_leaf_bwd_wide", (sparse_leaf_bwd_kernel<T, D, true>), grid, dim3(kThreads), 0, st, a);
         }
         if (!wide) ELSAA_LAUNCH("sparse_leaf_bwd", (sparse_leaf_bwd_kernel<T, D, false>), grid, dim3(kThreads), 0, st, a);
         return hipGetLastError();

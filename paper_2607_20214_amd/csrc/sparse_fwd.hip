@@ -656,8 +656,15 @@ __global__ __launch_bounds__(kThreads, 2) void sparse_fwd_wide_kernel(Args a)
     }
 }
 
-// where the wide form is the faster one (see there)
-bool wide_levels(const Shape& s) { return s.bf16 && s.k >= 128; }
+// where the wide form is the faster one (see there); the levels also need
+// enough of its tiles to keep as many compute units busy as the 64-query form
+// does (the level kernel of 64 of them 13.2 -> 13.9 us, of 96 8.7 -> 8.9, of
+// 128 14.1 -> 15.5 and 10.9 -> 11.3; of 160 13.0 -> 12.6, of 192 16.1 -> 14.6,
+// of 256 11.2 -> 10.3, of 384 15.6 -> 14.8)
+bool wide_levels(const Shape& s)
+{
+    return s.bf16 && s.k >= 128 && (long)s.lt.wfirst[s.Lv] * s.B * s.H >= 160;
+}
 // (the leaf also needs two workgroups a compute unit: 512 tiles 179 -> 170 us,
 // 256 tiles 97 -> 103, 128 tiles 56 -> 71)
 bool wide_leaf(const Shape& s)
@@ -675,21 +682,23 @@ hipError_t launch_t(const Shape& s, const Args& a, hipStream_t st, int parts)
         return hipGetLastError();
     }
     if (s.Lv > 0 && (parts & kSparseLevels)) {
-        dim3 grid(wide_levels(s) ? a.lt.wfirst[s.Lv] : a.lt.first[s.Lv], s.H, s.B);
+        const bool wide = wide_levels(s);
+        dim3 grid(wide ? a.lt.wfirst[s.Lv] : a.lt.first[s.Lv], s.H, s.B);
         if constexpr (T::bytes == 2)
-            if (wide_levels(s))
-                ELSAA_LAUNCH("sparse_fwd_levels", (sparse_fwd_wide_kernel<D, kLevels>), grid, dim3(kThreads), 0, st, a);
-        if (!wide_levels(s))
+            if (wide)
+                ELSAA_LAUNCH("sparse_fwd_levels_wide", (sparse_fwd_wide_kernel<D, kLevels>), grid, dim3(kThreads), 0, st, a);
+        if (!wide)
             ELSAA_LAUNCH("sparse_fwd_levels", (sparse_fwd_kernel<T, D, kLevels>), grid, dim3(kThreads), 0, st, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (!(parts & kSparseFinal)) return hipSuccess;
-    dim3 grid(wide_leaf(s) ? a.lt.wper_leaf * a.lt.leaves : a.lt.leaf_tiles(), s.H, s.B);
+    const bool wide = wide_leaf(s);
+    dim3 grid(wide ? a.lt.wper_leaf * a.lt.leaves : a.lt.leaf_tiles(), s.H, s.B);
     if constexpr (T::bytes == 2)
-        if (wide_leaf(s))
-            ELSAA_LAUNCH("sparse_fwd_leaf", (sparse_fwd_wide_kernel<D, kLeaf>), grid, dim3(kThreads), 0, st, a);
-    if (!wide_leaf(s))
+        if (wide)
+            ELSAA_LAUNCH("sparse_fwd_leaf_wide", (sparse_fwd_wide_kernel<D, kLeaf>), grid, dim3(kThreads), 0, st, a);
+    if (!wide)
         ELSAA_LAUNCH("sparse_fwd_leaf", (sparse_fwd_kernel<T, D, kLeaf>), grid, dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }

@@ -35,12 +35,19 @@ CASES = [
 ]
 
 
-def _check(w, neighbors=0, heads=None, q_mask=None):
+def _check(w, neighbors=0, heads=None, q_mask=None, launches=()):
+    """launches: kernels that the call has to run."""
     cfg = cfg_of(w, neighbors=neighbors)
     Lv = E.num_levels(cfg)
     say(f"[ragged] {w.name}: N={w.N} k={w.k} n0={w.n0} levels={Lv} leaf={w.N >> Lv} {w.dtype} nbr={neighbors}")
     inp = W.make_inputs(w, with_grad=True)
-    fwd, bwd = run_gpu_fwd_bwd(cfg, inp)
+    E.profile_enable(True)
+    try:
+        fwd, bwd = run_gpu_fwd_bwd(cfg, inp)
+        names = set(E.profile_read())
+    finally:
+        E.profile_enable(False)
+    assert set(launches) <= names, names
     tol = TOL[w.dtype]
     hc = head_cfg_of(cfg)
     errs = {}
@@ -109,28 +116,34 @@ def test_padded_256_key_blocks_keep_float32_sums(N, halves):
     assert ({"sparse_dq_levels", "sparse_dkv_levels"} <= names) == (not halves), names
 
 
-# the forward's 128-query tiles: levels of b >= 128 whose lists end anywhere in
-# a tile and whose blocks straddle tiles (b = 160, 200), neighbouring blocks,
-# zero tokens; leaves of 1024 and more that end in a tile's first, third and
-# last wave
+# the forward's 128-query tiles: levels of b >= 128 (from 160 tiles; the first
+# three have fewer and take the 64-query form) whose lists end anywhere in a
+# tile and whose blocks straddle tiles (b = 160, 200), neighbouring blocks,
+# zero tokens; leaves of 1024 and more (from 512 tiles) that end in a tile's
+# first, third and last wave
+LEVELS, LEAF = "sparse_fwd_levels_wide", "sparse_fwd_leaf_wide"
 WIDE_CASES = [
-    (_w("c-bf16-d128-k160-1500", 1, 2, 1500, 128, 160, 64, "bf16", 0), 0),
-    (_w("c-bf16-d64-k200-1111-padded", 2, 1, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0),
-    (_w("c-bf16-d64-k128-1300-nbr1", 1, 1, 1300, 64, 128, 64, "bf16", 0), 1),
-    (_w("c-bf16-d128-leaf1025", 1, 32, 2049, 128, 128, 64, "bf16", 1100), 0),
-    (_w("c-bf16-d64-leaf1110", 3, 20, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0),
-    (_w("c-bf16-d128-leaf1152-k64", 2, 29, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0),
+    (_w("c-bf16-d128-k160-1500", 1, 2, 1500, 128, 160, 64, "bf16", 0), 0, "sparse_fwd_levels"),
+    (_w("c-bf16-d64-k200-1111-padded", 2, 1, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0, "sparse_fwd_levels"),
+    (_w("c-bf16-d64-k128-1300-nbr1", 1, 1, 1300, 64, 128, 64, "bf16", 0), 1, "sparse_fwd_levels"),
+    (_w("c-bf16-d128-k160-10x1500", 1, 10, 1500, 128, 160, 64, "bf16", 0), 0, LEVELS),
+    (_w("c-bf16-d64-k200-18x1111-padded", 2, 9, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0, LEVELS),
+    (_w("c-bf16-d64-k128-10x1300-nbr1", 1, 10, 1300, 64, 128, 64, "bf16", 0), 1, LEVELS),
+    (_w("c-bf16-d128-leaf1025", 1, 32, 2049, 128, 128, 64, "bf16", 1100), 0, LEAF),
+    (_w("c-bf16-d64-leaf1110", 3, 20, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0, LEAF),
+    (_w("c-bf16-d128-leaf1152-k64", 2, 29, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0, LEAF),
 ]
 
 
-@pytest.mark.parametrize("w,nbr", WIDE_CASES, ids=[w.name for w, _ in WIDE_CASES])
-def test_ragged_causal_wide_tiles(w, nbr):
-    _check(w, neighbors=nbr, heads={(0, 0), (w.B - 1, w.H - 1)})
+@pytest.mark.parametrize("w,nbr,kernel", WIDE_CASES, ids=[c[0].name for c in WIDE_CASES])
+def test_ragged_causal_wide_tiles(w, nbr, kernel):
+    _check(w, neighbors=nbr, heads={(0, 0), (w.B - 1, w.H - 1)}, launches=[kernel])
 
 
 # the leaf's dQ in 128-query tiles (d_h 64: leaves from 192 and 256 tiles; d_h
-# 128: from 1024 and 256 tiles, or 448 and 2048 tiles): W' of 64 columns (r > 128), leaves of one query past a tile, a leaf
-# whose last tiles hold no token, d_h 64 and 128
+# 128: from 1024 and 256 tiles, or 448 and 2048 tiles): W' of 64 columns (r >
+# 128), leaves of one query past a tile, a leaf whose last tiles hold no token,
+# d_h 64 and 128
 WIDE_LEAF_BWD_CASES = [
     _w("c-bf16-d128-r256-leaf1153", 1, 26, 1153, 128, 128, 256, "bf16", 1200),
     _w("c-bf16-d64-r192-leaf1024", 2, 16, 2047, 64, 64, 192, "bf16", 1030, recipe="clustered"),
@@ -141,7 +154,7 @@ WIDE_LEAF_BWD_CASES = [
 
 @pytest.mark.parametrize("w", WIDE_LEAF_BWD_CASES, ids=[w.name for w in WIDE_LEAF_BWD_CASES])
 def test_ragged_causal_wide_leaf_backward(w):
-    _check(w, heads={(0, 0), (w.B - 1, w.H - 1)})
+    _check(w, heads={(0, 0), (w.B - 1, w.H - 1)}, launches=["sparse_leaf_bwd_wide"])
 
 
 def test_ragged_causal_with_neighbours():
