@@ -105,7 +105,7 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
         prods = [(T, 3 * dm, dm, 2), (T, dm, dm, 4), (T, dm, dm, 2),
                  (dm, dm, T, 4), (T, dm, 3 * dm, 4), (dm, 3 * dm, T, 4)]
         u["gemm"] = (sum(2 * (M * K + K * N_) + o * M * N_ for M, N_, K, o in prods),
-                     sum(2 * M * N_ * K for M, N_, K, _ in prods), ["gemm", "gemm_reduce"])
+                     sum(2 * M * N_ * K for M, N_, K, _ in prods), ["gemm_large", "gemm_small", "gemm_any", "gemm_reduce"])
     return u
 
 
@@ -155,7 +155,8 @@ KERNEL_SOURCES = {
     "race_dv": ["race_bwd.hip", "race_common.hpp", "common.hpp"],
     "race_rows_bwd": ["race_fwd.hip", "race_common.hpp", "bwd_rows.hpp", "common.hpp"],
     "bwd_rows": ["bwd_rows.hip", "bwd_rows.hpp", "common.hpp"],
-    "gemm": ["gemm.hip", "gemm_index.hpp", "common.hpp"], "gemm_reduce": ["gemm.hip", "gemm_index.hpp"],
+    "gemm_large": ["gemm.hip", "gemm_index.hpp", "common.hpp"], "gemm_small": ["gemm.hip", "gemm_index.hpp", "common.hpp"],
+    "gemm_any": ["gemm.hip", "gemm_index.hpp", "common.hpp"], "gemm_reduce": ["gemm.hip", "gemm_index.hpp"],
     "token_rules_fwd": ["token_rules.hip", "tile.hpp", "common.hpp"],
     "token_rules_bwd": ["token_rules.hip", "tile.hpp", "common.hpp"],
     "token_rules_reduce": ["token_rules.hip"],

@@ -582,9 +582,9 @@ int elsaa_gemm(const elsaa_gemm_desc* d, const void* A, const void* B, void* C, 
     const bool bkn = d->trans_b == 0, out_bf16 = d->c_dtype == ELSAA_BF16;
 #define ELSAA_GEMM_CASE(TA, BKN, OB)                                                                 \
     if (d->trans_a == TA && bkn == BKN && out_bf16 == OB) {                                           \
-        if (p.big) ELSAA_LAUNCH("gemm", (big::gemm_big_kernel<TA, BKN, OB>), grid, block, 0, stream, a); \
-        else if (p.any) ELSAA_LAUNCH("gemm", (gemm_kernel<TA, BKN, OB, true>), grid, block, 0, stream, a); \
-        else ELSAA_LAUNCH("gemm", (gemm_kernel<TA, BKN, OB, false>), grid, block, 0, stream, a);         \
+        if (p.big) ELSAA_LAUNCH("gemm_large", (big::gemm_big_kernel<TA, BKN, OB>), grid, block, 0, stream, a); \
+        else if (p.any) ELSAA_LAUNCH("gemm_any", (gemm_kernel<TA, BKN, OB, true>), grid, block, 0, stream, a); \
+        else ELSAA_LAUNCH("gemm_small", (gemm_kernel<TA, BKN, OB, false>), grid, block, 0, stream, a);   \
     }
     ELSAA_GEMM_CASE(0, 0, 0) ELSAA_GEMM_CASE(0, 0, 1) ELSAA_GEMM_CASE(0, 1, 0) ELSAA_GEMM_CASE(0, 1, 1)
     ELSAA_GEMM_CASE(1, 0, 0) ELSAA_GEMM_CASE(1, 0, 1) ELSAA_GEMM_CASE(1, 1, 0) ELSAA_GEMM_CASE(1, 1, 1)

@@ -34,7 +34,21 @@ def _check(got, ref, out_dtype, what=""):
         assert (err <= bound).all(), f"{what}: worst element ratio {(err / bound).max():.3f}"
 
 
-# ragged and small shapes, and whole tiles
+def _ran(fn):
+    """fn() and the GEMM kernel that it launched: "large" (256 x 256 tiles),
+    "small" (128 x 128) or "any" (128 x 128, element addresses)."""
+    E.profile_enable(True)
+    try:
+        out = fn()
+        torch.cuda.synchronize()
+        kinds = {k[5:] for k in E.profile_read() if k in ("gemm_large", "gemm_small", "gemm_any")}
+    finally:
+        E.profile_enable(False)
+    assert len(kinds) == 1, kinds
+    return out, kinds.pop()
+
+
+# ragged and small shapes, and whole tiles (all on 128 x 128 tiles)
 SHAPES = [(200, 136, 72), (384, 256, 320), (8, 8, 8), (512, 256, 128), (256, 768, 192)]
 
 
@@ -63,17 +77,18 @@ def test_gemm_split_k(ta, od):
     _check(got, oracle.gemm(A, B, ta, False), od, "split-K")
 
 
+@pytest.mark.parametrize("shape,kind", [((256, 512, 8192), "small"), ((1536, 1536, 8192), "large")])
 @pytest.mark.parametrize("ta,tb,od", [(1, 0, torch.float32), (1, 1, torch.bfloat16), (0, 1, torch.float32)])
-def test_gemm_split_k_large_tiles(ta, tb, od):
-    """Whole tiles with a long K, split over K."""
-    M, N, K = 256, 512, 8192
+def test_gemm_split_k_whole_tiles(shape, kind, ta, tb, od):
+    """Whole tiles with a long K, split over K, on each kernel."""
+    M, N, K = shape
     A = W.random_matrix(45 + ta, 1, (K, M) if ta else (M, K))
     B = W.random_matrix(45 + tb, 2, (N, K) if tb else (K, N))
-    got = E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=od)
-    torch.cuda.synchronize()
+    got, ran = _ran(lambda: E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=od))
+    assert ran == kind
     desc = E._GemmDesc(M, N, K, ta, tb, M if ta else K, K if tb else N, N, 0, 0, 0, 0, 0)
     assert E.gemm_workspace_bytes(desc) > 0
-    _check(got, oracle.gemm(A, B, ta, tb), od, "split-K large tiles")
+    _check(got, oracle.gemm(A, B, ta, tb), od, "split-K whole tiles")
 
 
 # large tiles with every edge ragged (M 11 x 256 + 24, N 12 x 256 + 8, K 15 x
@@ -86,8 +101,8 @@ def test_gemm_large_tiles_ragged(shape, ta, tb, od):
     M, N, K = shape
     A = W.random_matrix(46 + ta, 1, (K, M) if ta else (M, K))
     B = W.random_matrix(46 + tb, 2, (N, K) if tb else (K, N))
-    got = E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=od)
-    torch.cuda.synchronize()
+    got, ran = _ran(lambda: E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=od))
+    assert ran == "large"
     _check(got, oracle.gemm(A, B, ta, tb), od, f"{shape}")
 
 
@@ -97,8 +112,8 @@ def test_gemm_many_tiles_short_k(ta, tb):
     M, N, K = 4096, 4096, 40
     A = W.random_matrix(47, 1, (K, M) if ta else (M, K))
     B = W.random_matrix(47, 2, (N, K) if tb else (K, N))
-    got = E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=torch.float32)
-    torch.cuda.synchronize()
+    got, ran = _ran(lambda: E.gemm(_t(A), _t(B), bool(ta), bool(tb), out_dtype=torch.float32))
+    assert ran == "small"
     _check(got, oracle.gemm(A, B, ta, tb), torch.float32, f"K {K}")
 
 
@@ -106,8 +121,8 @@ def test_gemm_short_last_split():
     n, H, dh = 13448, 16, 64
     O = W.random_matrix(48, 1, (1, H, n, dh))
     dY = W.random_matrix(48, 2, (n, H * dh))
-    got = E.gemm(_t(O), _t(dY), trans_a=True, out_dtype=torch.float32)
-    torch.cuda.synchronize()
+    got, ran = _ran(lambda: E.gemm(_t(O), _t(dY), trans_a=True, out_dtype=torch.float32))
+    assert ran == "large"
     _check(got, oracle.gemm(oracle.heads_to_matrix(O), dY, True, False), torch.float32, "dW_O")
 
 
@@ -124,7 +139,8 @@ def test_gemm_head_major_ragged_sequences(Bb, S, H, dh):
     out = torch.empty(Bb, H, S, dh, dtype=torch.bfloat16, device=DEV)
     E.gemm(_t(X), _t(Wm), out=out)
     y = E.gemm(_t(O), _t(Wm), trans_b=True, out_dtype=torch.float32)
-    dw = E.gemm(_t(O), _t(Y), trans_a=True, out_dtype=torch.float32)
+    dw, ran = _ran(lambda: E.gemm(_t(O), _t(Y), trans_a=True, out_dtype=torch.float32))
+    assert ran == ("small" if Bb == 1 or S % 64 == 0 else "any")     # K-tiles that cross sequences
     dw2 = E.gemm(_t(X), _t(O), trans_a=True, out_dtype=torch.float32)
     torch.cuda.synchronize()
     Om = oracle.heads_to_matrix(O)
@@ -143,10 +159,20 @@ def test_gemm_repeatable():
     assert torch.equal(r1, r2)
 
 
-@pytest.mark.parametrize("Bb,S,H,dh", [(2, 96, 4, 16), (2, 256, 4, 64)])
-def test_block_projections_head_major(Bb, S, H, dh):
+# large: the products that take the large kernel.  Sequences of 576 and 448
+# tokens: its row tiles cross sequences and its K-tiles are 64-row pieces of
+# them; of 1024 tokens: whole tiles of several sequences
+@pytest.mark.parametrize("Bb,S,H,dh,large", [
+    (2, 96, 4, 16, ""), (2, 256, 4, 64, ""), (16, 576, 16, 64, "qkv y do dx dwqkv"), (9, 448, 16, 128, "qkv dwo dwqkv"),
+    (8, 1024, 16, 64, "qkv dwqkv")])
+def test_block_projections_head_major(Bb, S, H, dh, large):
     """Every product of one attention block (fwd and bwd) with the attention
     tensors in head-major [B, H, S, dh] storage."""
+    kinds = {}
+
+    def run(name, *a, **kw):
+        out, kinds[name] = _ran(lambda: E.gemm(*a, **kw))
+        return out
     dm = H * dh
     X = W.random_matrix(60, 1, (Bb * S, dm))
     Wqkv = W.random_matrix(60, 2, (dm, 3 * dm), 0.1)
@@ -157,19 +183,19 @@ def test_block_projections_head_major(Bb, S, H, dh):
     bf = torch.bfloat16
     # QKV = X W_qkv, written head-major with 3H heads
     qkv = torch.empty(Bb, 3 * H, S, dh, dtype=bf, device=DEV)
-    E.gemm(_t(X), _t(Wqkv), out=qkv)
+    run("qkv", _t(X), _t(Wqkv), out=qkv)
     # Y = O W_O with O read head-major
-    y = E.gemm(_t(O), _t(Wo), out_dtype=torch.float32)
+    y = run("y", _t(O), _t(Wo), out_dtype=torch.float32)
     # dO = dY W_O^T written head-major
     do = torch.empty(Bb, H, S, dh, dtype=torch.float32, device=DEV)
-    E.gemm(_t(dY), _t(Wo), trans_b=True, out=do)
+    run("do", _t(dY), _t(Wo), trans_b=True, out=do)
     # dW_O = O^T dY with O read head-major and transposed
-    dwo = E.gemm(_t(O), _t(dY), trans_a=True, out_dtype=torch.float32)
+    dwo = run("dwo", _t(O), _t(dY), trans_a=True, out_dtype=torch.float32)
     # dX = dQKV W_qkv^T with dQKV read head-major
-    dx = E.gemm(_t(dQKV), _t(Wqkv), trans_b=True, out_dtype=torch.float32)
+    dx = run("dx", _t(dQKV), _t(Wqkv), trans_b=True, out_dtype=torch.float32)
     # dW_qkv = X^T dQKV with dQKV read head-major
-    dwqkv = E.gemm(_t(X), _t(dQKV), trans_a=True, out_dtype=torch.float32)
-    torch.cuda.synchronize()
+    dwqkv = run("dwqkv", _t(X), _t(dQKV), trans_a=True, out_dtype=torch.float32)
+    assert {n for n, k in kinds.items() if k == "large"} == set(large.split()), kinds
     Om, dQm = oracle.heads_to_matrix(O), oracle.heads_to_matrix(dQKV)
     ref_qkv = oracle.matrix_to_heads(oracle.gemm(X, Wqkv), 3 * H, S)
     _check(qkv, ref_qkv, bf, "qkv")
