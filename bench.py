@@ -109,6 +109,22 @@ def survey_units(w, Lv: int, rules_G: int = 0, rules_lam: bool = False, rules_pa
     return u
 
 
+# launches that do the work of two units
+SHARED_LAUNCHES = {"sort_scan": ("sort", "lowrank_fwd"), "race_rows_bwd": ("bwd_rows", "lowrank_bwd")}
+
+
+def merge_shared(units: dict, launched) -> dict:
+    """The units with those joined ("a+b": bytes, flops and kernels of both)
+    whose work shared one of the launches that ran, so that no unit is
+    charged another one's time."""
+    out = dict(units)
+    for kernel, (a, b) in SHARED_LAUNCHES.items():
+        if kernel in launched and a in out and b in out:
+            (na, fa, ka), (nb, fb, kb) = out.pop(a), out.pop(b)
+            out[f"{a}+{b}"] = (na + nb, fa + fb, ka + kb)
+    return out
+
+
 def kernel_model(w, Lv: int) -> dict:
     """Bytes each sparse-branch kernel actually has to move as the path is
     split into kernels (name -> bytes per step): the survey accounting above
@@ -486,7 +502,7 @@ def main():
     ms_step = elapsed / args.steps * 1e3
     tokens = w.B * w.N * args.steps
     per_step = {name: ms / args.steps for name, (ms, n) in prof.items()}
-    units = survey_units(w, Lv, rules_G, bool(args.rules), rules_part)
+    units = merge_shared(survey_units(w, Lv, rules_G, bool(args.rules), rules_part), prof)
     peak_tf = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_F32_TFLOPS
 
     # per-unit roofline: algorithmic bytes / flops of the unit per step over

@@ -33,6 +33,20 @@ def test_kernel_model_adds_exactly_the_level_partials():
     assert km["sparse_bwd_levels"] - u["sparse_bwd_levels"][0] == slots * (3 * d * s + 12)
 
 
+def test_units_that_share_a_launch_are_charged_together():
+    """The sort that runs beside the RACE scan, and the row scalars formed in
+    the state pass: one figure each, nothing lost from the step's total."""
+    for w, Lv in ((W.TINY_FP32, 0), (W.CAUSAL_16K, 6)):
+        u = bench.survey_units(w, Lv)
+        m = bench.merge_shared(u, {"sort_scan", "race_rows_bwd", "race_out"})
+        assert set(u) - set(m) == {"sort", "lowrank_fwd", "bwd_rows", "lowrank_bwd"}
+        assert {"race_state_fwd", "race_out", "sort_scan"} <= set(m["sort+lowrank_fwd"][2])
+        assert {"race_rows_bwd", "race_bwd"} <= set(m["bwd_rows+lowrank_bwd"][2])
+        for i in (0, 1):
+            assert sum(v[i] for v in m.values()) == sum(v[i] for v in u.values())
+        assert bench.merge_shared(u, {"sort", "race_scan_fwd", "bwd_rows", "race_state_bwd"}) == u
+
+
 def test_kernel_model_matches_the_counted_traffic():
     """The committed rocprofv3 FETCH_SIZE / WRITE_SIZE summaries, where they
     were taken on the current kernel source, agree with the model within 5%."""
