@@ -48,7 +48,7 @@ struct LbArgs {
     int H, N, L, seg_len, nseg, causal;
     int items;              // B H nseg
     size_t BHN;
-    float two_beta, beta, inv_L;
+    float two_beta, inv_L;
 };
 
 // Non-causal passes only apply the total states: their workgroups hold no
@@ -723,7 +723,7 @@ hipError_t launch_race_bwd(const Shape& s, const float* Uq, const float* Uk, con
     a.W = W_race; a.wt_hi = wt_hi; a.wt_lo = wt_lo; a.items = s.B * s.H * s.nseg;
     a.H = s.H; a.N = s.N; a.L = s.L; a.seg_len = s.seg_len; a.nseg = s.nseg; a.causal = s.causal;
     a.BHN = BHN;
-    a.two_beta = 2.f * s.beta; a.beta = s.beta; a.inv_L = 1.f / (float)s.L;
+    a.two_beta = 2.f * s.beta; a.inv_L = 1.f / (float)s.L;
     a.states_f = states_f; a.states_b = states_b;
     a.du_q = du_q; a.du_k = du_k; a.dv = dv_lr;
     return dispatch<BwdFn>(s, a, st);

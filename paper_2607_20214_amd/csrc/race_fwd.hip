@@ -72,7 +72,7 @@ template <class T, int D>
 struct StageDots {
     using S = typename T::store_t;
     static constexpr int PER = 16 / T::bytes, CH = D / PER, PT = kC * CH / kThreads;
-    static_assert(CH == 8 || CH == 16 || CH == 32, "lanes per row");
+    static_assert(CH == 8 || CH == 16, "lanes per row");
     uint4 u[PT], ol[PT];
     f32x4 os[PT][PER / 4];
     RowIn in[PT];
@@ -103,11 +103,7 @@ struct StageDots {
     __device__ static __forceinline__ float lanes_sum(float v)
     {
         v = dpp(dpp(dpp(v, 0), 1), 2);
-        if constexpr (CH >= 16) v = dpp(v, 3);
-        if constexpr (CH == 32) {
-            const LanePair p = xpair16(v);
-            v = p.lo + p.hi;
-        }
+        if constexpr (CH == 16) v = dpp(v, 3);
         return v;
     }
     __device__ __forceinline__ void store(const RowArgs& r, size_t bh, int t0, int N, S* t, Parts<T, kC>& aw) const
