@@ -1466,22 +1466,23 @@ void launch_level_blocks(const Shape& s, const BArgs& a, hipStream_t st)
     else launch_blocks<T, D, BQ, kLevels, QB, false>("sparse_bwd_levels", a, nbx, s.B * s.H, st);
 }
 
-// Where the leaf's wide dQ is the faster one (whole backwards, d_h 128, us):
-// leaves from 1024 tokens once its tiles give every compute unit one (16
-// heads, one leaf of 2000: 167 -> 154; 32000 tokens, leaves of 4000: step
-// 4820 -> 4606; 24 and 128 tiles: 77 -> 90, 70 -> 74, slower),
-// shorter ones from 448 only where there are many (4096 tiles, leaves of 500:
-// 2199 -> 2166, of 1000: 2271 -> 2207; 256 tiles, leaves of 512: 137 -> 145).
-// Leaves of 256 gain nothing (853 both) and of 174 lose (639 -> 647): half of
-// a 128-query tile is the diagonal.  At d_h 64 a tile's loads and epilogue
-// weigh more and the line is lower (leaves of 200: 392 -> 385, of 250, 256
-// tiles: 66 -> 61, of 256, 512 tiles: 94 -> 92; 174: 321 -> 322, 131: 267 ->
-// 270; 64 tiles: 44 -> 46).
+// Where the leaf's wide dQ is the faster one (the leaf backward with the
+// 64-query form and with the wide one, us).  d_h 128: leaves from 1024 tokens
+// once its tiles give every compute unit one (256 tiles, leaves of 2000: 119 ->
+// 105; 264, of 1387: 98 -> 92), from 2560 tokens two (256 tiles, leaves of 4000:
+// 164 -> 179, 264, of 2775: 171 -> 175; 512, of 4000: 321 -> 311, 528, of 2775: 268 ->
+// 252; 4096 tiles, of 4000: 2437 -> 2238); shorter ones from 448 only where there
+// are many (2048 tiles, leaves of 512: 313 -> 300; 2304, of 700: 380 -> 374; 256
+// tiles, of 512: 50 -> 55): half of a 128-query tile is the diagonal.  At d_h 64 a
+// tile's loads and epilogue weigh more and the line is lower (512 tiles,
+// leaves of 256: 36.0 -> 34.0, of 512: 46.8 -> 45.9, of 2000: 114 -> 107; 4096, of 256:
+// 278 -> 269; but 384 tiles, of 512: 38.8 -> 39.7, of 4000: 161 -> 167; 1536 tiles,
+// leaves of 192: 76.2 -> 77.3).
 bool wide_leaf_dq(const Shape& s)
 {
     const long tiles = (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H;
-    if (s.D == 64) return s.bf16 && s.n_leaf >= 192 && tiles >= 256;
-    return s.bf16 && (s.n_leaf >= 1024 ? tiles >= 256 : s.n_leaf >= 448 && tiles >= 2048);
+    if (s.D == 64) return s.bf16 && s.n_leaf >= 224 && tiles >= 512;
+    return s.bf16 && (s.n_leaf >= 1024 ? tiles >= (s.n_leaf >= 2560 ? 512 : 256) : s.n_leaf >= 448 && tiles >= 2048);
 }
 
 template <class T, int D>

@@ -422,8 +422,8 @@ __global__ __launch_bounds__(kThreads, 3) void sparse_fwd_kernel(Args a)
 // and global loads per score, which (with the per-tile vector work around
 // them) bound the 64-query form where queries see hundreds of keys.  Used
 // for the levels from b = 128 (levels of 16K, b 128: 165 -> 145 us; of 64K,
-// b 256: 535 -> 428; d_h 64, 32K, b 128: 188 -> 172) and for causal leaves
-// from 1024 tokens (leaves of 4000: 802 -> 677 us, 2000: 288 -> 248).  In
+// b 256: 535 -> 428; d_h 64, 32K, b 128: 188 -> 172) and for long causal
+// leaves (of 4000 tokens: 802 -> 677 us, 2000: 288 -> 248; wide_leaf).  In
 // shorter leaves the diagonal tiles' unused halves and the one workgroup in
 // place of two cost more (leaves of 1000: 179 -> 183, of 512 307 -> 330, of
 // 174: 90 -> 119), and the non-causal blocks gain nothing (their rows' gather
@@ -665,11 +665,18 @@ bool wide_levels(const Shape& s)
 {
     return s.bf16 && s.k >= 128 && (long)s.lt.wfirst[s.Lv] * s.B * s.H >= 160;
 }
-// (the leaf also needs two workgroups a compute unit: 512 tiles 179 -> 170 us,
-// 256 tiles 97 -> 103, 128 tiles 56 -> 71)
+// The leaf's kernel in the 64-query form and the wide one, us.  d_h 128, from
+// 1024 tokens: two workgroups a compute unit (512 tiles; leaves of 2000: 92 ->
+// 81, of 4000: 156 -> 138; 704 tiles, leaves of 1387: 82.1 -> 80.9, of 2775: 155 ->
+// 131; 256 tiles, leaves of 2000: 66 -> 73).  At d_h 64 a tile's loads and
+// epilogue weigh more and a last partly filled round costs more: long leaves
+// that fill the chip twice (1056 tiles, leaves of 2775: 124 -> 112; 1024, of 4000:
+// 146 -> 120; but 704, of 2775: 87 -> 95; 768, of 4000: 116 -> 117; 1536, of 2000: 114
+// -> 119; 704, of 1387: 52 -> 56).
 bool wide_leaf(const Shape& s)
 {
-    return s.bf16 && s.n_leaf >= 1024 && (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H >= 512;
+    const long tiles = (long)s.lt.wper_leaf * s.lt.leaves * s.B * s.H;
+    return s.bf16 && (s.D == 64 ? s.n_leaf >= 2560 && tiles >= 1024 : s.n_leaf >= 1024 && tiles >= 512);
 }
 
 template <class T, int D>

@@ -119,8 +119,9 @@ def test_padded_256_key_blocks_keep_float32_sums(N, halves):
 # the forward's 128-query tiles: levels of b >= 128 (from 160 tiles; the first
 # three have fewer and take the 64-query form) whose lists end anywhere in a
 # tile and whose blocks straddle tiles (b = 160, 200), neighbouring blocks,
-# zero tokens; leaves of 1024 and more (from 512 tiles) that end in a tile's
-# first, third and last wave
+# zero tokens; leaves of 1024 and more (from 512 tiles; d_h 64: of 2560 and
+# more, from 1024 tiles, the case below that line takes the 64-query form)
+# that end in a tile's first, third and last wave
 LEVELS, LEAF = "sparse_fwd_levels_wide", "sparse_fwd_leaf_wide"
 WIDE_CASES = [
     (_w("c-bf16-d128-k160-1500", 1, 2, 1500, 128, 160, 64, "bf16", 0), 0, "sparse_fwd_levels"),
@@ -130,7 +131,8 @@ WIDE_CASES = [
     (_w("c-bf16-d64-k200-18x1111-padded", 2, 9, 1111, 64, 200, 64, "bf16", 0, recipe="clustered"), 0, LEVELS),
     (_w("c-bf16-d64-k128-10x1300-nbr1", 1, 10, 1300, 64, 128, 64, "bf16", 0), 1, LEVELS),
     (_w("c-bf16-d128-leaf1025", 1, 32, 2049, 128, 128, 64, "bf16", 1100), 0, LEAF),
-    (_w("c-bf16-d64-leaf1110", 3, 20, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0, LEAF),
+    (_w("c-bf16-d64-leaf1110", 3, 20, 1110, 64, 128, 64, "bf16", 1200, recipe="clustered"), 0, "sparse_fwd_leaf"),
+    (_w("c-bf16-d64-leaf2570", 7, 7, 2570, 64, 128, 64, "bf16", 2600, recipe="clustered"), 0, LEAF),
     (_w("c-bf16-d128-leaf1152-k64", 2, 29, 1152, 128, 64, 64, "bf16", 1152, recipe="clustered"), 0, LEAF),
 ]
 
@@ -140,21 +142,24 @@ def test_ragged_causal_wide_tiles(w, nbr, kernel):
     _check(w, neighbors=nbr, heads={(0, 0), (w.B - 1, w.H - 1)}, launches=[kernel])
 
 
-# the leaf's dQ in 128-query tiles (d_h 64: leaves from 192 and 256 tiles; d_h
+# the leaf's dQ in 128-query tiles (d_h 64: leaves from 224 and 512 tiles; d_h
 # 128: from 1024 and 256 tiles, or 448 and 2048 tiles): W' of 64 columns (r >
 # 128), leaves of one query past a tile, a leaf whose last tiles hold no token,
-# d_h 64 and 128
+# d_h 64 and 128; the last case, below the line, takes the 64-query form
 WIDE_LEAF_BWD_CASES = [
+    _w("c-bf16-d64-r32-leaf225", 4, 16, 900, 64, 64, 32, "bf16", 230, recipe="clustered"),
+    _w("c-bf16-d64-r64-leaf257", 4, 22, 514, 64, 64, 64, "bf16", 260),
     _w("c-bf16-d128-r256-leaf1153", 1, 26, 1153, 128, 128, 256, "bf16", 1200),
     _w("c-bf16-d64-r192-leaf1024", 2, 16, 2047, 64, 64, 192, "bf16", 1030, recipe="clustered"),
-    _w("c-bf16-d64-r32-leaf193", 2, 16, 772, 64, 64, 32, "bf16", 200, recipe="clustered"),
     _w("c-bf16-d128-r16-leaf513", 3, 22, 4099, 128, 64, 16, "bf16", 520),
+    _w("c-bf16-d64-r32-leaf193", 2, 16, 772, 64, 64, 32, "bf16", 200, recipe="clustered"),
 ]
 
 
 @pytest.mark.parametrize("w", WIDE_LEAF_BWD_CASES, ids=[w.name for w in WIDE_LEAF_BWD_CASES])
 def test_ragged_causal_wide_leaf_backward(w):
-    _check(w, heads={(0, 0), (w.B - 1, w.H - 1)}, launches=["sparse_leaf_bwd_wide"])
+    wide = "leaf193" not in w.name
+    _check(w, heads={(0, 0), (w.B - 1, w.H - 1)}, launches=["sparse_leaf_bwd_wide" if wide else "sparse_leaf_bwd"])
 
 
 def test_ragged_causal_with_neighbours():
