@@ -207,9 +207,10 @@ __global__ __launch_bounds__(kThreads, KIND == kStateRows && T::bytes == 2 ? 2 :
                 for (int j = 0; j < DW; ++j) S[ft][j] = T::mma(af, bv[j], S[ft][j]);
                 if (ft % 4 == w) {
                     if constexpr (!T::kSplit) {
+                        float s = 0.f;           // (eight tokens first: a shorter chain of sums)
 #pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            Aacc[ft / 4][0] += BWD ? af[i] * sm.aw.v[0][32 * kk + 8 * g + i] : af[i];
+                        for (int i = 0; i < 8; ++i) s += BWD ? af[i] * sm.aw.v[0][32 * kk + 8 * g + i] : af[i];
+                        Aacc[ft / 4][0] += s;
                     } else if constexpr (BWD) {
                         Aacc[ft / 4] = sm.aw.mma_b(af, 32 * kk + 8 * g, Aacc[ft / 4]);
                     } else {
@@ -343,8 +344,22 @@ __global__ __launch_bounds__((state_waves<D, RP>() * 64), 2) void race_out_kerne
 #pragma unroll
             for (int fs = 0; fs < FS; ++fs) {
                 qf[fs] = TP::row8(sm.phq, qi, 32 * fs + 8 * g);
-                if (fs / (FS / WS) == grp) da = sm.a_state.mma_a(32 * fs + 8 * g, qf[fs], da);
+                if (fs / (FS / WS) == grp) {
+                    if constexpr (T::kSplit) {
+                        da = sm.a_state.mma_a(32 * fs + 8 * g, qf[fs], da);
+                    } else {
+                        // float32: each lane group sums its own features, two
+                        // at a time, and the four parts are added in pairs
+                        // (the matrix cores' one chain of RP products is less
+                        // accurate: d_lr of 784 tokens, 64 features, off by
+                        // 1.43e-7 against 0.91e-7)
+                        const float* as = &sm.a_state.v[0][32 * fs + 8 * g];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) da[0] += qf[fs][i] * as[i] + qf[fs][4 + i] * as[4 + i];
+                    }
+                }
             }
+            if constexpr (!T::kSplit) da[0] = wave_sum16(da[0]);
             float rs = 0.f;
             if (a.causal) {
                 for (int kt = grp; kt < 4; kt += WS) {
