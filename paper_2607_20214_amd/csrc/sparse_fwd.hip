@@ -168,7 +168,9 @@ __device__ __forceinline__ void fuse_rows(const Args& a, size_t bh, int leaf, in
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             os[e] = o8[ps][e] * inv_den;
-            out[e] = os[e] * (gs[ps] * mf) + ol[e] * gl[ps];
+            // (the sparse product is the unrounded one: without gates the
+            // other is exact and the sum is rounded once)
+            out[e] = __builtin_fmaf(os[e], gs[ps] * mf, ol[e] * gl[ps]);
         }
         float* po = a.O_s + row * D + c8;
         *(f32x4*)po = f32x4{os[0], os[1], os[2], os[3]};

@@ -31,3 +31,15 @@ def test_low_rank_denominator(N, d, r, causal):
             den += float(np.sum(ref ** 2))
     say(f"[f32 sums] N={N} d={d} r={r} causal={causal}: {(num / den) ** 0.5:.3e}")
     assert (num / den) ** 0.5 <= 2 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,d,causal", [(784, 64, False), (600, 128, True)])
+def test_fusion_rounds_once(N, d, causal):
+    """Without gates O = m O_s + O_lr from the saved parts with one rounding:
+    the 64-bit sum rounded to float32 (which can differ from the fused
+    product's single rounding only next to a tie of the 64-bit sum)."""
+    w = W.Workload(f"f32-fuse-{N}-{d}", 1, 2, N, d, 64, 32, causal, "f32", recipe="iid", qk_scale=d ** -0.25, seed=98)
+    got, _ = run_gpu_fwd(cfg_of(w), W.make_inputs(w))
+    m, o_s, o_lr = (got[k].astype(np.float64) for k in ("m", "O_s", "O_lr"))
+    once = (m[..., None] * o_s + o_lr).astype(np.float32)
+    assert (got["O"] != once).mean() < 1e-4
