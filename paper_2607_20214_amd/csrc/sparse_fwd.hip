@@ -589,10 +589,8 @@ __global__ __launch_bounds__(kThreads, 2) void sparse_fwd_wide_kernel(Args a)
         for (int m = 0; m < 4; ++m) {
             float pv[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                pv[j] = fast_exp2(fmaf(st[m >> 1][8 * (m & 1) + j], a.tau2, -m_use));
-                psum += pv[j];
-            }
+            for (int j = 0; j < 8; ++j) pv[j] = fast_exp2(fmaf(st[m >> 1][8 * (m & 1) + j], a.tau2, -m_use));
+            psum += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
             const F pf = T::pack(pv);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {

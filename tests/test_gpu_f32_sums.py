@@ -1,16 +1,20 @@
-"""float32 storage keeps the accuracy of blocked sums: the low-rank
-denominator d_lr, a sum of positive terms over the features and the tokens.
+"""Results held in float32 keep the accuracy of blocked sums.
 
-Bar: 2-norm error <= 2 u of the result (u = 2^-24, half a unit in the last
+The low-rank denominator d_lr (float32 storage), a sum of positive terms over
+the features and the tokens: 2-norm error <= 2 u of the result (u = 2^-24, half a unit in the last
 place).  A value carries the roundings of its features (three products and a
 sigmoid pair of a few u each, averaged over the r features and N tokens that
 enter it), of short chains of sums and of the final scaling: 0.9e-7 measured.
 One chain over all r products adds about sqrt(r / 3) u / 2 at r = 64, which
 is past the bar (1.43e-7 measured)."""
+import math
+
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2607_20214_amd as E
 from gpu_util import cfg_of, head_cfg_of, run_gpu_fwd, say
 from paper_2607_20214_amd import workloads as W
 
@@ -43,3 +47,32 @@ def test_fusion_rounds_once(N, d, causal):
     m, o_s, o_lr = (got[k].astype(np.float64) for k in ("m", "O_s", "O_lr"))
     once = (m[..., None] * o_s + o_lr).astype(np.float32)
     assert (got["O"] != once).mean() < 1e-4
+
+
+@pytest.mark.parametrize("N,H,d", [(1024, 64, 128), (2560, 52, 64)])
+def test_wide_leaf_denominator(N, H, d):
+    """One key of weight 1 and the others of 2^-25.5, each of them less than
+    half a unit in the last place of 1: a chain that starts with the first key
+    loses every one it adds, 31 of a lane's first tile (6.5e-7 = 11 u); sums
+    of eight lose three of them (1.1 u).  Rows of the first tile, bar 8 u for
+    log d: those, at most u for each later addition to the first key's sum
+    (the second four, three more eights, the other half wave) and 2 u for the
+    logarithm."""
+    q = torch.zeros(1, H, N, d, device="cuda", dtype=torch.bfloat16)
+    k = torch.zeros_like(q)
+    q[..., 0] = 16.0
+    k[:, :, 1:, 0] = -25.5 * math.log(2.0) * d ** 0.5 / 16.0
+    v = torch.randn(1, H, N, d, device="cuda").bfloat16()
+    cfg = E.Config(B=1, H=H, N=N, d_h=d, k=128, r=32, causal=True, n0=N)
+    E.profile_enable(True)
+    try:
+        lse = E.fwd(cfg, q, k, v, torch.randn(H, 5, d, device="cuda"), torch.randn(H, 2, 4, d, device="cuda"))[1]
+        names = set(E.profile_read())
+    finally:
+        E.profile_enable(False)
+    assert "sparse_fwd_leaf_wide" in names, names
+    s = float(q[0, 0, 1, 0]) * float(k[0, 0, 1, 0]) * d ** -0.5
+    ref = torch.log1p(torch.arange(64, dtype=torch.float64) * math.exp(s))
+    err = (lse[0, :, :64].double().cpu() - ref).abs().max().item()
+    say(f"[f32 sums] wide leaf N={N} d={d}: log d off by {err:.3e}")
+    assert err <= 8 * 2.0 ** -24
