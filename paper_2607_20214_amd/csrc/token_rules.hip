@@ -576,13 +576,11 @@ __global__ __launch_bounds__(256) void token_rules_reduce_kernel(TrRedArgs r)
     float s = 0.f;
     for (int b = 0; b < r.B; ++b) {
         const float* p = r.part + ((size_t)(b * r.H + h) * r.nchunk) * L.stride() + e;
-        for (int c0 = 0; c0 < r.nchunk; c0 += 8) {            // eight loads in flight, added in order
+        for (int c0 = 0; c0 < r.nchunk; c0 += 8) {            // eight loads in flight, added in pairs
             float v[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = c0 + j < r.nchunk ? p[(size_t)(c0 + j) * L.stride()] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (c0 + j < r.nchunk) s += v[j];
+            s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
     }
     const int G = L.G, D = L.D;

@@ -76,3 +76,29 @@ def test_wide_leaf_denominator(N, H, d):
     err = (lse[0, :, :64].double().cpu() - ref).abs().max().item()
     say(f"[f32 sums] wide leaf N={N} d={d}: log d off by {err:.3e}")
     assert err <= 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("B,H,N,G", [(2, 8, 4096, 64), (2, 8, 4096, 0), (1, 4, 16384, 64)])
+def test_token_rule_parameter_sums(B, H, N, G):
+    """dlam_c = sum of dlambda over the tokens: the workgroups' partial sums
+    (32 to 128 per head here) are added in blocks.  An addition's rounding is
+    about 0.4 u of the sum so far, so a chain of K of them gives 0.4 u
+    sqrt(K / 3): 0.7 u for eight blocks and as much inside a workgroup, but
+    1.3 u to 2.6 u for the partial sums in one chain.  Bar 1.4 u."""
+    errs = []
+    for seed in range(4):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+
+        def rand(*shape):
+            return torch.randn(*shape, generator=g, device="cuda")
+        p = dict(lam_w=rand(H, 64) * 0.1, lam_b=rand(H) * 0.1, lam_c=rand(H).abs() + 0.1)
+        if G:
+            p.update(W1=rand(H, G, 64) * 0.1, b1=rand(H, G) * 0.1, W2=rand(H, 2, G) * 0.1, b2=rand(H, 2) * 0.1)
+        q, dl = rand(B, H, N, 64).bfloat16(), rand(B, H, N) + 2
+        cfg = E.Config(B=B, H=H, N=N, d_h=64, k=64, r=32, causal=True)
+        got = E.token_rules_bwd(cfg, E.TokenRules(**p), q, rand(B, H, N, 2) if G else None, dl)["dlam_c"]
+        ref = dl.double().sum((0, 2))
+        errs.append(((got.double() - ref) / ref).pow(2).mean().item())
+    err = float(np.mean(errs)) ** 0.5
+    say(f"[f32 sums] dlam_c B={B} H={H} N={N} G={G}: {err:.3e}")
+    assert err <= 1.4 * 2.0 ** -24
