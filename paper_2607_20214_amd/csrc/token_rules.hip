@@ -48,15 +48,15 @@ struct TrArgs {
     int H, N, nchunk, chunk_rows;
 };
 
-// sigmoid(x) from e = exp(-|x|) in (0, 1] and one reciprocal refined by a
-// Newton step (within an ulp; a full division takes ten more instructions,
-// and the two layers evaluate this 80 to 160 times per row tile and lane)
+// sigmoid(x) = n / (1 + e) with e = exp(-|x|) in (0, 1], n = 1 or e: one
+// reciprocal and a quotient corrected by its remainder, as accurate as a full
+// division, which takes ten more instructions (the two layers evaluate this 80
+// to 160 times per row tile and lane)
 __device__ __forceinline__ float sigm(float x)
 {
-    const float e = __expf(-fabsf(x)), d = 1.f + e;
-    float r = __builtin_amdgcn_rcpf(d);
-    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
-    return x >= 0.f ? r : e * r;
+    const float e = __expf(-fabsf(x)), d = 1.f + e, n = x >= 0.f ? 1.f : e;
+    const float r = __builtin_amdgcn_rcpf(d), q = n * r;
+    return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
 }
 
 template <class T, int D, int G, bool LAM>

@@ -102,3 +102,21 @@ def test_token_rule_parameter_sums(B, H, N, G):
     err = float(np.mean(errs)) ** 0.5
     say(f"[f32 sums] dlam_c B={B} H={H} N={N} G={G}: {err:.3e}")
     assert err <= 1.4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_token_rule_sigmoid(dtype):
+    """With W2 = 0 the gates are sigmoid(b2) and nothing else.  For x in [-1, 0]
+    the rounding of 1 + e (2.1e-8 of it, rms), of the quotient (2.4e-8) and
+    of the exponential (2.4e-8 of what is left of it) come to 4.0e-8; one more
+    rounded product, as in e times a reciprocal, to 4.7e-8.  Bar 4.3e-8."""
+    H = 512
+    b2 = torch.linspace(-1, 0, 2 * H, device="cuda").view(H, 2)
+    zero = [torch.zeros(*s, device="cuda") for s in ((H, 64, 64), (H, 64), (H, 2, 64))]
+    cfg = E.Config(B=1, H=H, N=64, d_h=64, k=64, r=32, causal=True, dtype=dtype)
+    q = torch.zeros(1, H, 64, 64, device="cuda", dtype=cfg.torch_dtype)
+    gates, _ = E.token_rules_fwd(cfg, E.TokenRules(W1=zero[0], b1=zero[1], W2=zero[2], b2=b2), q)
+    ref = torch.sigmoid(b2.double())
+    err = ((gates[0, :, 0].double() - ref) / ref).pow(2).mean().sqrt().item()
+    say(f"[f32 sums] sigmoid {dtype}: {err:.3e}")
+    assert err <= 4.3e-8
